@@ -135,7 +135,7 @@ static void batch_release(qk_mps_batch *b) {
   (void)hipGetDevice(&cur);
   (void)hipSetDevice(b->device);
   void *ptrs[] = {b->f64,          b->f32,        b->sbf16,       b->si8,       b->dims_dev,
-                  b->pad_dev,      b->site_off_dev, b->split_off_dev, b->i8_off_dev, b->disc_dev,
+                  b->pad_dev,      b->bond_dev,    b->site_off_dev, b->split_off_dev, b->i8_off_dev, b->disc_dev,
                   b->maxdisc_dev,  b->degen_dev,   b->unconv_dev};
   // the batch may still be in use by enqueued work: wait before the memory
   // goes back to the allocator
@@ -145,7 +145,7 @@ static void batch_release(qk_mps_batch *b) {
   delete b;
 }
 
-qk_status batch_create(int64_t n, int32_t m, const std::vector<int32_t> &pad,
+qk_status batch_create(int64_t n, int32_t m, const std::vector<int32_t> &pad, const std::vector<int32_t> &bond,
                        hipStream_t stream, qk_mps_batch **out, bool with_f64) {
   auto *b = new qk_mps_batch();
   if (hipGetDevice(&b->device) != hipSuccess) {
@@ -156,6 +156,7 @@ qk_status batch_create(int64_t n, int32_t m, const std::vector<int32_t> &pad,
   b->n = n;
   b->m = m;
   b->pad = pad;
+  b->bond = bond;
   compute_layout(b);
   auto alloc = [&](void **p, size_t bytes) -> bool {
     if (bytes == 0) bytes = 16;
@@ -167,6 +168,7 @@ qk_status batch_create(int64_t n, int32_t m, const std::vector<int32_t> &pad,
   bool good = (!with_f64 || alloc((void **)&b->f64, sizeof(double2) * nn * size_t(b->mps_stride))) &&
               alloc((void **)&b->dims_dev, sizeof(int32_t) * nn * size_t(m + 1)) &&
               alloc((void **)&b->pad_dev, sizeof(int32_t) * size_t(m + 1)) &&
+              alloc((void **)&b->bond_dev, sizeof(int32_t) * size_t(m + 1)) &&
               alloc((void **)&b->site_off_dev, sizeof(int64_t) * size_t(m + 1)) &&
               alloc((void **)&b->split_off_dev, sizeof(int64_t) * size_t(m + 1)) &&
               alloc((void **)&b->i8_off_dev, sizeof(int64_t) * size_t(m + 1)) &&
@@ -181,6 +183,7 @@ qk_status batch_create(int64_t n, int32_t m, const std::vector<int32_t> &pad,
                                " x " + std::to_string(m) + " sites");
   }
   if (hipMemcpyAsync(b->pad_dev, pad.data(), sizeof(int32_t) * (m + 1), hipMemcpyHostToDevice, stream) != hipSuccess ||
+      hipMemcpyAsync(b->bond_dev, bond.data(), sizeof(int32_t) * (m + 1), hipMemcpyHostToDevice, stream) != hipSuccess ||
       hipMemcpyAsync(b->site_off_dev, b->site_off.data(), sizeof(int64_t) * (m + 1), hipMemcpyHostToDevice, stream) != hipSuccess ||
       hipMemcpyAsync(b->split_off_dev, b->split_off.data(), sizeof(int64_t) * (m + 1), hipMemcpyHostToDevice, stream) != hipSuccess ||
       hipMemcpyAsync(b->i8_off_dev, b->i8_off.data(), sizeof(int64_t) * (m + 1), hipMemcpyHostToDevice, stream) != hipSuccess ||
@@ -322,6 +325,14 @@ qk_status launch_repad_f64(const qk_mps_batch *src, qk_mps_batch *dst, hipStream
 }  // namespace qk
 }
 
+// Largest bond of n profiles of m + 1 bonds at each cut (1 for none).
+static std::vector<int32_t> largest_bonds(const int32_t *dims, int64_t n, int m) {
+  std::vector<int32_t> bond(m + 1, 1);
+  for (int64_t i = 0; i < n; ++i)
+    for (int l = 0; l <= m; ++l) bond[l] = std::max(bond[l], dims[i * (m + 1) + l]);
+  return bond;
+}
+
 // The simulation allocates for the largest bonds its chi cap allows; once
 // the states are known, the batch is re-laid with the pads of the bonds they
 // reached (pad of the largest bond at each site), so Gram kernels of the
@@ -334,13 +345,16 @@ static qk_status shrink_to_bonds(qk_mps_batch **pb, hipStream_t stream) {
   std::vector<int32_t> dims(size_t(b->n) * (m + 1));
   QK_HIP_CHECK(hipMemcpyAsync(dims.data(), b->dims_dev, sizeof(int32_t) * dims.size(), hipMemcpyDeviceToHost, stream));
   QK_HIP_CHECK(hipStreamSynchronize(stream));
-  std::vector<int32_t> pad(m + 1, 1);
-  for (int64_t i = 0; i < b->n; ++i)
-    for (int l = 0; l <= m; ++l) pad[l] = std::max(pad[l], dims[size_t(i) * (m + 1) + l]);
-  for (int l = 0; l <= m; ++l) pad[l] = std::min(pad_of(pad[l]), b->pad[l]);
-  if (pad == b->pad) return QK_OK;
+  std::vector<int32_t> bond = largest_bonds(dims.data(), b->n, m), pad(m + 1);
+  for (int l = 0; l <= m; ++l) pad[l] = std::min(pad_of(bond[l]), b->pad[l]);
+  if (pad == b->pad) {
+    b->bond = bond;
+    QK_HIP_CHECK(hipMemcpyAsync(b->bond_dev, b->bond.data(), sizeof(int32_t) * bond.size(), hipMemcpyHostToDevice, stream));
+    QK_HIP_CHECK(hipStreamSynchronize(stream));
+    return QK_OK;
+  }
   qk_mps_batch *c = nullptr;
-  qk_status st = batch_create(b->n, m, pad, stream, &c);
+  qk_status st = batch_create(b->n, m, pad, bond, stream, &c);
   if (st != QK_OK) return st;
   st = launch_repad_f64(b, c, stream);
   const size_t n = size_t(b->n);
@@ -388,7 +402,7 @@ static qk_status simulate_impl(const double *features_dev, int64_t n_points, con
     pad[l] = pad_of(int(std::min<int64_t>(chi_max, cap)));
   }
   qk_mps_batch *b = nullptr;
-  st = batch_create(n_points, m, pad, stream, &b);
+  st = batch_create(n_points, m, pad, pad, stream, &b);
   if (st != QK_OK) return st;
   auto gates = compile_circuit(*spec);
   st = run_simulation(b, features_dev, gates, *spec, chi_max, cutoff, stream, fn, user, every, graph_circuits,
@@ -410,6 +424,14 @@ static qk_status check_pair_batches(const qk_mps_batch *a, const qk_mps_batch *b
   if (a->device != dev || b->device != dev)
     return fail(QK_EINVAL, "batch lives on another device than the current one");
   return QK_OK;
+}
+
+static int max_pad_of(const qk_mps_batch *x) {
+  return *std::max_element(x->pad.begin(), x->pad.end());
+}
+
+static int max_bond_of(const qk_mps_batch *x) {
+  return *std::max_element(x->bond.begin(), x->bond.end());
 }
 
 static qk_status make_job(const qk_mps_batch *a, int64_t a0, int64_t na, const qk_mps_batch *b,
@@ -471,12 +493,11 @@ static qk_status make_job(const qk_mps_batch *a, int64_t a0, int64_t na, const q
   job->upper = upper ? 1 : 0;
   job->tiles_i = 0;
   job->tiles_j = 0;
-  job->pair_begin = 0;
+  job->a_bond = am->bond_dev;
+  job->b_bond = bm->bond_dev;
+  job->max_bond = std::max(max_bond_of(am), max_bond_of(bm));
+  job->max_pad = std::max(max_pad_of(am), max_pad_of(bm));
   return QK_OK;
-}
-
-static int max_pad_of(const qk_mps_batch *x) {
-  return *std::max_element(x->pad.begin(), x->pad.end());
 }
 
 // Entries and algorithmic flops of one Gram job.  An overlap costs, per site
@@ -709,7 +730,7 @@ qk_status mps_batch_import(const double *tensors_host, const int32_t *dims_host,
   std::vector<int32_t> pad(m + 1);
   for (int l = 0; l <= m; ++l) pad[l] = pad_of(maxd[l]);
   qk_mps_batch *b = nullptr;
-  qk_status st = batch_create(n, m, pad, stream, &b);
+  qk_status st = batch_create(n, m, pad, maxd, stream, &b);
   if (st != QK_OK) return st;
   std::vector<double2> host(size_t(std::max<int64_t>(n, 1)) * size_t(b->mps_stride), double2{0.0, 0.0});
   const double *src = tensors_host;
@@ -858,7 +879,7 @@ qk_status mps_batch_gather(const qk_mps_batch *src, const int64_t *idx_host, int
     if (idx_host[k] < 0 || idx_host[k] >= src->n) return fail(QK_EINVAL, "gather index out of range");
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
   qk_mps_batch *b = nullptr;
-  qk_status st = batch_create(count, src->m, src->pad, stream, &b, (forms & QK_FORM_FP64) != 0);
+  qk_status st = batch_create(count, src->m, src->pad, src->bond, stream, &b, (forms & QK_FORM_FP64) != 0);
   if (st != QK_OK) return st;
   b->n_two_qubit_gates = src->n_two_qubit_gates;
   const size_t nn = size_t(std::max<int64_t>(count, 1));
@@ -1010,7 +1031,7 @@ qk_status mps_batch_load(const char *path, void *hip_stream, qk_mps_batch **out)
       if (d[l] < 1 || d[l] > pad[l]) return fail(QK_EINVAL, "bond dimension outside [1, pad]");
   }
   qk_mps_batch *b = nullptr;
-  qk_status st = batch_create(n, m, pad, stream, &b);
+  qk_status st = batch_create(n, m, pad, largest_bonds(dims.data(), n, m), stream, &b);
   if (st != QK_OK) return st;
   b->n_two_qubit_gates = hdr32[1];
   const size_t per = sizeof(double2) * size_t(b->mps_stride);

@@ -126,10 +126,10 @@ constexpr size_t kGramCounterBytes = sizeof(unsigned long long) * kQueues * kCou
 // Decode the next pair of this workgroup's queue.  Returns false when the
 // queue is empty; *valid is false for pairs outside the job's range or below
 // the diagonal.
-__device__ inline bool next_pair(const GramJobDev *jobs, const GramTile *tiles, int64_t n_tiles, int nq, int side,
-                                 unsigned long long *counters, int64_t *s_slot, int *job, int64_t *i,
+__device__ inline bool next_pair(const GramJobDev *jobs, const GramTile *tiles, int64_t n_tiles, int nq, int th,
+                                 int tw, unsigned long long *counters, int64_t *s_slot, int *job, int64_t *i,
                                  int64_t *j, bool *valid) {
-  const int tile_pairs = side * side;
+  const int tile_pairs = th * tw;
   const int x = int(blockIdx.x % unsigned(nq));
   if (threadIdx.x == 0) *s_slot = int64_t(atomicAdd(counters + x * kCounterStride, 1ull));
   __syncthreads();
@@ -145,8 +145,8 @@ __device__ inline bool next_pair(const GramJobDev *jobs, const GramTile *tiles, 
   const GramTile t = tiles[tile];
   const int q = int(p % tile_pairs);
   const GramJobDev &J = jobs[t.job];
-  const int64_t li = int64_t(t.ti) * side + q / side;
-  const int64_t lj = int64_t(t.tj) * side + q % side;
+  const int64_t li = int64_t(t.ti) * th + q / tw;
+  const int64_t lj = int64_t(t.tj) * tw + q % tw;
   *job = t.job;
   *i = li;
   *j = lj;
@@ -430,6 +430,348 @@ __device__ void overlap_wide(const GramJobDev &J, int64_t ia, int64_t ib, T2 *E0
   ov_im = r.y;
   ov_exp = expacc;
   __syncthreads();   // every wave has read the result before the next pair overwrites it
+}
+
+// ------------------------------------------------------------------------
+// FP64 / FP32 forms at small bonds: one wave per pair, everything in
+// registers.  MFMA accumulator rows are the operand rows of the next MFMA
+// (FP64: directly, FP32: after a 4 x 4 transpose between the lane rows and
+// the four registers), so E passes from site to site without LDS or a
+// barrier, and the loops stop at the batch's largest bond of each site, not
+// at its pad.  Bounds: MFMA issue where the pairs fill the chip (a bond-32
+// FP64 site takes 384 MFMAs of 64 cycles), else the chain of one site's
+// dependent MFMAs and loads.
+// Largest magnitude exponent of the wave's values: bits are the sign-less
+// upper halves, whose order is the order of magnitudes.
+__device__ inline uint32_t wave_max_bits(uint32_t v) {
+  auto step = [&](uint32_t o) { v = v > o ? v : o; };
+  step(uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x128, 0xf, 0xf, true)));   // row_ror 8, 4, 2, 1
+  step(uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x124, 0xf, 0xf, true)));
+  step(uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x122, 0xf, 0xf, true)));
+  step(uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x121, 0xf, 0xf, true)));
+  auto a = __builtin_amdgcn_permlane16_swap(int(v), int(v), false, false);
+  v = uint32_t(a[0]) > uint32_t(a[1]) ? uint32_t(a[0]) : uint32_t(a[1]);
+  a = __builtin_amdgcn_permlane32_swap(int(v), int(v), false, false);
+  return uint32_t(a[0]) > uint32_t(a[1]) ? uint32_t(a[0]) : uint32_t(a[1]);
+}
+
+// 4 x 4 transpose between the four registers and the four lane rows: out
+// register q of row g is in register g of row q.
+__device__ inline void rows_to_regs(f32x4 &v) {
+  auto sw32 = [](float &a, float &b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(a), __float_as_int(b), false, false);
+    a = __int_as_float(int(r[0]));
+    b = __int_as_float(int(r[1]));
+  };
+  auto sw16 = [](float &a, float &b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(a), __float_as_int(b), false, false);
+    a = __int_as_float(int(r[0]));
+    b = __int_as_float(int(r[1]));
+  };
+  float r0 = v[0], r1 = v[1], r2 = v[2], r3 = v[3];
+  sw32(r0, r2);
+  sw32(r1, r3);
+  sw16(r0, r1);
+  sw16(r2, r3);
+  v = f32x4{r0, r1, r2, r3};
+}
+
+// Exponent of the largest magnitude whose sign-less upper bits are given (0
+// for zero and below the normal range, which is then left unscaled).
+__device__ inline int exp_of_bits(uint32_t bits, double) { return (bits >> 20) ? int(bits >> 20) - 1023 : 0; }
+__device__ inline int exp_of_bits(uint32_t bits, float) { return (bits >> 23) ? int(bits >> 23) - 127 : 0; }
+__device__ inline uint32_t mag_bits(double x) { return uint32_t(__double2hiint(x)) & 0x7fffffffu; }
+__device__ inline uint32_t mag_bits(float x) { return __float_as_uint(x) & 0x7fffffffu; }
+
+// Pairs with bonds up to 16 NT.  E[rt][kt] holds rows 16 rt + j and columns
+// 16 kt + 4 q + g (register q).  Per ket column block: T_s (GEMM1), then its
+// part of E'^T (GEMM2); the site tensors are read in 16-row blocks (zero
+// beyond the bonds).  FP64 forms a complex product by three real ones
+// (Re = P0 - P1, Im = P2 - P0 - P1 with P2 the product of the sums): 25 %
+// fewer MFMAs on the bound resource; FP32 keeps the four products in the
+// order of the kernel for larger bonds, whose results it reproduces bit for
+// bit.
+template <typename T, typename V4, typename T2, int NT>
+__device__ inline void overlap_wave(const GramJobDev &J, int64_t ia, int64_t ib, T &ov_re, T &ov_im, int &ov_exp) {
+  constexpr bool k3 = sizeof(T) == 8;
+  constexpr int NP = k3 ? 3 : 2;   // accumulators of a complex tile
+  const int lane = threadIdx.x & 63;
+  const int j = lane & 15, g = lane >> 4;
+  const T2 *A = reinterpret_cast<const T2 *>(J.a_base) + ia * J.a_stride;
+  const T2 *B = reinterpret_cast<const T2 *>(J.b_base) + ib * J.b_stride;
+  const auto apad = gview(J.a_pad), bpad = gview(J.b_pad), abond = gview(J.a_bond), bbond = gview(J.b_bond);
+  const V4 zero = V4{0, 0, 0, 0};
+  V4 E[NT][NT][2];
+#pragma unroll
+  for (int r = 0; r < NT; ++r)
+#pragma unroll
+    for (int c = 0; c < NT; ++c) E[r][c][0] = E[r][c][1] = zero;
+  if (lane == 0) E[0][0][0][0] = T(1);
+  int expacc = 0;
+  int pa = apad[0], pb = bpad[0], na = 1, nb = 1;   // pads and 16-row block counts at the left bond
+  const int m = J.m;
+  for (int l = 0; l < m; ++l) {
+    const int pan = apad[l + 1], pbn = bpad[l + 1];
+    const int nan = NT == 1 ? 1 : (abond[l + 1] + 15) >> 4, nbn = NT == 1 ? 1 : (bbond[l + 1] + 15) >> 4;
+    V4 En[NT][NT][2];   // E'^T: [ket column block][bra column block]
+    uint32_t mx = 0;
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) {
+      V4 P[NT][NP];
+#pragma unroll
+      for (int at = 0; at < NT; ++at)
+#pragma unroll
+        for (int u = 0; u < NP; ++u) P[at][u] = zero;
+      if (ct < nbn) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          V4 Q[NT][NP];
+#pragma unroll
+          for (int rt = 0; rt < NT; ++rt)
+#pragma unroll
+            for (int u = 0; u < NP; ++u) Q[rt][u] = zero;
+          // GEMM1: T_s[a][b'] = sum_b E[a][b] B_s[b][b']
+#pragma unroll
+          for (int kt = 0; kt < NT; ++kt) {
+            if (kt < nb) {
+              T2 bv[4];
+#pragma unroll
+              for (int q = 0; q < 4; ++q) bv[q] = gload_c(B + (s * pb + 16 * kt + 4 * q + g) * pbn + 16 * ct + j);
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                for (int rt = 0; rt < NT; ++rt) {
+                  if (rt < na) {
+                    const T er = E[rt][kt][0][q], ei = E[rt][kt][1][q];
+                    if constexpr (k3) {
+                      Q[rt][0] = mma(er, bv[q].x, Q[rt][0]);
+                      Q[rt][1] = mma(ei, bv[q].y, Q[rt][1]);
+                      Q[rt][NP - 1] = mma(er + ei, bv[q].x + bv[q].y, Q[rt][NP - 1]);
+                    } else {
+                      Q[rt][0] = mma(er, bv[q].x, Q[rt][0]);
+                      Q[rt][0] = mma(ei, -bv[q].y, Q[rt][0]);
+                      Q[rt][1] = mma(er, bv[q].y, Q[rt][1]);
+                      Q[rt][1] = mma(ei, bv[q].x, Q[rt][1]);
+                    }
+                  }
+                }
+              }
+            }
+          }
+          // GEMM2: E'^T[b'][a'] += sum_a T_s[a][b'] conj(A_s[a][a'])
+#pragma unroll
+          for (int rt = 0; rt < NT; ++rt) {
+            if (rt < na) {
+#pragma unroll
+              for (int at = 0; at < NT; ++at) {
+                if (at < nan) {
+                  T2 av[4];
+#pragma unroll
+                  for (int e = 0; e < 4; ++e)
+                    av[e] = gload_c(A + (s * pa + 16 * rt + acc_row<T>(g, e)) * pan + 16 * at + j);
+#pragma unroll
+                  for (int e = 0; e < 4; ++e) {
+                    if constexpr (k3) {
+                      const T tr = Q[rt][0][e] - Q[rt][1][e];
+                      const T ti = Q[rt][NP - 1][e] - Q[rt][0][e] - Q[rt][1][e];
+                      // re = Tr Ar + Ti Ai; im = (Tr + Ti)(Ar - Ai) - Tr Ar + Ti Ai
+                      P[at][0] = mma(tr, av[e].x, P[at][0]);
+                      P[at][1] = mma(ti, av[e].y, P[at][1]);
+                      P[at][NP - 1] = mma(tr + ti, av[e].x - av[e].y, P[at][NP - 1]);
+                    } else {
+                      const T tr = Q[rt][0][e], ti = Q[rt][1][e];
+                      P[at][0] = mma(tr, av[e].x, P[at][0]);
+                      P[at][0] = mma(ti, av[e].y, P[at][0]);
+                      P[at][1] = mma(ti, av[e].x, P[at][1]);
+                      P[at][1] = mma(-tr, av[e].y, P[at][1]);
+                    }
+                  }
+                }
+              }
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int at = 0; at < NT; ++at) {
+        if constexpr (k3) {
+          En[ct][at][0] = P[at][0] + P[at][1];
+          En[ct][at][1] = P[at][NP - 1] - P[at][0] + P[at][1];
+        } else {
+          En[ct][at][0] = P[at][0];
+          En[ct][at][1] = P[at][1];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t x = mag_bits(En[ct][at][0][e]), y = mag_bits(En[ct][at][1][e]);
+          mx = mx > x ? mx : x;
+          mx = mx > y ? mx : y;
+        }
+      }
+    }
+    // rescale by a power of two (exact) and turn E'^T into the next E
+    const int e2 = exp_of_bits(wave_max_bits(mx), T(0));
+    const T scale = ldexp(T(1), -e2);
+    expacc += e2;
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+      for (int at = 0; at < NT; ++at)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          V4 v = En[ct][at][u];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] *= scale;
+          if constexpr (!k3) rows_to_regs(v);
+          E[at][ct][u] = v;
+        }
+    A += 2 * pa * pan;
+    B += 2 * pb * pbn;
+    pa = pan;
+    pb = pbn;
+    na = nan;
+    nb = nbn;
+  }
+  ov_re = E[0][0][0][0];   // lane 0
+  ov_im = E[0][0][1][0];
+  ov_exp = expacc;
+}
+
+// Bonds up to 4, FP64: four pairs per wave on v_mfma_f64_4x4x4 (four
+// independent 4 x 4 blocks; block b is lanes with (lane >> 2) & 3 == b; A
+// operand [i][k] and B operand [k][j] at lane i (j) + 4 b + 16 k, result
+// [i][j] at lane j + 4 b + 16 i, verified on gfx950).  The result E'^T is
+// the next site's operand E as it stands.  Site tensors are loaded four
+// sites ahead: with bond-2 states a site is 12 MFMAs, far less than a load's
+// latency.
+struct QuadSite {
+  double2 a[2], b[2];   // bra and ket values of this lane, s = 0, 1
+};
+
+__device__ inline void overlap_quad(const GramJobDev &J, int64_t ia, int64_t ib, double &ov_re, double &ov_im,
+                                    int &ov_exp) {
+  constexpr int kAhead = 4;
+  const int lane = threadIdx.x & 63;
+  const int j = lane & 3, k = lane >> 4;
+  const double2 *A = reinterpret_cast<const double2 *>(J.a_base) + ia * J.a_stride;
+  const double2 *B = reinterpret_cast<const double2 *>(J.b_base) + ib * J.b_stride;
+  const auto apad = gview(J.a_pad), bpad = gview(J.b_pad);
+  const int m = J.m;
+  QuadSite w[kAhead];
+  int pa[kAhead + 1], pb[kAhead + 1];   // pads of the group of sites that is loaded next
+#pragma unroll
+  for (int u = 0; u <= kAhead; ++u) {
+    pa[u] = apad[min(u, m)];
+    pb[u] = bpad[min(u, m)];
+  }
+  // loads site u of the group (sites beyond m are not read)
+  auto load = [&](int l, int u) {
+    if (l < m) {
+      const int ra = k * pa[u + 1] + j, rb = k * pb[u + 1] + j, sa = pa[u] * pa[u + 1], sb = pb[u] * pb[u + 1];
+      w[u].a[0] = gload_c(A + ra);
+      w[u].a[1] = gload_c(A + sa + ra);
+      w[u].b[0] = gload_c(B + rb);
+      w[u].b[1] = gload_c(B + sb + rb);
+      A += 2 * sa;
+      B += 2 * sb;
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) load(u, u);
+  double er = lane < 16 && j == 0 ? 1.0 : 0.0, ei = 0.0;   // E[0][0] = 1: lanes 0, 4, 8, 12
+  int expacc = 0;
+  for (int l0 = 0; l0 < m; l0 += kAhead) {
+    pa[0] = pa[kAhead];
+    pb[0] = pb[kAhead];
+#pragma unroll
+    for (int u = 1; u <= kAhead; ++u) {
+      pa[u] = apad[min(l0 + kAhead + u, m)];
+      pb[u] = bpad[min(l0 + kAhead + u, m)];
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      if (l0 + u < m) {
+        double q0 = 0.0, q1 = 0.0, q2 = 0.0;
+        const double es = er + ei;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const double2 a = w[u].a[s], b = w[u].b[s];
+          // T = E B (three real products), then E'^T += T^T conj(A)
+          const double p0 = __builtin_amdgcn_mfma_f64_4x4x4f64(er, b.x, 0.0, 0, 0, 0);
+          const double p1 = __builtin_amdgcn_mfma_f64_4x4x4f64(ei, b.y, 0.0, 0, 0, 0);
+          const double p2 = __builtin_amdgcn_mfma_f64_4x4x4f64(es, b.x + b.y, 0.0, 0, 0, 0);
+          const double tr = p0 - p1, ti = p2 - p0 - p1;
+          q0 = __builtin_amdgcn_mfma_f64_4x4x4f64(tr, a.x, q0, 0, 0, 0);
+          q1 = __builtin_amdgcn_mfma_f64_4x4x4f64(ti, a.y, q1, 0, 0, 0);
+          q2 = __builtin_amdgcn_mfma_f64_4x4x4f64(tr + ti, a.x - a.y, q2, 0, 0, 0);
+        }
+        load(l0 + kAhead + u, u);
+        er = q0 + q1;
+        ei = q2 - q0 + q1;
+        // each block by its own power of two
+        uint32_t mx = max(mag_bits(er), mag_bits(ei));
+        mx = max(mx, uint32_t(__builtin_amdgcn_mov_dpp(int(mx), 0xB1, 0xf, 0xf, true)));   // quad_perm [1,0,3,2]
+        mx = max(mx, uint32_t(__builtin_amdgcn_mov_dpp(int(mx), 0x4E, 0xf, 0xf, true)));   // quad_perm [2,3,0,1]
+        auto x = __builtin_amdgcn_permlane16_swap(int(mx), int(mx), false, false);
+        mx = max(uint32_t(x[0]), uint32_t(x[1]));
+        x = __builtin_amdgcn_permlane32_swap(int(mx), int(mx), false, false);
+        mx = max(uint32_t(x[0]), uint32_t(x[1]));
+        const int e2 = exp_of_bits(mx, 0.0);
+        er = ldexp(er, -e2);
+        ei = ldexp(ei, -e2);
+        expacc += e2;
+      }
+    }
+  }
+  ov_re = er;   // lanes 0, 4, 8, 12
+  ov_im = ei;
+  ov_exp = expacc;
+}
+
+// Pairs of a wave kernel: one-wave workgroups take units (one pair, or four
+// neighbouring columns of one row at bonds up to 4) from the atomic queue;
+// the next unit's index is fetched while the current one is contracted.
+template <typename T, int NT>
+__global__ __launch_bounds__(64, NT == 2 ? 2 : 4) void gram_wave_kernel(const GramJobDev *__restrict__ jobs,
+                                                                         const GramTile *__restrict__ tiles,
+                                                                         int64_t n_units, int th, int tw,
+                                                                         unsigned long long *counter) {
+  constexpr int kPer = NT == 0 ? 4 : 1;   // pairs per unit
+  const int lane = threadIdx.x;
+  const int upt = th * tw / kPer;   // units per tile (tw is a multiple of 4)
+  int64_t next = int64_t(blockIdx.x);   // the first unit of each workgroup is its index
+  while (next < n_units) {
+    const int64_t u = next;
+    unsigned long long f = 0;
+    if (lane == 0) f = atomicAdd(counter, 1ull);
+    const GramTile t = tiles[u / upt];
+    const int q = int(u % upt) * kPer;
+    const GramJobDev &J = jobs[t.job];
+    const int64_t li = int64_t(t.ti) * th + q / tw;
+    const int64_t lj = int64_t(t.tj) * tw + q % tw;
+    if constexpr (NT == 0) {
+      const int64_t ljb = lj + ((lane >> 2) & 3);
+      auto ok = [&](int64_t c) { return li < J.na && c < J.nb && (!J.upper || J.b0 + c >= J.a0 + li); };
+      if (ok(lj) || ok(lj + 3) || ok(lj + 1) || ok(lj + 2)) {
+        double re, im;
+        int ex;
+        overlap_quad(J, J.a0 + li, J.b0 + (ljb < J.nb ? ljb : J.nb - 1), re, im, ex);
+        if (lane < 16 && (lane & 3) == 0 && ok(ljb)) write_k(J, li, ljb, ldexp(re * re + im * im, 2 * ex));
+      }
+    } else if (li < J.na && lj < J.nb && (!J.upper || J.b0 + lj >= J.a0 + li)) {
+      T re, im;
+      int ex;
+      if constexpr (sizeof(T) == 8) {
+        overlap_wave<double, f64x4, double2, NT>(J, J.a0 + li, J.b0 + lj, re, im, ex);
+        if (lane == 0) write_k(J, li, lj, ldexp(re * re + im * im, 2 * ex));
+      } else {
+        overlap_wave<float, f32x4, float2, NT>(J, J.a0 + li, J.b0 + lj, re, im, ex);
+        if (lane == 0) write_k(J, li, lj, ldexp(double(re) * re + double(im) * im, 2 * ex));
+      }
+    }
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(f)), hi = __builtin_amdgcn_readfirstlane(uint32_t(f >> 32));
+    next = int64_t((uint64_t(hi) << 32) | lo) + int64_t(gridDim.x);
+  }
 }
 
 // A pointer that is the same in every lane, moved to scalar registers.
@@ -1197,7 +1539,7 @@ constexpr int threads_of() {
 template <int PREC, int MAXP>
 __global__ __launch_bounds__(threads_of<PREC>(), 2) void gram_kernel(const GramJobDev *__restrict__ jobs,
                                                         const GramTile *__restrict__ tiles,
-                                                        int64_t n_tiles, int nq, int side,
+                                                        int64_t n_tiles, int nq, int th, int tw,
                                                         unsigned long long *counters) {
   extern __shared__ __align__(16) uint8_t smem[];
   __shared__ int64_t s_slot;
@@ -1209,7 +1551,7 @@ __global__ __launch_bounds__(threads_of<PREC>(), 2) void gram_kernel(const GramJ
   int job;
   int64_t i, j;
   bool valid;
-  while (next_pair(jobs, tiles, n_tiles, nq, side, counters, &s_slot, &job, &i, &j, &valid)) {
+  while (next_pair(jobs, tiles, n_tiles, nq, th, tw, counters, &s_slot, &job, &i, &j, &valid)) {
     if (!valid) continue;
     const GramJobDev &J = jobs[job];
     double k;
@@ -1251,8 +1593,8 @@ size_t lds_bytes() {
 
 template <int PREC, int MAXP>
 qk_status launch_one(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int64_t n_tiles,
-                     unsigned long long *counters, const GramConfig &cfg, hipStream_t stream, int *grid_out,
-                     hipEvent_t ev0, hipEvent_t ev1) {
+                     unsigned long long *counters, const GramConfig &cfg, int th, int tw, hipStream_t stream,
+                     int *grid_out) {
   int dev = 0, cus = 256;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -1264,14 +1606,12 @@ qk_status launch_one(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int6
   QK_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads_of<PREC>(), lds));
   per_cu = std::max(per_cu, 1);
   int64_t grid = int64_t(cus) * per_cu;
-  grid = std::min<int64_t>(grid, std::max<int64_t>(n_tiles * cfg.tile_side * cfg.tile_side, 1));
+  grid = std::min<int64_t>(grid, std::max<int64_t>(n_tiles * th * tw, 1));
   // every queue needs workgroups: at most one queue per workgroup
   const int nq = int(std::min<int64_t>(cfg.queues, grid));
-  if (ev0) QK_HIP_CHECK(hipEventRecord(ev0, stream));
   hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(threads_of<PREC>()), lds, stream, jobs_dev, tiles_dev,
-                     n_tiles, nq, cfg.tile_side, counters);
+                     n_tiles, nq, th, tw, counters);
   QK_HIP_CHECK(hipGetLastError());
-  if (ev1) QK_HIP_CHECK(hipEventRecord(ev1, stream));
   *grid_out = int(grid);
   return QK_OK;
 }
@@ -1283,14 +1623,14 @@ constexpr size_t kWideSlot = size_t(2) * kWideP * kWideP;   // complex elements 
 template <int PREC>
 __global__ __launch_bounds__(kWideThreads, 1) void gram_wide_kernel(const GramJobDev *__restrict__ jobs,
                                                                   const GramTile *__restrict__ tiles,
-                                                                  int64_t n_tiles, int nq, int side,
+                                                                  int64_t n_tiles, int nq, int th, int tw,
                                                                   unsigned long long *counters, uint8_t *escratch) {
   __shared__ int64_t s_slot;
   __shared__ double s_red[kWideWaves];
   int job;
   int64_t i, j;
   bool valid;
-  while (next_pair(jobs, tiles, n_tiles, nq, side, counters, &s_slot, &job, &i, &j, &valid)) {
+  while (next_pair(jobs, tiles, n_tiles, nq, th, tw, counters, &s_slot, &job, &i, &j, &valid)) {
     if (!valid) continue;
     const GramJobDev &J = jobs[job];
     double k;
@@ -1314,8 +1654,8 @@ __global__ __launch_bounds__(kWideThreads, 1) void gram_wide_kernel(const GramJo
 
 template <int PREC>
 qk_status launch_wide(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int64_t n_tiles,
-                      unsigned long long *counters, const GramConfig &cfg, const DevAlloc &al, hipStream_t stream,
-                      int *grid_out, hipEvent_t ev0, hipEvent_t ev1) {
+                      unsigned long long *counters, const GramConfig &cfg, int th, int tw, const DevAlloc &al,
+                      hipStream_t stream, int *grid_out) {
   int dev = 0, cus = 256;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -1324,21 +1664,17 @@ qk_status launch_wide(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int
   QK_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kWideThreads, 0));
   per_cu = std::max(per_cu, 1);
   int64_t grid = int64_t(cus) * per_cu;
-  grid = std::min<int64_t>(grid, std::max<int64_t>(n_tiles * cfg.tile_side * cfg.tile_side, 1));
+  grid = std::min<int64_t>(grid, std::max<int64_t>(n_tiles * th * tw, 1));
   const int nq = int(std::min<int64_t>(cfg.queues, grid));
   // one E / E' slot per workgroup
   const size_t slot = (PREC == QK_FP64 ? sizeof(double2) : sizeof(float2)) * kWideSlot;
   uint8_t *es = static_cast<uint8_t *>(dev_alloc(al, slot * size_t(grid), stream, true));
   if (!es) return fail(QK_ENOMEM, "device allocation of the Gram E scratch failed");
   qk_status st = QK_OK;
-  if (ev0 && hipEventRecord(ev0, stream) != hipSuccess) st = fail(QK_EDEVICE, "event record failed");
-  if (st == QK_OK) {
-    hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(kWideThreads), 0, stream, jobs_dev, tiles_dev, n_tiles, nq,
-                       cfg.tile_side, counters, es);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) st = fail(QK_EDEVICE, std::string("Gram kernel launch -> ") + hipGetErrorString(e));
-  }
-  if (st == QK_OK && ev1 && hipEventRecord(ev1, stream) != hipSuccess) st = fail(QK_EDEVICE, "event record failed");
+  hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(kWideThreads), 0, stream, jobs_dev, tiles_dev, n_tiles, nq, th,
+                     tw, counters, es);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) st = fail(QK_EDEVICE, std::string("Gram kernel launch -> ") + hipGetErrorString(e));
   dev_free(al, es, stream, true);
   *grid_out = int(grid);
   return st;
@@ -1375,6 +1711,41 @@ qk_status noalloc_scratch(void **ptr) {
   return QK_OK;
 }
 
+// Kernel of a job.  The plain forms go by the largest bond of its two
+// batches (the pads are multiples of 32).  The lines lie at the MFMA tile
+// sizes, 4, 16 and two tiles of 16: below a line the next kernel spends its
+// MFMAs on zeros and, with one pair per workgroup, most of its time in
+// barriers and idle waves.  One row of 1,000 165-site pairs at bond 2:
+// 9.34 ms with the workgroup kernel, 0.39 ms at four pairs per wave; 12,880
+// 50-site FP32 pairs at bond 32: 15.5 ms against 7.2 ms at one pair per wave
+// (both whole calls).  At three tiles of 16 the FP64 operands leave no
+// registers for a second wave per SIMD, so larger bonds take a workgroup.
+enum GramKernel { KERNEL_QUAD = 0, KERNEL_WAVE16, KERNEL_WAVE32, KERNEL_BLOCK, KERNEL_WIDE, KERNEL_KINDS };
+
+static int kernel_of(const GramJobDev &J, qk_precision prec) {
+  if (prec != QK_FP64 && prec != QK_FP32) return KERNEL_BLOCK;
+  if (prec == QK_FP64 && J.max_bond <= 4) return KERNEL_QUAD;
+  if (J.max_bond <= 32) return J.max_bond <= 16 ? KERNEL_WAVE16 : KERNEL_WAVE32;
+  return J.max_pad <= 64 ? KERNEL_BLOCK : KERNEL_WIDE;
+}
+
+template <typename T, int NT>
+static qk_status launch_wave(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int64_t n_tiles,
+                             unsigned long long *counters, int th, int tw, hipStream_t stream, int *grid_out) {
+  int dev = 0, cus = 256;
+  (void)hipGetDevice(&dev);
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  auto kern = gram_wave_kernel<T, NT>;
+  int per_cu = 0;
+  QK_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64, 0));
+  const int64_t units = n_tiles * (int64_t(th) * tw / (NT == 0 ? 4 : 1));
+  const int64_t grid = std::min<int64_t>(int64_t(cus) * std::max(per_cu, 1), units);
+  hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(64), 0, stream, jobs_dev, tiles_dev, units, th, tw, counters);
+  QK_HIP_CHECK(hipGetLastError());
+  *grid_out = int(grid);
+  return QK_OK;
+}
+
 qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs_in, int max_pad, qk_precision prec,
                           const GramConfig &cfg, hipStream_t stream, qk_gram_stats *stats, void *ws_given,
                           size_t ws_cap) {
@@ -1386,28 +1757,47 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs_in, int max_pad, q
   if (cfg.maxp < max_pad) return fail(QK_EINVAL, "tile configuration smaller than the batch's bond pads");
   const int side = cfg.tile_side;
   std::vector<GramJobDev> jobs = jobs_in;
+  // One launch per kernel kind that the jobs need: a pair's bits then do not
+  // depend on the jobs it is launched with.  Tiles hold side * side entries;
+  // a kind whose jobs have fewer than `side` rows takes flatter, wider ones.
+  struct Part {
+    size_t tile0 = 0;
+    int64_t n_tiles = 0;
+    int th = 0, tw = 0;
+  } parts[KERNEL_KINDS];
   std::vector<GramTile> tiles;
-  for (size_t k = 0; k < jobs.size(); ++k) {
-    GramJobDev &J = jobs[k];
-    J.tiles_i = (J.na + side - 1) / side;
-    J.tiles_j = (J.nb + side - 1) / side;
-    J.pair_begin = int64_t(tiles.size()) * (side * side);
-    for (int64_t ti = 0; ti < J.tiles_i; ++ti)
-      for (int64_t tj = 0; tj < J.tiles_j; ++tj) {
-        if (J.upper) {
-          // skip tiles entirely below the global diagonal
-          const int64_t max_col = J.b0 + std::min(J.nb, (tj + 1) * side) - 1;
-          const int64_t min_row = J.a0 + ti * side;
-          if (max_col < min_row) continue;
+  for (int kind = 0; kind < KERNEL_KINDS; ++kind) {
+    Part &pt = parts[kind];
+    int64_t rows = 0;
+    for (const GramJobDev &J : jobs)
+      if (kernel_of(J, prec) == kind) rows = std::max(rows, J.na);
+    pt.th = side;
+    while (pt.th > 1 && pt.th / 2 >= rows) pt.th /= 2;
+    pt.tw = side * side / pt.th;
+    pt.tile0 = tiles.size();
+    for (size_t k = 0; k < jobs.size(); ++k) {
+      GramJobDev &J = jobs[k];
+      if (kernel_of(J, prec) != kind) continue;
+      J.tiles_i = (J.na + pt.th - 1) / pt.th;
+      J.tiles_j = (J.nb + pt.tw - 1) / pt.tw;
+      for (int64_t ti = 0; ti < J.tiles_i; ++ti)
+        for (int64_t tj = 0; tj < J.tiles_j; ++tj) {
+          if (J.upper) {
+            // skip tiles entirely below the global diagonal
+            const int64_t max_col = J.b0 + std::min(J.nb, (tj + 1) * pt.tw) - 1;
+            const int64_t min_row = J.a0 + ti * pt.th;
+            if (max_col < min_row) continue;
+          }
+          tiles.push_back(GramTile{int32_t(k), int32_t(ti), int32_t(tj), 0});
         }
-        tiles.push_back(GramTile{int32_t(k), int32_t(ti), int32_t(tj), 0});
-      }
+    }
+    pt.n_tiles = int64_t(tiles.size() - pt.tile0);
   }
   if (stats) {
     stats->tiles = int64_t(tiles.size());
     stats->tile_side = side;
     stats->queues = cfg.queues;
-    stats->block = cfg.maxp;
+    stats->block = parts[KERNEL_WIDE].n_tiles ? kWideP : parts[KERNEL_BLOCK].n_tiles ? 64 : kPadQuantum;
     stats->workgroups = 0;
     stats->kernel_ms = 0.0;
   }
@@ -1415,25 +1805,25 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs_in, int max_pad, q
   const int64_t n_tiles = int64_t(tiles.size());
   const size_t jbytes = sizeof(GramJobDev) * jobs.size();
   const size_t tbytes = sizeof(GramTile) * tiles.size();
-  // workspace: [queue counters | job table | tile list], uploaded in one copy
-  // whose counter bytes are zero (no memset node in the stream)
-  const size_t ws_bytes = kGramCounterBytes + jbytes + tbytes;
+  // workspace: [queue counters of every kind | job table | tile list],
+  // uploaded in one copy whose counter bytes are zero (no memset node in the
+  // stream)
+  const size_t cbytes = kGramCounterBytes * KERNEL_KINDS;
+  const size_t ws_bytes = cbytes + jbytes + tbytes;
   if (ws_given && ws_bytes > ws_cap)
     return fail(QK_EINVAL, "the Gram work queue needs " + std::to_string(ws_bytes) + " bytes (" +
                                std::to_string(n_tiles) + " pair tiles of side " + std::to_string(side) +
                                "), above the " + std::to_string(ws_cap) + "-byte scratch");
   std::vector<uint8_t> host(ws_bytes, 0);
-  std::memcpy(host.data() + kGramCounterBytes, jobs.data(), jbytes);
-  std::memcpy(host.data() + kGramCounterBytes + jbytes, tiles.data(), tbytes);
+  std::memcpy(host.data() + cbytes, jobs.data(), jbytes);
+  std::memcpy(host.data() + cbytes + jbytes, tiles.data(), tbytes);
   const DevAlloc al = allocator_for_current_device();
   uint8_t *ws = static_cast<uint8_t *>(ws_given);
   if (!ws) {
     ws = static_cast<uint8_t *>(dev_alloc(al, ws_bytes, stream, true));
     if (!ws) return fail(QK_ENOMEM, "device allocation of the Gram work queue failed");
   }
-  auto *counters = reinterpret_cast<unsigned long long *>(ws);
-  auto *jobs_dev = reinterpret_cast<GramJobDev *>(ws + kGramCounterBytes);
-  auto *tiles_dev = reinterpret_cast<GramTile *>(ws + kGramCounterBytes + jbytes);
+  auto *jobs_dev = reinterpret_cast<GramJobDev *>(ws + cbytes);
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   qk_status st = QK_OK;
   if (hipMemcpyAsync(ws, host.data(), ws_bytes, hipMemcpyHostToDevice, stream) != hipSuccess ||
@@ -1441,24 +1831,41 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs_in, int max_pad, q
       hipStreamSynchronize(stream) != hipSuccess)
     st = fail(QK_EDEVICE, "upload of the Gram work queue failed");
   if (st == QK_OK && stats &&
-      (hipEventCreate(&ev0) != hipSuccess || hipEventCreate(&ev1) != hipSuccess))
+      (hipEventCreate(&ev0) != hipSuccess || hipEventCreate(&ev1) != hipSuccess ||
+       hipEventRecord(ev0, stream) != hipSuccess))
     st = fail(QK_EDEVICE, "event creation failed");
   int grid = 0;
-  if (st == QK_OK) {
-    if (cfg.maxp == kWideP && (prec == QK_FP64 || prec == QK_FP32))
-      st = prec == QK_FP64 ? launch_wide<QK_FP64>(jobs_dev, tiles_dev, n_tiles, counters, cfg, al, stream, &grid, ev0, ev1)
-                           : launch_wide<QK_FP32>(jobs_dev, tiles_dev, n_tiles, counters, cfg, al, stream, &grid, ev0, ev1);
+  for (int kind = 0; kind < KERNEL_KINDS && st == QK_OK; ++kind) {
+    const Part &pt = parts[kind];
+    if (pt.n_tiles == 0) continue;
+    auto *counters = reinterpret_cast<unsigned long long *>(ws + kGramCounterBytes * kind);
+    auto *tiles_dev = reinterpret_cast<GramTile *>(ws + cbytes + jbytes) + pt.tile0;
+    int wgs = 0;
+    if (kind == KERNEL_QUAD)
+      st = launch_wave<double, 0>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.th, pt.tw, stream, &wgs);
+    else if (kind == KERNEL_WAVE16)
+      st = prec == QK_FP64
+               ? launch_wave<double, 1>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.th, pt.tw, stream, &wgs)
+               : launch_wave<float, 1>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.th, pt.tw, stream, &wgs);
+    else if (kind == KERNEL_WAVE32)
+      st = prec == QK_FP64
+               ? launch_wave<double, 2>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.th, pt.tw, stream, &wgs)
+               : launch_wave<float, 2>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.th, pt.tw, stream, &wgs);
+    else if (kind == KERNEL_WIDE)
+      st = prec == QK_FP64
+               ? launch_wide<QK_FP64>(jobs_dev, tiles_dev, pt.n_tiles, counters, cfg, pt.th, pt.tw, al, stream, &wgs)
+               : launch_wide<QK_FP32>(jobs_dev, tiles_dev, pt.n_tiles, counters, cfg, pt.th, pt.tw, al, stream, &wgs);
     else if (prec == QK_FP64)
-      st = cfg.maxp == 32 ? launch_one<QK_FP64, 32>(jobs_dev, tiles_dev, n_tiles, counters, cfg, stream, &grid, ev0, ev1)
-                          : launch_one<QK_FP64, 64>(jobs_dev, tiles_dev, n_tiles, counters, cfg, stream, &grid, ev0, ev1);
+      st = launch_one<QK_FP64, 64>(jobs_dev, tiles_dev, pt.n_tiles, counters, cfg, pt.th, pt.tw, stream, &wgs);
     else if (prec == QK_FP32)
-      st = cfg.maxp == 32 ? launch_one<QK_FP32, 32>(jobs_dev, tiles_dev, n_tiles, counters, cfg, stream, &grid, ev0, ev1)
-                          : launch_one<QK_FP32, 64>(jobs_dev, tiles_dev, n_tiles, counters, cfg, stream, &grid, ev0, ev1);
+      st = launch_one<QK_FP32, 64>(jobs_dev, tiles_dev, pt.n_tiles, counters, cfg, pt.th, pt.tw, stream, &wgs);
     else if (prec == QK_SPLIT_BF16)
-      st = launch_one<QK_SPLIT_BF16, 64>(jobs_dev, tiles_dev, n_tiles, counters, cfg, stream, &grid, ev0, ev1);
+      st = launch_one<QK_SPLIT_BF16, 64>(jobs_dev, tiles_dev, pt.n_tiles, counters, cfg, pt.th, pt.tw, stream, &wgs);
     else
-      st = launch_one<QK_SPLIT_I8, 64>(jobs_dev, tiles_dev, n_tiles, counters, cfg, stream, &grid, ev0, ev1);
+      st = launch_one<QK_SPLIT_I8, 64>(jobs_dev, tiles_dev, pt.n_tiles, counters, cfg, pt.th, pt.tw, stream, &wgs);
+    grid += wgs;
   }
+  if (st == QK_OK && stats && hipEventRecord(ev1, stream) != hipSuccess) st = fail(QK_EDEVICE, "event record failed");
   if (!ws_given) dev_free(al, ws, stream, true);
   if (st == QK_OK && stats) {
     float ms = 0.f;

@@ -99,6 +99,7 @@ struct qk_mps_batch {
   int64_t n = 0;
   int32_t m = 0;
   std::vector<int32_t> pad;        // m + 1 entries
+  std::vector<int32_t> bond;       // m + 1 entries: no bond of the batch is larger (at most the pad)
   std::vector<int64_t> site_off;   // m + 1 entries (last = mps_stride)
   int64_t mps_stride = 0;          // complex elements per MPS
   std::vector<int64_t> split_off;  // m + 1 entries, bytes
@@ -113,6 +114,7 @@ struct qk_mps_batch {
 
   int32_t *dims_dev = nullptr;     // n * (m + 1)
   int32_t *pad_dev = nullptr;      // m + 1
+  int32_t *bond_dev = nullptr;     // m + 1
   int64_t *site_off_dev = nullptr; // m + 1
   int64_t *split_off_dev = nullptr;// m + 1
   int64_t *i8_off_dev = nullptr;   // m + 1
@@ -126,8 +128,9 @@ struct qk_mps_batch {
 
 namespace qk {
 
-// Allocate a batch with the given pad profile (device memory zeroed).
-qk_status batch_create(int64_t n, int32_t m, const std::vector<int32_t> &pad,
+// Allocate a batch with the given pad profile and largest bonds (device
+// memory zeroed).
+qk_status batch_create(int64_t n, int32_t m, const std::vector<int32_t> &pad, const std::vector<int32_t> &bond,
                        hipStream_t stream, qk_mps_batch **out, bool with_f64 = true);
 qk_status batch_ensure_packed(qk_mps_batch *b, qk_precision prec, hipStream_t stream);
 
@@ -160,8 +163,10 @@ struct GramJobDev {
   int64_t ldk;
   int32_t m;
   int32_t upper;                   // symmetric: only global j >= i
+  const int32_t *a_bond;           // m + 1: largest bond of batch a at each cut
+  const int32_t *b_bond;
+  int32_t max_bond, max_pad;       // over both batches
   int64_t tiles_i, tiles_j;        // tile grid of this job
-  int64_t pair_begin;              // first flat pair index of this job
 };
 
 // Gram kernel configuration: block size of the plain forms (32, 64 or 128), pair

@@ -1,0 +1,110 @@
+"""Gram kernels by bond dimension: four pairs per wave at bonds up to 4
+(FP64), one pair per wave at bonds up to 16 and 32, one pair per workgroup
+above.  Bonds at the edges of each, ragged blocks, single rows, fewer rows
+than a pair tile, and jobs of several kernels in one call, against the
+oracle's overlaps of the same left-canonical states.
+
+Tolerances: FP64 1e-12 (rounding of 13 sites of at most 33 x 33 products,
+~1e-14, with a wide margin); FP32 1e-5 (13 sites x 2 products x sqrt(2 x 33)
+roundings of 6e-8 on K <= 1).
+"""
+import numpy as np
+import pytest
+
+from oracle import gram as ogram
+from tests.gpu_util import require_gpu
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"fp64": 1e-12, "fp32": 1e-5}
+
+
+def random_mps(rng, m, bond, near=None, eps=0.05):
+    """Left-canonical MPS with bonds min(bond, 2^l, 2^(m-l)); close to
+    `near` when given, so that off-diagonal entries are not all zero."""
+    out = []
+    for l in range(m):
+        dl, dr = (min(bond, 2 ** min(x, m - x)) for x in (l, l + 1))
+        z = rng.standard_normal((2 * dl, dr)) + 1j * rng.standard_normal((2 * dl, dr))
+        if near is not None:
+            z = near[l].reshape(2 * dl, dr) + eps * z / np.sqrt(2 * dl)
+        u, r = np.linalg.qr(z)
+        u = u * (np.diag(r) / np.abs(np.diag(r)))[None, :]
+        out.append(u.reshape(dl, 2, dr))
+    return out
+
+
+@pytest.mark.parametrize("bond", [1, 2, 3, 4, 5, 8, 16, 17, 31, 32, 33])
+def test_bonds_vs_oracle(bond):
+    import paper_2411_09336_amd as q
+    require_gpu()
+    rng = np.random.default_rng(bond)
+    m = 13
+    base = random_mps(rng, m, bond)
+    mps = [random_mps(rng, m, bond, base) for _ in range(11)]
+    K_ref = np.array([[abs(ogram.overlap(a, b)) ** 2 for b in mps] for a in mps])
+    b = q.import_batch(mps)
+    for prec, tol in TOL.items():
+        K = q.gram(b, precision=prec).cpu().numpy()
+        print(bond, prec, "max|dK|", np.abs(K - K_ref).max(), "off-diagonal", K_ref[0, 1])
+        assert np.abs(K - K_ref).max() < tol
+        # a single row, and ragged blocks around the four-pair units
+        for a0, na, b0, nb in ((3, 1, 0, 11), (0, 11, 10, 1), (2, 5, 3, 7), (9, 2, 1, 3)):
+            Kb = q.gram_block(b, a0, na, b, b0, nb, precision=prec).cpu().numpy()
+            assert np.abs(Kb - K_ref[a0:a0 + na, b0:b0 + nb]).max() < tol
+
+
+@pytest.mark.parametrize("n,m", [(1, 1), (2, 2), (3, 3), (5, 6), (37, 9)])
+def test_sites_and_sizes(n, m):
+    """Chains shorter than the sites loaded ahead, and triangles that end
+    inside a tile."""
+    import paper_2411_09336_amd as q
+    require_gpu()
+    rng = np.random.default_rng(100 * n + m)
+    for bond in (2, 4, 12):
+        base = random_mps(rng, m, bond)
+        mps = [random_mps(rng, m, bond, base) for _ in range(n)]
+        K_ref = np.array([[abs(ogram.overlap(a, c)) ** 2 for c in mps] for a in mps])
+        b = q.import_batch(mps)
+        for prec, tol in TOL.items():
+            assert np.abs(q.gram(b, precision=prec).cpu().numpy() - K_ref).max() < tol
+
+
+def test_scaled_states():
+    """Unnormalised states (every site scaled by 1e-3 or 1e3): the rescaling
+    by powers of two of each pair keeps FP64 and FP32 in range."""
+    import paper_2411_09336_amd as q
+    require_gpu()
+    rng = np.random.default_rng(5)
+    for bond in (4, 16, 32):
+        mps = [random_mps(rng, 13, bond) for _ in range(3)]
+        scaled = [[t * f for t in a] for a, f in zip(mps, (1e-3, 1.0, 1e3))]
+        norms = np.array([1e-3 ** 13, 1.0, 1e3 ** 13])
+        K_ref = np.array([[abs(ogram.overlap(a, c)) ** 2 for c in mps] for a in mps])
+        b = q.import_batch(scaled)
+        for prec, tol in TOL.items():
+            K = q.gram(b, precision=prec).cpu().numpy() / np.outer(norms, norms) ** 2
+            assert np.abs(K - K_ref).max() < 2 * tol
+
+
+def test_jobs_of_several_kernels():
+    """Jobs at bonds 2, 16, 32 and 40 in one call: the bits of separate
+    calls, for every form that takes them."""
+    import paper_2411_09336_amd as q
+    torch = require_gpu()
+    rng = np.random.default_rng(9)
+    batches = []
+    for bond, m in ((2, 7), (16, 11), (32, 12), (40, 13)):
+        base = random_mps(rng, m, bond)
+        batches.append(q.import_batch([random_mps(rng, m, bond, base) for _ in range(6)]))
+    for prec in ("fp64", "fp32"):
+        jobs = []
+        for b in batches:
+            jobs.append(dict(a=b, b=b, na=6, nb=6, upper_only=True,
+                             out=torch.zeros((6, 6), dtype=torch.float64, device="cuda")))
+            jobs.append(dict(a=b, b=b, a0=1, na=2, b0=0, nb=5,
+                             out=torch.zeros((2, 5), dtype=torch.float64, device="cuda")))
+        q.gram_multi(jobs, precision=prec)
+        for k, b in enumerate(batches):
+            assert torch.equal(jobs[2 * k]["out"], q.gram(b, precision=prec))
+            assert torch.equal(jobs[2 * k + 1]["out"], q.gram_block(b, 1, 2, b, 0, 5, precision=prec))
