@@ -13,7 +13,7 @@
 // Four arithmetic forms:
 //  * FP64 and FP32: plain operands, v_mfma_f64_16x16x4 / v_mfma_f32_16x16x4,
 //    E rescaled by a power of two after every site (exact) against underflow;
-//    four waves per pair, wave w computes E' for the ket column block w.
+//    one wave to eight waves per pair, by the bonds.
 //  * split-BF16 and split-int8: 31-bit fixed-point codes with one exponent
 //    per row (E, T^T) or column (site tensors), cut into four 8-bit digits;
 //    the digit products are carried by bf16 MFMAs (exact leading-digit
@@ -175,126 +175,212 @@ __device__ constexpr int acc_row(int g, int e) {
   return sizeof(T) == 8 ? 4 * e + g : 4 * g + e;
 }
 
+// Largest magnitude exponent of the wave's values: bits are the sign-less
+// upper halves, whose order is the order of magnitudes.
+__device__ inline uint32_t wave_max_bits(uint32_t v) {
+  auto step = [&](uint32_t o) { v = v > o ? v : o; };
+  step(uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x128, 0xf, 0xf, true)));   // row_ror 8, 4, 2, 1
+  step(uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x124, 0xf, 0xf, true)));
+  step(uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x122, 0xf, 0xf, true)));
+  step(uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x121, 0xf, 0xf, true)));
+  auto a = __builtin_amdgcn_permlane16_swap(int(v), int(v), false, false);
+  v = uint32_t(a[0]) > uint32_t(a[1]) ? uint32_t(a[0]) : uint32_t(a[1]);
+  a = __builtin_amdgcn_permlane32_swap(int(v), int(v), false, false);
+  return uint32_t(a[0]) > uint32_t(a[1]) ? uint32_t(a[0]) : uint32_t(a[1]);
+}
+
+// Exponent of the largest magnitude whose sign-less upper bits are given (0
+// for zero and below the normal range, which is then left unscaled).
+__device__ inline int exp_of_bits(uint32_t bits, double) { return (bits >> 20) ? int(bits >> 20) - 1023 : 0; }
+__device__ inline int exp_of_bits(uint32_t bits, float) { return (bits >> 23) ? int(bits >> 23) - 127 : 0; }
+__device__ inline uint32_t mag_bits(double x) { return uint32_t(__double2hiint(x)) & 0x7fffffffu; }
+__device__ inline uint32_t mag_bits(float x) { return __float_as_uint(x) & 0x7fffffffu; }
+
 // ------------------------------------------------------------------------
-// FP64 / FP32 forms.  E in LDS in MFMA A-operand fragment order:
-// fragment (rt, kq) holds E[16 rt + i][4 kq + g] at lane i + 16 g, as an
-// interleaved complex value.
-template <typename T, typename V4, typename T2, int MAXP>
-__device__ void overlap_plain(const GramJobDev &J, int64_t ia, int64_t ib, T2 *E, T *s_red,
-                              T &ov_re, T &ov_im, int &ov_exp) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+// FP64 / FP32 forms at bonds 33 .. 64, one pair per workgroup of four waves;
+// wave w computes E' for the ket column block w.  E in LDS in MFMA A-operand
+// fragment order: fragment (rt, kq) holds E[16 rt + i][4 kq + g] at lane
+// i + 16 g, as an interleaved complex value.  The loops stop at the batches'
+// largest bonds of the site.  FP64 forms a complex product by three real
+// ones (as overlap_wave), FP32 by four.  Bound: MFMA issue.  Site values are
+// loaded one step of MFMAs ahead (12 of 64 cycles in FP64, longer than an L2
+// hit), and the steps of a site are straight-line code where both bonds take
+// all four (or three) 16-row blocks, so that loads are not serialised by
+// branches.  12,880 pairs of 100 sites at bond 64: FP64 211 -> 117 ms (82
+// algorithmic TFLOP/s; 61 by MFMA count of the 78.6 of the matrix cores),
+// FP32 78.9 -> 55.1 ms for 8,256; bond 45: FP64 37.1 -> 12.9 ms for 2,080.
+constexpr int kPlainBlocks = 4;
+
+// One wave's part of a site: ket column block ct, E of nrt x nkq fragments,
+// nat bra column blocks.  F: nrt and nat are both F, or 0: as given.
+template <int F, typename T, typename V4, typename T2>
+__device__ __forceinline__ void plain_site(const T2 *A, const T2 *B, const T2 *E, int pa, int pan, int pb, int pbn,
+                                           int nrt_, int nkq, int nat_, int ct, int lane,
+                                           V4 (&Ep)[kPlainBlocks][sizeof(T) == 8 ? 3 : 2]) {
+  constexpr bool k3 = sizeof(T) == 8;
+  constexpr int NP = k3 ? 3 : 2;   // accumulators of a complex tile
+  constexpr int NT = F ? F : kPlainBlocks;
+  const int nrt = F ? F : nrt_, nat = F ? F : nat_;
   const int j = lane & 15, g = lane >> 4;
-  const T2 *abase = reinterpret_cast<const T2 *>(J.a_base) + ia * J.a_stride;
-  const T2 *bbase = reinterpret_cast<const T2 *>(J.b_base) + ib * J.b_stride;
-  {
-    const int n0 = gview(J.a_pad)[0] * gview(J.b_pad)[0];
-    for (int x = tid; x < n0; x += kThreads) {
-      T2 z;
-      z.x = T(0);
-      z.y = T(0);
-      E[x] = z;
-    }
-    __syncthreads();
-    if (tid == 0) E[0].x = T(1);
-    __syncthreads();
-  }
-  int expacc = 0;
-  constexpr int NT = MAXP / 16;
-  constexpr int CT_PER_WAVE = (NT + 3) / 4;
-  for (int l = 0; l < J.m; ++l) {
-    const int Da = gview(J.a_pad)[l], Dan = gview(J.a_pad)[l + 1], Db = gview(J.b_pad)[l], Dbn = gview(J.b_pad)[l + 1];
-    const T2 *A = abase + gview(J.a_off)[l];
-    const T2 *B = bbase + gview(J.b_off)[l];
-    const int nrt = Da / 16, nkq = Db / 4, nat = Dan / 16, nct = Dbn / 16, nkqn = Dbn / 4;
-    V4 Ep[CT_PER_WAVE][NT][2];
-    T lmax = T(0);
+  const V4 zero = V4{0, 0, 0, 0};
+#pragma unroll 1
+  for (int s = 0; s < 2; ++s) {
+    V4 Q[NT][NP];
 #pragma unroll
-    for (int c = 0; c < CT_PER_WAVE; ++c) {
-      const int ct = wave + 4 * c;
+    for (int rt = 0; rt < NT; ++rt)
 #pragma unroll
-      for (int at = 0; at < NT; ++at) {
-        Ep[c][at][0] = V4{0, 0, 0, 0};
-        Ep[c][at][1] = V4{0, 0, 0, 0};
-      }
-      if (ct >= nct) continue;
+      for (int u = 0; u < NP; ++u) Q[rt][u] = zero;
+    // GEMM1: T_s[a][b'] = sum_b E[a][b] B_s[b][b'],  b' in block ct
+    const T2 *Bc = B + (s * pb + g) * pbn + 16 * ct + j;
+    const T2 *Er = E + lane;
+    T2 bv = gload_c(Bc);
+#pragma unroll (k3 ? 1 : 2)
+    for (int kq = 0; kq < nkq; ++kq) {
+      const T2 b0 = bv;
+      T2 ev[NT];
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        V4 Tt[NT][2];
+      for (int rt = 0; rt < NT; ++rt) ev[rt] = Er[(rt < nrt ? rt : 0) * nkq * 64];
+      Er += 64;
+      if (kq + 1 < nkq) bv = gload_c(Bc + 4 * (kq + 1) * pbn);
+      const T bs = b0.x + b0.y;
 #pragma unroll
-        for (int rt = 0; rt < NT; ++rt) {
-          Tt[rt][0] = V4{0, 0, 0, 0};
-          Tt[rt][1] = V4{0, 0, 0, 0};
-        }
-        // GEMM1: T_s[a][b'] = sum_b E[a][b] B_s[b][b'],  b' in block ct
-        for (int kq = 0; kq < nkq; ++kq) {
-          const T2 bv = gload_c(B + (size_t(s) * Db + 4 * kq + g) * Dbn + 16 * ct + j);
-          const T bneg = -bv.y;
-#pragma unroll
-          for (int rt = 0; rt < NT; ++rt) {
-            if (rt < nrt) {
-              const T2 ev = E[(rt * nkq + kq) * 64 + lane];
-              Tt[rt][0] = mma(ev.x, bv.x, Tt[rt][0]);
-              Tt[rt][0] = mma(ev.y, bneg, Tt[rt][0]);
-              Tt[rt][1] = mma(ev.x, bv.y, Tt[rt][1]);
-              Tt[rt][1] = mma(ev.y, bv.x, Tt[rt][1]);
-            }
+      for (int rt = 0; rt < NT; ++rt) {
+        if (rt < nrt) {
+          Q[rt][0] = mma(ev[rt].x, b0.x, Q[rt][0]);
+          if constexpr (k3) {
+            Q[rt][1] = mma(ev[rt].y, b0.y, Q[rt][1]);
+            Q[rt][NP - 1] = mma(ev[rt].x + ev[rt].y, bs, Q[rt][NP - 1]);
+          } else {
+            Q[rt][1] = mma(ev[rt].x, b0.y, Q[rt][1]);
+            Q[rt][0] = mma(ev[rt].y, -b0.y, Q[rt][0]);
+            Q[rt][1] = mma(ev[rt].y, b0.x, Q[rt][1]);
           }
         }
-        // GEMM2: E'^T[b'][a'] += sum_a T_s[a][b'] conj(A_s[a][a'])
+      }
+    }
+    // GEMM2: E'^T[b'][a'] += sum_a T_s[a][b'] conj(A_s[a][a'])
+    const T2 *Ac = A + s * pa * pan + j;
+    T2 av[2][NT];
+    auto load = [&](int x, T2 (&v)[NT]) {   // rows of step x = 4 rt + e
+      const T2 *arow = Ac + (16 * (x >> 2) + acc_row<T>(g, x & 3)) * pan;
 #pragma unroll
-        for (int rt = 0; rt < NT; ++rt) {
-          if (rt < nrt) {
+      for (int at = 0; at < NT; ++at)
+        if (at < nat) v[at] = gload_c(arow + 16 * at);
+    };
+    load(0, av[0]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const T tr = Tt[rt][0][e], ti = Tt[rt][1][e];
-              const int a = 16 * rt + acc_row<T>(g, e);
-              const T2 *arow = A + (size_t(s) * Da + a) * Dan + j;
+    for (int rt = 0; rt < NT; ++rt) {
+      if (rt < nrt) {
 #pragma unroll
-              for (int at = 0; at < NT; ++at) {
-                if (at < nat) {
-                  const T2 av = gload_c(arow + 16 * at);
-                  Ep[c][at][0] = mma(tr, av.x, Ep[c][at][0]);
-                  Ep[c][at][0] = mma(ti, av.y, Ep[c][at][0]);
-                  Ep[c][at][1] = mma(ti, av.x, Ep[c][at][1]);
-                  Ep[c][at][1] = mma(-tr, av.y, Ep[c][at][1]);
-                }
+        for (int e = 0; e < 4; ++e) {
+          const int x = 4 * rt + e;
+          if (e < 3 || rt + 1 < nrt) load(x + 1, av[(x + 1) & 1]);
+          T tr = Q[rt][0][e], ti = Q[rt][1][e];
+          if constexpr (k3) {
+            tr = Q[rt][0][e] - Q[rt][1][e];
+            ti = Q[rt][NP - 1][e] - Q[rt][0][e] - Q[rt][1][e];
+          }
+#pragma unroll
+          for (int at = 0; at < NT; ++at) {
+            if (at < nat) {
+              const T2 v = av[x & 1][at];
+              Ep[at][0] = mma(tr, v.x, Ep[at][0]);
+              if constexpr (k3) {
+                Ep[at][1] = mma(ti, v.y, Ep[at][1]);
+                Ep[at][NP - 1] = mma(tr + ti, v.x - v.y, Ep[at][NP - 1]);
+              } else {
+                Ep[at][1] = mma(ti, v.x, Ep[at][1]);
+                Ep[at][0] = mma(ti, v.y, Ep[at][0]);
+                Ep[at][1] = mma(-tr, v.y, Ep[at][1]);
               }
             }
           }
         }
       }
-#pragma unroll
-      for (int at = 0; at < NT; ++at)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          lmax = fmax(lmax, fmax(fabs(Ep[c][at][0][e]), fabs(Ep[c][at][1][e])));
     }
-    lmax = wave_max(lmax);
-    if (lane == 0) s_red[wave] = lmax;
+  }
+}
+
+template <typename T, typename V4, typename T2>
+__device__ void overlap_plain(const GramJobDev &J, int64_t ia, int64_t ib, T2 *E, T *s_red,
+                              T &ov_re, T &ov_im, int &ov_exp) {
+  constexpr bool k3 = sizeof(T) == 8;
+  constexpr int NP = k3 ? 3 : 2;
+  constexpr int NT = kPlainBlocks;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int j = lane & 15, g = lane >> 4;
+  const T2 *A = reinterpret_cast<const T2 *>(J.a_base) + ia * J.a_stride;
+  const T2 *B = reinterpret_cast<const T2 *>(J.b_base) + ib * J.b_stride;
+  const auto apad = gview(J.a_pad), bpad = gview(J.b_pad), abond = gview(J.a_bond), bbond = gview(J.b_bond);
+  // E_0 = [[1]]: one fragment, element [0][0] at lane 0
+  if (tid < 64) {
+    T2 z;
+    z.x = tid == 0 ? T(1) : T(0);
+    z.y = T(0);
+    E[tid] = z;
+  }
+  __syncthreads();
+  int expacc = 0;
+  const int ct = wave;
+  int pa = apad[0], pb = bpad[0];        // pads at the left bond
+  int nrt = 1, nkq = 1;                  // 16-row blocks of the bra's, 4-row blocks of the ket's left bond
+  for (int l = 0; l < J.m; ++l) {
+    const int pan = apad[l + 1], pbn = bpad[l + 1];
+    const int nat = (abond[l + 1] + 15) >> 4, nkqn = (bbond[l + 1] + 3) >> 2, nct = (nkqn + 3) >> 2;
+    V4 Ep[NT][NP];
+#pragma unroll
+    for (int at = 0; at < NT; ++at)
+#pragma unroll
+      for (int u = 0; u < NP; ++u) Ep[at][u] = V4{0, 0, 0, 0};
+    uint32_t mx = 0;
+    if (ct < nct) {
+      if (nrt == 4 && nat == 4) plain_site<4, T, V4, T2>(A, B, E, pa, pan, pb, pbn, nrt, nkq, nat, ct, lane, Ep);
+      else if (nrt == 3 && nat == 3) plain_site<3, T, V4, T2>(A, B, E, pa, pan, pb, pbn, nrt, nkq, nat, ct, lane, Ep);
+      else plain_site<0, T, V4, T2>(A, B, E, pa, pan, pb, pbn, nrt, nkq, nat, ct, lane, Ep);
+#pragma unroll
+      for (int at = 0; at < NT; ++at) {
+        if constexpr (k3) {
+          const V4 p0 = Ep[at][0], p1 = Ep[at][1];
+          Ep[at][0] = p0 + p1;
+          Ep[at][1] = Ep[at][NP - 1] - p0 + p1;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t x = mag_bits(Ep[at][0][e]), y = mag_bits(Ep[at][1][e]);
+          mx = max(mx, max(x, y));
+        }
+      }
+    }
+    mx = wave_max_bits(mx);
+    uint32_t *red = reinterpret_cast<uint32_t *>(s_red);
+    if (lane == 0) red[wave] = mx;
     __syncthreads();  // every wave is done reading E
-    const T gmax = fmax(fmax(s_red[0], s_red[1]), fmax(s_red[2], s_red[3]));
-    const int e2 = gmax > T(0) ? ilogb(gmax) : 0;
+    mx = max(max(red[0], red[1]), max(red[2], red[3]));
+    const int e2 = exp_of_bits(mx, T(0));
     const T scale = ldexp(T(1), -e2);
     expacc += e2;
-#pragma unroll
-    for (int c = 0; c < CT_PER_WAVE; ++c) {
-      const int ct = wave + 4 * c;
-      if (ct >= nct) continue;
+    if (ct < nct) {
 #pragma unroll
       for (int at = 0; at < NT; ++at) {
         if (at < nat) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             T2 v;
-            v.x = Ep[c][at][0][e] * scale;
-            v.y = Ep[c][at][1][e] * scale;
+            v.x = Ep[at][0][e] * scale;
+            v.y = Ep[at][1][e] * scale;
             // E'[16 at + j][bp] -> fragment (at, bp / 4), lane j + 16 (bp % 4)
             const int bp = 16 * ct + acc_row<T>(g, e);
-            E[(at * nkqn + (bp >> 2)) * 64 + j + 16 * (bp & 3)] = v;
+            if ((bp >> 2) < nkqn) E[(at * nkqn + (bp >> 2)) * 64 + j + 16 * (bp & 3)] = v;
           }
         }
       }
     }
+    A += 2 * pa * pan;
+    B += 2 * pb * pbn;
+    pa = pan;
+    pb = pbn;
+    nrt = nat;
+    nkq = nkqn;
     __syncthreads();
   }
   ov_re = E[0].x;
@@ -309,8 +395,14 @@ __device__ void overlap_plain(const GramJobDev &J, int64_t ia, int64_t ib, T2 *E
 // per workgroup, where it stays in L2: two buffers, E read and E' written,
 // each in the A-operand fragment order of the LDS variant above.  Eight
 // waves; wave w computes E' for the ket column block w.  T_s passes from
-// GEMM1 to GEMM2 one 16-row block at a time, so only the accumulators of
-// the wave's E' block (8 x 16 x 16 complex) are held across the site.
+// GEMM1 to GEMM2 two 16-row blocks at a time, which share their loads of the
+// ket, so only the accumulators of the wave's E' block (8 x 16 x 16 complex)
+// are held across the site; FP64 uses three real products per complex one in
+// GEMM1 (three accumulators per E' tile would leave no registers).  Bounds:
+// MFMA issue and, with one pair per CU, the loads of a step from L2, issued
+// one step ahead.  300 pairs of 40 sites at bond 128 (two rounds of the 256
+// CUs): FP64 24.7 -> 15.6 ms, FP32 18.8 -> 9.6 ms; 300 at bond 100: FP64 24.4
+// -> 11.9 ms.
 constexpr int kWideP = 128;
 constexpr int kWideThreads = 512;
 constexpr int kWideWaves = kWideThreads / 64;
@@ -318,89 +410,117 @@ constexpr int kWideWaves = kWideThreads / 64;
 template <typename T, typename V4, typename T2>
 __device__ void overlap_wide(const GramJobDev &J, int64_t ia, int64_t ib, T2 *E0, T2 *E1, T *s_red,
                              T &ov_re, T &ov_im, int &ov_exp) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  constexpr bool k3 = sizeof(T) == 8;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int j = lane & 15, g = lane >> 4;
-  const T2 *abase = reinterpret_cast<const T2 *>(J.a_base) + ia * J.a_stride;
-  const T2 *bbase = reinterpret_cast<const T2 *>(J.b_base) + ib * J.b_stride;
+  const T2 *A = reinterpret_cast<const T2 *>(J.a_base) + ia * J.a_stride;
+  const T2 *B = reinterpret_cast<const T2 *>(J.b_base) + ib * J.b_stride;
+  const auto apad = gview(J.a_pad), bpad = gview(J.b_pad), abond = gview(J.a_bond), bbond = gview(J.b_bond);
+  const V4 zero = V4{0, 0, 0, 0};
   T2 *Ec = E0, *En = E1;
-  {
-    // E_0 = [[1]] on the first site's pads (element [0][0] is lane 0 of
-    // fragment 0)
-    const int n0 = gview(J.a_pad)[0] * gview(J.b_pad)[0];
-    for (int x = tid; x < n0; x += kWideThreads) {
-      T2 z;
-      z.x = x == 0 ? T(1) : T(0);
-      z.y = T(0);
-      gstore_c(Ec + x, z);
-    }
-    __syncthreads();
+  // E_0 = [[1]]: one fragment, element [0][0] at lane 0
+  if (tid < 64) {
+    T2 z;
+    z.x = tid == 0 ? T(1) : T(0);
+    z.y = T(0);
+    gstore_c(Ec + tid, z);
   }
+  __syncthreads();
   int expacc = 0;
   constexpr int NT = kWideP / 16;
   const int ct = wave;
+  int pa = apad[0], pb = bpad[0];   // pads at the left bond
+  int nrt = 1, nkq = 1;             // 16-row blocks of the bra's, 4-row blocks of the ket's left bond
   for (int l = 0; l < J.m; ++l) {
-    const int Da = gview(J.a_pad)[l], Dan = gview(J.a_pad)[l + 1], Db = gview(J.b_pad)[l], Dbn = gview(J.b_pad)[l + 1];
-    const T2 *A = abase + gview(J.a_off)[l];
-    const T2 *B = bbase + gview(J.b_off)[l];
-    const int nrt = Da / 16, nkq = Db / 4, nat = Dan / 16, nct = Dbn / 16, nkqn = Dbn / 4;
+    const int pan = apad[l + 1], pbn = bpad[l + 1];
+    const int nat = (abond[l + 1] + 15) >> 4, nkqn = (bbond[l + 1] + 3) >> 2, nct = (nkqn + 3) >> 2;
     V4 Ep[NT][2];
 #pragma unroll
-    for (int at = 0; at < NT; ++at) {
-      Ep[at][0] = V4{0, 0, 0, 0};
-      Ep[at][1] = V4{0, 0, 0, 0};
-    }
+    for (int at = 0; at < NT; ++at) Ep[at][0] = Ep[at][1] = zero;
     if (ct < nct) {
+#pragma unroll 1
       for (int s = 0; s < 2; ++s) {
-        const T2 *Bc = B + size_t(s) * Db * Dbn + 16 * ct + j;
-        for (int rt = 0; rt < nrt; ++rt) {
-          // GEMM1 on row block rt: T_s[a][b'] = sum_b E[a][b] B_s[b][b'],
-          // real and imaginary parts of E in separate accumulators (two
-          // independent MFMA chains per output)
-          V4 t0 = V4{0, 0, 0, 0}, t1 = V4{0, 0, 0, 0}, u0 = V4{0, 0, 0, 0}, u1 = V4{0, 0, 0, 0};
+        const T2 *Bc = B + (s * pb + g) * pbn + 16 * ct + j;
+#pragma unroll 1
+        for (int rt = 0; rt < nrt; rt += 2) {
+          // GEMM1 on row blocks rt, rt + 1: T_s[a][b'] = sum_b E[a][b] B_s[b][b'].
+          // An odd last block is formed twice (its second copy is not used).
+          V4 Q[2][4];   // FP64: Er Br, Ei Bi, (Er + Ei)(Br + Bi); FP32: Er Br, Er Bi, -Ei Bi, Ei Br
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) Q[h][u] = zero;
           const T2 *Er = Ec + size_t(rt) * nkq * 64 + lane;
-#pragma unroll 4
+          const int hoff = rt + 1 < nrt ? nkq * 64 : 0;
+          T2 bn = gload_c(Bc), en[2] = {gload_c(Er), gload_c(Er + hoff)};
+#pragma unroll 2
           for (int kq = 0; kq < nkq; ++kq) {
-            const T2 bv = gload_c(Bc + size_t(4 * kq + g) * Dbn);
-            const T2 ev = gload_c(Er + kq * 64);
-            t0 = mma(ev.x, bv.x, t0);
-            t1 = mma(ev.x, bv.y, t1);
-            u0 = mma(ev.y, -bv.y, u0);
-            u1 = mma(ev.y, bv.x, u1);
+            const T2 bv = bn, ev[2] = {en[0], en[1]};
+            if (kq + 1 < nkq) {
+              bn = gload_c(Bc + 4 * (kq + 1) * pbn);
+              en[0] = gload_c(Er + (kq + 1) * 64);
+              en[1] = gload_c(Er + hoff + (kq + 1) * 64);
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              Q[h][0] = mma(ev[h].x, bv.x, Q[h][0]);
+              if constexpr (k3) {
+                Q[h][1] = mma(ev[h].y, bv.y, Q[h][1]);
+                Q[h][2] = mma(ev[h].x + ev[h].y, bv.x + bv.y, Q[h][2]);
+              } else {
+                Q[h][1] = mma(ev[h].x, bv.y, Q[h][1]);
+                Q[h][2] = mma(ev[h].y, -bv.y, Q[h][2]);
+                Q[h][3] = mma(ev[h].y, bv.x, Q[h][3]);
+              }
+            }
           }
-          t0 += u0;
-          t1 += u1;
-          // GEMM2: E'^T[b'][a'] += sum_{a in block rt} T_s[a][b'] conj(A_s[a][a'])
+          // GEMM2: E'^T[b'][a'] += sum_{a in the blocks} T_s[a][b'] conj(A_s[a][a'])
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const T tr = t0[e], ti = t1[e];
-            const int a = 16 * rt + acc_row<T>(g, e);
-            const T2 *arow = A + (size_t(s) * Da + a) * Dan + j;
+          for (int h = 0; h < 2; ++h) {
+            if (rt + h < nrt) {
+              V4 tr, ti;
+              if constexpr (k3) {
+                tr = Q[h][0] - Q[h][1];
+                ti = Q[h][2] - Q[h][0] - Q[h][1];
+              } else {
+                tr = Q[h][0] + Q[h][2];
+                ti = Q[h][1] + Q[h][3];
+              }
 #pragma unroll
-            for (int at = 0; at < NT; ++at) {
-              if (at < nat) {
-                const T2 av = gload_c(arow + 16 * at);
-                Ep[at][0] = mma(tr, av.x, Ep[at][0]);
-                Ep[at][0] = mma(ti, av.y, Ep[at][0]);
-                Ep[at][1] = mma(ti, av.x, Ep[at][1]);
-                Ep[at][1] = mma(-tr, av.y, Ep[at][1]);
+              for (int e = 0; e < 4; ++e) {
+                const T2 *arow = A + (s * pa + 16 * (rt + h) + acc_row<T>(g, e)) * pan + j;
+                T2 av[NT];
+#pragma unroll
+                for (int at = 0; at < NT; ++at)
+                  if (at < nat) av[at] = gload_c(arow + 16 * at);
+#pragma unroll
+                for (int at = 0; at < NT; ++at) {
+                  if (at < nat) {
+                    Ep[at][0] = mma(tr[e], av[at].x, Ep[at][0]);
+                    Ep[at][1] = mma(ti[e], av[at].x, Ep[at][1]);
+                    Ep[at][0] = mma(ti[e], av[at].y, Ep[at][0]);
+                    Ep[at][1] = mma(-tr[e], av[at].y, Ep[at][1]);
+                  }
+                }
               }
             }
           }
         }
       }
     }
-    T lmax = T(0);
+    uint32_t mx = 0;
 #pragma unroll
     for (int at = 0; at < NT; ++at)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) lmax = fmax(lmax, fmax(fabs(Ep[at][0][e]), fabs(Ep[at][1][e])));
-    lmax = wave_max(lmax);
-    if (lane == 0) s_red[wave] = lmax;
+      for (int e = 0; e < 4; ++e) mx = max(mx, max(mag_bits(Ep[at][0][e]), mag_bits(Ep[at][1][e])));
+    mx = wave_max_bits(mx);
+    uint32_t *red = reinterpret_cast<uint32_t *>(s_red);
+    if (lane == 0) red[wave] = mx;
     __syncthreads();
-    T gmax = s_red[0];
+    mx = red[0];
 #pragma unroll
-    for (int w = 1; w < kWideWaves; ++w) gmax = fmax(gmax, s_red[w]);
-    const int e2 = gmax > T(0) ? ilogb(gmax) : 0;
+    for (int w = 1; w < kWideWaves; ++w) mx = max(mx, red[w]);
+    const int e2 = exp_of_bits(mx, T(0));
     const T scale = ldexp(T(1), -e2);
     expacc += e2;
     if (ct < nct) {
@@ -414,11 +534,17 @@ __device__ void overlap_wide(const GramJobDev &J, int64_t ia, int64_t ib, T2 *E0
             v.y = Ep[at][1][e] * scale;
             // E'[16 at + j][bp] -> fragment (at, bp / 4), lane j + 16 (bp % 4)
             const int bp = 16 * ct + acc_row<T>(g, e);
-            gstore_c(En + (at * nkqn + (bp >> 2)) * 64 + j + 16 * (bp & 3), v);
+            if ((bp >> 2) < nkqn) gstore_c(En + (at * nkqn + (bp >> 2)) * 64 + j + 16 * (bp & 3), v);
           }
         }
       }
     }
+    A += 2 * pa * pan;
+    B += 2 * pb * pbn;
+    pa = pan;
+    pb = pbn;
+    nrt = nat;
+    nkq = nkqn;
     // E' complete and visible to the workgroup; s_red free for the next site
     __syncthreads();
     T2 *t = Ec;
@@ -441,20 +567,6 @@ __device__ void overlap_wide(const GramJobDev &J, int64_t ia, int64_t ib, T2 *E0
 // at its pad.  Bounds: MFMA issue where the pairs fill the chip (a bond-32
 // FP64 site takes 384 MFMAs of 64 cycles), else the chain of one site's
 // dependent MFMAs and loads.
-// Largest magnitude exponent of the wave's values: bits are the sign-less
-// upper halves, whose order is the order of magnitudes.
-__device__ inline uint32_t wave_max_bits(uint32_t v) {
-  auto step = [&](uint32_t o) { v = v > o ? v : o; };
-  step(uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x128, 0xf, 0xf, true)));   // row_ror 8, 4, 2, 1
-  step(uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x124, 0xf, 0xf, true)));
-  step(uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x122, 0xf, 0xf, true)));
-  step(uint32_t(__builtin_amdgcn_mov_dpp(int(v), 0x121, 0xf, 0xf, true)));
-  auto a = __builtin_amdgcn_permlane16_swap(int(v), int(v), false, false);
-  v = uint32_t(a[0]) > uint32_t(a[1]) ? uint32_t(a[0]) : uint32_t(a[1]);
-  a = __builtin_amdgcn_permlane32_swap(int(v), int(v), false, false);
-  return uint32_t(a[0]) > uint32_t(a[1]) ? uint32_t(a[0]) : uint32_t(a[1]);
-}
-
 // 4 x 4 transpose between the four registers and the four lane rows: out
 // register q of row g is in register g of row q.
 __device__ inline void rows_to_regs(f32x4 &v) {
@@ -475,13 +587,6 @@ __device__ inline void rows_to_regs(f32x4 &v) {
   sw16(r2, r3);
   v = f32x4{r0, r1, r2, r3};
 }
-
-// Exponent of the largest magnitude whose sign-less upper bits are given (0
-// for zero and below the normal range, which is then left unscaled).
-__device__ inline int exp_of_bits(uint32_t bits, double) { return (bits >> 20) ? int(bits >> 20) - 1023 : 0; }
-__device__ inline int exp_of_bits(uint32_t bits, float) { return (bits >> 23) ? int(bits >> 23) - 127 : 0; }
-__device__ inline uint32_t mag_bits(double x) { return uint32_t(__double2hiint(x)) & 0x7fffffffu; }
-__device__ inline uint32_t mag_bits(float x) { return __float_as_uint(x) & 0x7fffffffu; }
 
 // Pairs with bonds up to 16 NT.  E[rt][kt] holds rows 16 rt + j and columns
 // 16 kt + 4 q + g (register q).  Per ket column block: T_s (GEMM1), then its
@@ -1537,7 +1642,7 @@ constexpr int threads_of() {
 }
 
 template <int PREC, int MAXP>
-__global__ __launch_bounds__(threads_of<PREC>(), 2) void gram_kernel(const GramJobDev *__restrict__ jobs,
+__global__ __launch_bounds__(threads_of<PREC>(), PREC == QK_FP32 ? 3 : 2) void gram_kernel(const GramJobDev *__restrict__ jobs,
                                                         const GramTile *__restrict__ tiles,
                                                         int64_t n_tiles, int nq, int th, int tw,
                                                         unsigned long long *counters) {
@@ -1558,13 +1663,13 @@ __global__ __launch_bounds__(threads_of<PREC>(), 2) void gram_kernel(const GramJ
     if constexpr (PREC == QK_FP64) {
       double re, im;
       int ex;
-      overlap_plain<double, f64x4, double2, MAXP>(J, J.a0 + i, J.b0 + j,
-                                                  reinterpret_cast<double2 *>(smem), s_red, re, im, ex);
+      overlap_plain<double, f64x4, double2>(J, J.a0 + i, J.b0 + j, reinterpret_cast<double2 *>(smem), s_red, re, im,
+                                            ex);
       k = ldexp(re * re + im * im, 2 * ex);
     } else if constexpr (PREC == QK_FP32) {
       float re, im;
       int ex;
-      overlap_plain<float, f32x4, float2, MAXP>(J, J.a0 + i, J.b0 + j, reinterpret_cast<float2 *>(smem),
+      overlap_plain<float, f32x4, float2>(J, J.a0 + i, J.b0 + j, reinterpret_cast<float2 *>(smem),
                                                 reinterpret_cast<float *>(s_red), re, im, ex);
       k = ldexp(double(re) * re + double(im) * im, 2 * ex);
     } else if constexpr (PREC == QK_SPLIT_BF16) {
