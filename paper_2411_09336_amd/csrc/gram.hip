@@ -234,7 +234,7 @@ __device__ __forceinline__ void plain_site(const T2 *A, const T2 *B, const T2 *E
     const T2 *Bc = B + (s * pb + g) * pbn + 16 * ct + j;
     const T2 *Er = E + lane;
     T2 bv = gload_c(Bc);
-#pragma unroll (k3 ? 1 : 2)
+#pragma unroll 1
     for (int kq = 0; kq < nkq; ++kq) {
       const T2 b0 = bv;
       T2 ev[NT];
@@ -833,52 +833,6 @@ __device__ inline void overlap_quad(const GramJobDev &J, int64_t ia, int64_t ib,
   ov_exp = expacc;
 }
 
-// Pairs of a wave kernel: one-wave workgroups take units (one pair, or four
-// neighbouring columns of one row at bonds up to 4) from the atomic queue;
-// the next unit's index is fetched while the current one is contracted.
-template <typename T, int NT>
-__global__ __launch_bounds__(64, NT == 2 ? 2 : 4) void gram_wave_kernel(const GramJobDev *__restrict__ jobs,
-                                                                         const GramTile *__restrict__ tiles,
-                                                                         int64_t n_units, int th, int tw,
-                                                                         unsigned long long *counter) {
-  constexpr int kPer = NT == 0 ? 4 : 1;   // pairs per unit
-  const int lane = threadIdx.x;
-  const int upt = th * tw / kPer;   // units per tile (tw is a multiple of 4)
-  int64_t next = int64_t(blockIdx.x);   // the first unit of each workgroup is its index
-  while (next < n_units) {
-    const int64_t u = next;
-    unsigned long long f = 0;
-    if (lane == 0) f = atomicAdd(counter, 1ull);
-    const GramTile t = tiles[u / upt];
-    const int q = int(u % upt) * kPer;
-    const GramJobDev &J = jobs[t.job];
-    const int64_t li = int64_t(t.ti) * th + q / tw;
-    const int64_t lj = int64_t(t.tj) * tw + q % tw;
-    if constexpr (NT == 0) {
-      const int64_t ljb = lj + ((lane >> 2) & 3);
-      auto ok = [&](int64_t c) { return li < J.na && c < J.nb && (!J.upper || J.b0 + c >= J.a0 + li); };
-      if (ok(lj) || ok(lj + 3) || ok(lj + 1) || ok(lj + 2)) {
-        double re, im;
-        int ex;
-        overlap_quad(J, J.a0 + li, J.b0 + (ljb < J.nb ? ljb : J.nb - 1), re, im, ex);
-        if (lane < 16 && (lane & 3) == 0 && ok(ljb)) write_k(J, li, ljb, ldexp(re * re + im * im, 2 * ex));
-      }
-    } else if (li < J.na && lj < J.nb && (!J.upper || J.b0 + lj >= J.a0 + li)) {
-      T re, im;
-      int ex;
-      if constexpr (sizeof(T) == 8) {
-        overlap_wave<double, f64x4, double2, NT>(J, J.a0 + li, J.b0 + lj, re, im, ex);
-        if (lane == 0) write_k(J, li, lj, ldexp(re * re + im * im, 2 * ex));
-      } else {
-        overlap_wave<float, f32x4, float2, NT>(J, J.a0 + li, J.b0 + lj, re, im, ex);
-        if (lane == 0) write_k(J, li, lj, ldexp(double(re) * re + double(im) * im, 2 * ex));
-      }
-    }
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(f)), hi = __builtin_amdgcn_readfirstlane(uint32_t(f >> 32));
-    next = int64_t((uint64_t(hi) << 32) | lo) + int64_t(gridDim.x);
-  }
-}
-
 // A pointer that is the same in every lane, moved to scalar registers.
 template <typename T>
 __device__ inline T *uniform_ptr(T *p) {
@@ -1362,6 +1316,29 @@ struct I8Acc {
   i32x4 re[5], im[5];
 };
 
+// The products of digit a of the LDS (or register) operand's planes x0, x1
+// with the digits b <= 3 - a of the site operand (and, if P22_RE, the (2, 2)
+// pair in the real part).
+template <bool CPL1, bool P22_RE>
+__device__ inline void i8_digit(const uint4 &x0, const uint4 &x1, int a, const uint4 (&Y0)[4], const uint4 (&Y1)[4],
+                                I8Acc &acc) {
+  const uint4 P = x0, Q = CPL1 ? not4(x1) : x1, R = CPL1 ? x0 : not4(x0), S = x1;
+  // digit pairs (a, b) with a + b <= 3
+  const int nb = a == 0 ? 4 : a == 1 ? 3 : a == 2 ? 2 : 1;
+#pragma unroll
+  for (int b = 0; b < nb; ++b) {
+    const int c = a + b;
+    acc.re[c] = mma_i8(P, Y0[b], acc.re[c]);
+    acc.im[c] = mma_i8(R, Y1[b], acc.im[c]);
+    acc.re[c] = mma_i8(Q, Y1[b], acc.re[c]);
+    acc.im[c] = mma_i8(S, Y0[b], acc.im[c]);
+  }
+  if (P22_RE && a == 2) {   // (2, 2) into class 4 of the real part
+    acc.re[4] = mma_i8(P, Y0[2], acc.re[4]);
+    acc.re[4] = mma_i8(Q, Y1[2], acc.re[4]);
+  }
+}
+
 // Same products with the LDS operand read one digit at a time (tile base tg:
 // fragments (digit a, plane 0 / 1) at (2 a + q) KiB).  CPL1: complement plane 1
 // in the real part (GEMM1: re += X0 Y0 + (~X1) Y1, im += X0 Y1 + X1 Y0);
@@ -1379,25 +1356,9 @@ __device__ inline void i8_block_lds(const uint8_t *tg, const uint4 (&Y0)[4], con
     acc.im[c] = (!CPL1 && c < 4) ? corr[c] : i32x4{0, 0, 0, 0};
   }
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const uint4 x0 = *reinterpret_cast<const uint4 *>(tg + (a * 2 + 0) * kI8FragBytes);
-    const uint4 x1 = *reinterpret_cast<const uint4 *>(tg + (a * 2 + 1) * kI8FragBytes);
-    const uint4 P = x0, Q = CPL1 ? not4(x1) : x1, R = CPL1 ? x0 : not4(x0), S = x1;
-    // digit pairs (a, b) with a + b <= 3
-    const int nb = a == 0 ? 4 : a == 1 ? 3 : a == 2 ? 2 : 1;
-#pragma unroll
-    for (int b = 0; b < nb; ++b) {
-      const int c = a + b;
-      acc.re[c] = mma_i8(P, Y0[b], acc.re[c]);
-      acc.im[c] = mma_i8(R, Y1[b], acc.im[c]);
-      acc.re[c] = mma_i8(Q, Y1[b], acc.re[c]);
-      acc.im[c] = mma_i8(S, Y0[b], acc.im[c]);
-    }
-    if (P22_RE && a == 2) {   // (2, 2) into class 4 of the real part
-      acc.re[4] = mma_i8(P, Y0[2], acc.re[4]);
-      acc.re[4] = mma_i8(Q, Y1[2], acc.re[4]);
-    }
-  }
+  for (int a = 0; a < 4; ++a)
+    i8_digit<CPL1, P22_RE>(*reinterpret_cast<const uint4 *>(tg + (a * 2 + 0) * kI8FragBytes),
+                           *reinterpret_cast<const uint4 *>(tg + (a * 2 + 1) * kI8FragBytes), a, Y0, Y1, acc);
 }
 
 // Exact digit sum of element e of a class accumulator set (corrections
@@ -1636,6 +1597,336 @@ __device__ void overlap_i8(const GramJobDev &J, int64_t ia, int64_t ib, uint8_t 
   __syncthreads();
 }
 
+// ------------------------------------------------------------------------
+// Split forms at bonds up to 16 NT (NT = 1, 2): one wave per pair.  The site
+// blocks are those of the workgroup kernels, of which only the filled tiles
+// are read, and every value, exponent and digit is formed by the same
+// operations in the same order, so K has the same bits; but a 64 x 64 site
+// costs 16 (4) times the MFMAs that these bonds need.  An accumulator's rows
+// are the bytes (slots) of the next operand in the same lane, so E and T
+// stay in registers; only the row exponents cross lanes, through 64 bytes of
+// LDS of the wave.  5,050 pairs of 100 sites: split-BF16 30.3 -> 5.8 ms at
+// bond 32 and 1.5 ms at bonds up to 16, split-int8 18.7 -> 8.0 and 2.0 ms
+// (VALU slicing now outweighs the MFMAs, which both carriers hide less).
+__device__ inline double rows_max(double x) {   // over the four lane rows
+  auto step = [&](auto sw) {
+    const auto lo = sw(__double2loint(x)), hi = sw(__double2hiint(x));
+    x = fmax(__hiloint2double(int(hi[0]), int(lo[0])), __hiloint2double(int(hi[1]), int(lo[1])));
+  };
+  step([](int v) { return __builtin_amdgcn_permlane16_swap(v, v, false, false); });
+  step([](int v) { return __builtin_amdgcn_permlane32_swap(v, v, false, false); });
+  return x;
+}
+
+// Exponents of rows 4 g .. 4 g + 3 of a 16-row tile from the value that lane
+// j holds for row j.
+__device__ inline int4 rows_of_lanes(int *s_e, int lane, int e) {
+  if (lane < 16) s_e[lane] = e;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const int4 r = *reinterpret_cast<const int4 *>(s_e + 4 * (lane >> 4));
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  return r;
+}
+__device__ inline int pick(const int4 &v, int e) { return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w; }
+
+// What the two forms do with a 16-row operand (four digits of two planes), a
+// column block of a site and a tile of FP64 values.
+struct WaveI8 {
+  template <int NT>
+  struct Operand {
+    uint32_t d[4][2][NT];   // [digit][plane][16-row tile of the contraction]; the operand's other words are zero
+    __device__ uint4 at(int k, int q) const { return make_uint4(d[k][q][0], NT > 1 ? d[k][q][NT - 1] : 0u, 0u, 0u); }
+  };
+  struct Site {
+    uint4 f[8];
+    int e, cs[4];
+  };
+  static constexpr int64_t kSiteBytes = kI8SiteBytes;
+  static constexpr int kShift = 38;
+  static constexpr bool kFence = true;   // one tile's accumulators live (registers)
+  __device__ static void load(const uint8_t *site, int s, int c, int lane, Site &o) {
+    const SiteRsrc r = site_rsrc<kI8SiteBytes>(site);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      o.f[k] = i8_frag(r, s, k, 0, c, lane);
+      o.f[4 + k] = i8_frag(r, s, k, 1, c, lane);
+    }
+    const int col = 16 * c + (lane & 15);
+    o.e = int(gview(reinterpret_cast<const int8_t *>(site))[s * 128 + col]);
+    const auto p = gview(reinterpret_cast<const int *>(site + kI8ExpBytes) + s * 256 + col);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o.cs[k] = p[64 * k];
+  }
+  // complex 16 x 16 tile in units of 2^-(62 - 24) of the exponents' product:
+  // GEMM1 X B (re = Xr Br - Xi Bi, im = Xr Bi + Xi Br), GEMM2 X conj(A)
+  template <bool GEMM2, int NT>
+  __device__ static void tile(const Operand<NT> &X, const Site &y, double (&v)[2][4]) {
+    i32x4 corr[4];
+    i8_corrections(y.cs, corr);
+    constexpr bool CPL1 = !GEMM2, P22 = GEMM2 && QK_I8_PAIR22;
+    I8Acc acc;
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+      acc.re[c] = (CPL1 && c < 4) ? corr[c] : i32x4{0, 0, 0, 0};
+      acc.im[c] = (!CPL1 && c < 4) ? corr[c] : i32x4{0, 0, 0, 0};
+    }
+    const uint4(&Y0)[4] = *reinterpret_cast<const uint4(*)[4]>(&y.f[0]);
+    const uint4(&Y1)[4] = *reinterpret_cast<const uint4(*)[4]>(&y.f[4]);
+#pragma unroll
+    for (int a = 0; a < 4; ++a) i8_digit<CPL1, P22>(X.at(a, 0), X.at(a, 1), a, Y0, Y1, acc);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[0][e] = i8_value<P22>(acc.re, e);
+      v[1][e] = i8_value<false>(acc.im, e);
+    }
+  }
+  __device__ static int exponent(double mx) { return exp_above_i8(mx); }
+  // rows of tile t of a column (both planes) as bytes 4 t .. 4 t + 3
+  template <int NT>
+  __device__ static void slice(const double (&V)[NT][2][4], int ex, Operand<NT> &o) {
+    const double scale = ldexp(1.0, 31 - ex);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      uint32_t w[NT][4];
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        transpose_digits(biased_digit_word(V[t][q][0], scale), biased_digit_word(V[t][q][1], scale),
+                         biased_digit_word(V[t][q][2], scale), biased_digit_word(V[t][q][3], scale), w[t]);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) o.d[k][q][t] = w[t][k];
+    }
+  }
+  template <int NT>
+  __device__ static void one(int lane, Operand<NT> &o) {   // E_0 = [[1]]: exponent 1, leading digit 64
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) o.d[k][0][t] = o.d[k][1][t] = 0;
+    if (lane == 0) o.d[0][0][0] = 64;
+  }
+};
+
+struct WaveBf16 {
+  template <int NT>
+  struct Operand {
+    Sl4 d[2];   // [plane]
+  };
+  struct Site {
+    Sl4 f[2];
+    int e;
+  };
+  static constexpr int64_t kSiteBytes = kSplitSiteBytes;
+  static constexpr int kShift = 14;
+  static constexpr bool kFence = false;
+  __device__ static void load(const uint8_t *site, int s, int c, int lane, Site &o) {
+    const SiteRsrc r = site_rsrc<kSplitSiteBytes>(site);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      o.f[0].v[k] = split_frag(r, s, k, 0, 0, c, lane);
+      o.f[1].v[k] = split_frag(r, s, k, 1, 0, c, lane);
+    }
+    o.e = int(gview(reinterpret_cast<const int8_t *>(site))[s * 128 + 16 * c + (lane & 15)]);
+  }
+  template <bool GEMM2, int NT>
+  __device__ static void tile(const Operand<NT> &X, const Site &y, double (&v)[2][4]) {
+    f32x4 h[2], lo[2];
+    h[0] = h[1] = lo[0] = lo[1] = f32x4{0, 0, 0, 0};
+    const Sl4 yn = neg4(y.f[1]);
+    if constexpr (!GEMM2) {
+      slice_mac<false>(X.d[0], y.f[0], h[0], lo[0]);
+      slice_mac<false>(X.d[1], yn, h[0], lo[0]);
+      slice_mac<false>(X.d[0], y.f[1], h[1], lo[1]);
+      slice_mac<false>(X.d[1], y.f[0], h[1], lo[1]);
+    } else {
+      slice_mac<true>(X.d[0], y.f[0], h[0], lo[0]);
+      slice_mac<true>(X.d[1], y.f[1], h[0], lo[0]);
+      slice_mac<false>(X.d[1], y.f[0], h[1], lo[1]);
+      slice_mac<false>(X.d[0], yn, h[1], lo[1]);
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[q][e] = double(h[q][e]) + double(lo[q][e]);
+  }
+  __device__ static int exponent(double mx) { return exp_above_w(mx); }
+  template <int NT>
+  __device__ static void slice(const double (&V)[NT][2][4], int ex, Operand<NT> &o) {
+    const double scale = ldexp(1.0, 31 - ex);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      float sl[2][4][4] = {};
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) slice4_word(V[t][q][e], scale, sl[t][e]);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        o.d[q].v[k] = make_uint4(pack_bf16_pair(sl[0][0][k], sl[0][1][k]), pack_bf16_pair(sl[0][2][k], sl[0][3][k]),
+                                 pack_bf16_pair(sl[1][0][k], sl[1][1][k]), pack_bf16_pair(sl[1][2][k], sl[1][3][k]));
+    }
+  }
+  template <int NT>
+  __device__ static void one(int lane, Operand<NT> &o) {   // E_0 = [[1]]: exponent 1, leading slice 64
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o.d[0].v[k] = o.d[1].v[k] = make_uint4(0, 0, 0, 0);
+    if (lane == 0) o.d[0].v[0].x = bf16_bits_exact(64.0f);
+  }
+};
+
+template <class F, int NT>
+__device__ inline void overlap_split_wave(const GramJobDev &J, int64_t ia, int64_t ib, int *s_e, double &ov_re,
+                                          double &ov_im) {
+  const int lane = threadIdx.x & 63;
+  const uint8_t *A = reinterpret_cast<const uint8_t *>(J.a_base) + ia * J.a_stride;
+  const uint8_t *B = reinterpret_cast<const uint8_t *>(J.b_base) + ib * J.b_stride;
+  const auto abond = gview(J.a_bond), bbond = gview(J.b_bond);
+  typename F::template Operand<NT> E[NT];   // row tile rt of E
+  int4 ea[NT];                 // exponents of its rows 4 g .. 4 g + 3
+#pragma unroll
+  for (int rt = 0; rt < NT; ++rt) {
+    F::template one<NT>(rt == 0 ? lane : 1, E[rt]);
+    ea[rt] = make_int4(rt == 0 && lane < 16 ? 1 : 0, 0, 0, 0);
+  }
+  int na = 1;   // 16-row tiles at the bra's left bond
+  for (int l = 0; l < J.m; ++l) {
+    const int nan = NT == 1 ? 1 : (abond[l + 1] + 15) >> 4, nbn = NT == 1 ? 1 : (bbond[l + 1] + 15) >> 4;
+    double Ep[NT][NT][2][4];   // E'^T: [bra block at][ket block ct]
+#pragma unroll
+    for (int at = 0; at < NT; ++at)
+#pragma unroll
+      for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) Ep[at][ct][q][e] = 0.0;
+#pragma unroll 1
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+      for (int ct = 0; ct < NT; ++ct) {
+        if (ct < nbn) {
+          // GEMM1: T_s[a][b'] = sum_b E[a][b] B_s[b][b'], b' in block ct
+          typename F::Site y;
+          F::load(B, s, ct, lane, y);
+          double Td[NT][2][4], tmax = 0.0;
+#pragma unroll
+          for (int rt = 0; rt < NT; ++rt) {
+            if (rt < na) {
+              F::template tile<false, NT>(E[rt], y, Td[rt]);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const int ex = pick(ea[rt], e) + y.e - F::kShift;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                  Td[rt][q][e] = ldexp(Td[rt][q][e], ex);
+                  tmax = fmax(tmax, fabs(Td[rt][q][e]));
+                }
+              }
+              if (F::kFence && NT > 1) tile_fence(Td[rt]);
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) Td[rt][0][e] = Td[rt][1][e] = 0.0;
+            }
+          }
+          const int eT = F::exponent(rows_max(tmax));
+          typename F::template Operand<NT> T;
+          F::template slice<NT>(Td, eT, T);
+          const int4 et = rows_of_lanes(s_e, lane, eT);
+          // GEMM2: E'^T[b'][a'] += sum_a T_s[a][b'] conj(A_s[a][a'])
+#pragma unroll
+          for (int at = 0; at < NT; ++at) {
+            if (at < nan) {
+              F::load(A, s, at, lane, y);
+              double v[2][4];
+              F::template tile<true, NT>(T, y, v);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const int ex = pick(et, e) + y.e - F::kShift;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) Ep[at][ct][q][e] += ldexp(v[q][e], ex);
+              }
+              if (F::kFence && NT > 1) tile_fence(Ep[at][ct]);
+            }
+          }
+        }
+      }
+    }
+    ov_re = Ep[0][0][0][0];   // E_m[0][0] in lane 0
+    ov_im = Ep[0][0][1][0];
+#pragma unroll
+    for (int at = 0; at < NT; ++at) {
+      double rm = 0.0;
+#pragma unroll
+      for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) rm = fmax(rm, fmax(fabs(Ep[at][ct][0][e]), fabs(Ep[at][ct][1][e])));
+      const int er = F::exponent(rows_max(rm));
+      F::template slice<NT>(Ep[at], er, E[at]);
+      ea[at] = rows_of_lanes(s_e, lane, er);
+    }
+    A += F::kSiteBytes;
+    B += F::kSiteBytes;
+    na = nan;
+  }
+}
+
+// Pairs of a wave kernel: one-wave workgroups take units (one pair, or four
+// neighbouring columns of one row at bonds up to 4) from the atomic queue;
+// the next unit's index is fetched while the current one is contracted.
+template <int PREC, int NT>
+__global__ __launch_bounds__(64, NT == 2 && PREC != QK_FP32 ? 2 : PREC == QK_SPLIT_BF16 || PREC == QK_SPLIT_I8 ? 3 : 4) void gram_wave_kernel(const GramJobDev *__restrict__ jobs,
+                                                                         const GramTile *__restrict__ tiles,
+                                                                         int64_t n_units, int th, int tw,
+                                                                         unsigned long long *counter) {
+  constexpr int kPer = NT == 0 ? 4 : 1;   // pairs per unit
+  __shared__ __align__(16) int s_e[16];
+  const int lane = threadIdx.x;
+  const int upt = th * tw / kPer;   // units per tile (tw is a multiple of 4)
+  int64_t next = int64_t(blockIdx.x);   // the first unit of each workgroup is its index
+  while (next < n_units) {
+    const int64_t u = next;
+    unsigned long long f = 0;
+    if (lane == 0) f = atomicAdd(counter, 1ull);
+    const GramTile t = tiles[u / upt];
+    const int q = int(u % upt) * kPer;
+    const GramJobDev &J = jobs[t.job];
+    const int64_t li = int64_t(t.ti) * th + q / tw;
+    const int64_t lj = int64_t(t.tj) * tw + q % tw;
+    if constexpr (NT == 0) {
+      const int64_t ljb = lj + ((lane >> 2) & 3);
+      auto ok = [&](int64_t c) { return li < J.na && c < J.nb && (!J.upper || J.b0 + c >= J.a0 + li); };
+      if (ok(lj) || ok(lj + 3) || ok(lj + 1) || ok(lj + 2)) {
+        double re, im;
+        int ex;
+        overlap_quad(J, J.a0 + li, J.b0 + (ljb < J.nb ? ljb : J.nb - 1), re, im, ex);
+        if (lane < 16 && (lane & 3) == 0 && ok(ljb)) write_k(J, li, ljb, ldexp(re * re + im * im, 2 * ex));
+      }
+    } else if (li < J.na && lj < J.nb && (!J.upper || J.b0 + lj >= J.a0 + li)) {
+      if constexpr (PREC == QK_FP64) {
+        double re, im;
+        int ex;
+        overlap_wave<double, f64x4, double2, NT>(J, J.a0 + li, J.b0 + lj, re, im, ex);
+        if (lane == 0) write_k(J, li, lj, ldexp(re * re + im * im, 2 * ex));
+      } else if constexpr (PREC == QK_FP32) {
+        float re, im;
+        int ex;
+        overlap_wave<float, f32x4, float2, NT>(J, J.a0 + li, J.b0 + lj, re, im, ex);
+        if (lane == 0) write_k(J, li, lj, ldexp(double(re) * re + double(im) * im, 2 * ex));
+      } else {
+        double re, im;
+        if constexpr (PREC == QK_SPLIT_BF16) overlap_split_wave<WaveBf16, NT>(J, J.a0 + li, J.b0 + lj, s_e, re, im);
+        else overlap_split_wave<WaveI8, NT>(J, J.a0 + li, J.b0 + lj, s_e, re, im);
+        if (lane == 0) write_k(J, li, lj, re * re + im * im);
+      }
+    }
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(f)), hi = __builtin_amdgcn_readfirstlane(uint32_t(f >> 32));
+    next = int64_t((uint64_t(hi) << 32) | lo) + int64_t(gridDim.x);
+  }
+}
+
 template <int PREC>
 constexpr int threads_of() {
   return PREC == QK_SPLIT_BF16 ? kSplitThreads : PREC == QK_SPLIT_I8 ? kI8Threads : kThreads;
@@ -1817,7 +2108,8 @@ qk_status noalloc_scratch(void **ptr) {
 }
 
 // Kernel of a job.  The plain forms go by the largest bond of its two
-// batches (the pads are multiples of 32).  The lines lie at the MFMA tile
+// batches (the pads are multiples of 32), and so do the split forms, whose
+// site blocks are 64 x 64 at any bond.  The lines lie at the MFMA tile
 // sizes, 4, 16 and two tiles of 16: below a line the next kernel spends its
 // MFMAs on zeros and, with one pair per workgroup, most of its time in
 // barriers and idle waves.  One row of 1,000 165-site pairs at bond 2:
@@ -1828,19 +2120,18 @@ qk_status noalloc_scratch(void **ptr) {
 enum GramKernel { KERNEL_QUAD = 0, KERNEL_WAVE16, KERNEL_WAVE32, KERNEL_BLOCK, KERNEL_WIDE, KERNEL_KINDS };
 
 static int kernel_of(const GramJobDev &J, qk_precision prec) {
-  if (prec != QK_FP64 && prec != QK_FP32) return KERNEL_BLOCK;
   if (prec == QK_FP64 && J.max_bond <= 4) return KERNEL_QUAD;
   if (J.max_bond <= 32) return J.max_bond <= 16 ? KERNEL_WAVE16 : KERNEL_WAVE32;
   return J.max_pad <= 64 ? KERNEL_BLOCK : KERNEL_WIDE;
 }
 
-template <typename T, int NT>
+template <int PREC, int NT>
 static qk_status launch_wave(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int64_t n_tiles,
                              unsigned long long *counters, int th, int tw, hipStream_t stream, int *grid_out) {
   int dev = 0, cus = 256;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  auto kern = gram_wave_kernel<T, NT>;
+  auto kern = gram_wave_kernel<PREC, NT>;
   int per_cu = 0;
   QK_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64, 0));
   const int64_t units = n_tiles * (int64_t(th) * tw / (NT == 0 ? 4 : 1));
@@ -1946,16 +2237,19 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs_in, int max_pad, q
     auto *counters = reinterpret_cast<unsigned long long *>(ws + kGramCounterBytes * kind);
     auto *tiles_dev = reinterpret_cast<GramTile *>(ws + cbytes + jbytes) + pt.tile0;
     int wgs = 0;
+    auto wave = [&](auto launch) { return launch(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.th, pt.tw, stream, &wgs); };
     if (kind == KERNEL_QUAD)
-      st = launch_wave<double, 0>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.th, pt.tw, stream, &wgs);
+      st = wave(launch_wave<QK_FP64, 0>);
     else if (kind == KERNEL_WAVE16)
-      st = prec == QK_FP64
-               ? launch_wave<double, 1>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.th, pt.tw, stream, &wgs)
-               : launch_wave<float, 1>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.th, pt.tw, stream, &wgs);
+      st = prec == QK_FP64         ? wave(launch_wave<QK_FP64, 1>)
+           : prec == QK_FP32       ? wave(launch_wave<QK_FP32, 1>)
+           : prec == QK_SPLIT_BF16 ? wave(launch_wave<QK_SPLIT_BF16, 1>)
+                                   : wave(launch_wave<QK_SPLIT_I8, 1>);
     else if (kind == KERNEL_WAVE32)
-      st = prec == QK_FP64
-               ? launch_wave<double, 2>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.th, pt.tw, stream, &wgs)
-               : launch_wave<float, 2>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.th, pt.tw, stream, &wgs);
+      st = prec == QK_FP64         ? wave(launch_wave<QK_FP64, 2>)
+           : prec == QK_FP32       ? wave(launch_wave<QK_FP32, 2>)
+           : prec == QK_SPLIT_BF16 ? wave(launch_wave<QK_SPLIT_BF16, 2>)
+                                   : wave(launch_wave<QK_SPLIT_I8, 2>);
     else if (kind == KERNEL_WIDE)
       st = prec == QK_FP64
                ? launch_wide<QK_FP64>(jobs_dev, tiles_dev, pt.n_tiles, counters, cfg, pt.th, pt.tw, al, stream, &wgs)

@@ -19,6 +19,9 @@ from tests.gpu_util import require_gpu
 pytestmark = pytest.mark.gpu
 
 TOL = {"fp64": 1e-12, "fp32": 1e-5}
+# split forms: 31-bit codes of two operands at 2 x 13 products, 2^-31 each way
+# on |<a|b>|, twice that on K: 4 x 26 x 2^-31 = 4.8e-8
+SPLIT_TOL = {"split_bf16": 5e-8, "split_i8": 5e-8}
 
 
 def random_mps(rng, m, bond, near=None, eps=0.05):
@@ -56,6 +59,30 @@ def test_bonds_vs_oracle(bond):
             assert np.abs(Kb - K_ref[a0:a0 + na, b0:b0 + nb]).max() < tol
 
 
+@pytest.mark.parametrize("bond", [1, 2, 5, 15, 16, 17, 31, 32])
+def test_split_bonds(bond):
+    """The split forms at one pair per wave: against the oracle, and the bits
+    of the workgroup kernel, which takes the same states when a state of bond
+    40 stands beside them in the batch (so does FP32)."""
+    import paper_2411_09336_amd as q
+    torch = require_gpu()
+    rng = np.random.default_rng(1000 + bond)
+    m, n = 13, 9
+    base = random_mps(rng, m, bond)
+    mps = [random_mps(rng, m, bond, base) for _ in range(n)]
+    K_ref = np.array([[abs(ogram.overlap(a, c)) ** 2 for c in mps] for a in mps])
+    small = q.import_batch(mps)
+    mixed = q.import_batch(mps + [random_mps(rng, m, 40)])
+    for prec in ("split_bf16", "split_i8", "fp32"):
+        K = q.gram(small, precision=prec)
+        assert torch.equal(K, q.gram(mixed, precision=prec)[:n, :n])
+        row = q.gram_block(small, 2, 1, small, 2, 7, precision=prec)
+        assert torch.equal(K[2:3, 2:], row)
+        err = np.abs(K.cpu().numpy() - K_ref).max()
+        print(bond, prec, "max|dK|", err)
+        assert err < SPLIT_TOL.get(prec, 1e-5)
+
+
 @pytest.mark.parametrize("n,m", [(1, 1), (2, 2), (3, 3), (5, 6), (37, 9)])
 def test_sites_and_sizes(n, m):
     """Chains shorter than the sites loaded ahead, and triangles that end
@@ -68,7 +95,7 @@ def test_sites_and_sizes(n, m):
         mps = [random_mps(rng, m, bond, base) for _ in range(n)]
         K_ref = np.array([[abs(ogram.overlap(a, c)) ** 2 for c in mps] for a in mps])
         b = q.import_batch(mps)
-        for prec, tol in TOL.items():
+        for prec, tol in {**TOL, **SPLIT_TOL}.items():
             assert np.abs(q.gram(b, precision=prec).cpu().numpy() - K_ref).max() < tol
 
 
@@ -99,7 +126,7 @@ def test_jobs_of_several_kernels():
     for bond, m in ((2, 7), (16, 11), (32, 12), (40, 13)):
         base = random_mps(rng, m, bond)
         batches.append(q.import_batch([random_mps(rng, m, bond, base) for _ in range(6)]))
-    for prec in ("fp64", "fp32"):
+    for prec in ("fp64", "fp32", "split_bf16", "split_i8"):
         jobs = []
         for b in batches:
             jobs.append(dict(a=b, b=b, na=6, nb=6, upper_only=True,
