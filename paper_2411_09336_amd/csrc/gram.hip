@@ -762,21 +762,32 @@ __device__ inline void overlap_quad(const GramJobDev &J, int64_t ia, int64_t ib,
   const double2 *B = reinterpret_cast<const double2 *>(J.b_base) + ib * J.b_stride;
   const auto apad = gview(J.a_pad), bpad = gview(J.b_pad);
   const int m = J.m;
+  const auto abond = gview(J.a_bond), bbond = gview(J.b_bond);
   QuadSite w[kAhead];
-  int pa[kAhead + 1], pb[kAhead + 1];   // pads of the group of sites that is loaded next
+  // pads and bonds of the group of sites that is loaded next
+  int pa[kAhead + 1], pb[kAhead + 1], da[kAhead + 1], db[kAhead + 1];
+  auto shape = [&](int u, int l) {
+    pa[u] = apad[min(l, m)];
+    pb[u] = bpad[min(l, m)];
+    da[u] = abond[min(l, m)];
+    db[u] = bbond[min(l, m)];
+  };
 #pragma unroll
-  for (int u = 0; u <= kAhead; ++u) {
-    pa[u] = apad[min(u, m)];
-    pb[u] = bpad[min(u, m)];
-  }
-  // loads site u of the group (sites beyond m are not read)
+  for (int u = 0; u <= kAhead; ++u) shape(u, u);
+  // loads site u of the group (sites beyond m and the zeros beyond the bonds
+  // are not read: at bond 2 half the cache lines)
   auto load = [&](int l, int u) {
     if (l < m) {
       const int ra = k * pa[u + 1] + j, rb = k * pb[u + 1] + j, sa = pa[u] * pa[u + 1], sb = pb[u] * pb[u + 1];
-      w[u].a[0] = gload_c(A + ra);
-      w[u].a[1] = gload_c(A + sa + ra);
-      w[u].b[0] = gload_c(B + rb);
-      w[u].b[1] = gload_c(B + sb + rb);
+      w[u].a[0] = w[u].a[1] = w[u].b[0] = w[u].b[1] = make_double2(0.0, 0.0);
+      if (k < da[u] && j < da[u + 1]) {
+        w[u].a[0] = gload_c(A + ra);
+        w[u].a[1] = gload_c(A + sa + ra);
+      }
+      if (k < db[u] && j < db[u + 1]) {
+        w[u].b[0] = gload_c(B + rb);
+        w[u].b[1] = gload_c(B + sb + rb);
+      }
       A += 2 * sa;
       B += 2 * sb;
     }
@@ -788,11 +799,10 @@ __device__ inline void overlap_quad(const GramJobDev &J, int64_t ia, int64_t ib,
   for (int l0 = 0; l0 < m; l0 += kAhead) {
     pa[0] = pa[kAhead];
     pb[0] = pb[kAhead];
+    da[0] = da[kAhead];
+    db[0] = db[kAhead];
 #pragma unroll
-    for (int u = 1; u <= kAhead; ++u) {
-      pa[u] = apad[min(l0 + kAhead + u, m)];
-      pb[u] = bpad[min(l0 + kAhead + u, m)];
-    }
+    for (int u = 1; u <= kAhead; ++u) shape(u, l0 + kAhead + u);
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
       if (l0 + u < m) {

@@ -197,8 +197,13 @@ std::vector<GramConfig> gram_config_candidates(qk_precision prec, int max_pad);
 void store_gram_config(qk_precision prec, int max_pad, const GramConfig &c);
 void clear_gram_configs();
 
-// Simulation launchers.
-qk_status run_simulation(qk_mps_batch *b, const double *features_dev,
+// Simulation: the step list of a circuit under a bond cap and cutoff, with
+// the largest bond that its steps can leave at each cut, and its launchers.
+struct SimPlan;
+SimPlan *make_sim_plan(const std::vector<qk_gate> &gates, int m, int chi, double cutoff);
+void free_sim_plan(SimPlan *plan);
+const std::vector<int32_t> &sim_plan_bonds(const SimPlan *plan);
+qk_status run_simulation(qk_mps_batch *b, const SimPlan *plan, const double *features_dev,
                          const std::vector<qk_gate> &gates,
                          const qk_circuit_spec &spec, int chi, double cutoff,
                          hipStream_t stream, qk_progress_fn fn = nullptr,

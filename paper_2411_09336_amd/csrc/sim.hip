@@ -1602,8 +1602,86 @@ qk_status launch_repad_f64(const qk_mps_batch *src, qk_mps_batch *dst, hipStream
   return QK_OK;
 }
 
-qk_status run_simulation(qk_mps_batch *b, const double *features_dev, const std::vector<qk_gate> &gates,
-                         const qk_circuit_spec &spec, int chi, double cutoff, hipStream_t stream, qk_progress_fn fn,
+// The step list shared by every circuit: runs of Rz records, centre moves
+// and two-qubit gates in circuit order, then the final moves to the last
+// site.  gate_no[i] is the number of two-qubit gates done after step i when
+// step i is a gate, and 0 otherwise.
+struct SimPlan {
+  std::vector<SimStep> steps;
+  std::vector<int64_t> gate_no;
+  std::vector<int32_t> bond;   // largest bond that any step can leave at each cut
+  int size = 2;                // largest Jacobi matrix the bonds allow
+  bool wide = false;           // some step may lie next to a bond above kWideFrom
+};
+
+SimPlan *make_sim_plan(const std::vector<qk_gate> &gates, int m, int chi, double cutoff) {
+  auto *plan = new SimPlan();
+  auto &steps = plan->steps;
+  auto &gate_no = plan->gate_no;
+  int &size = plan->size;
+  bool &wide = plan->wide;
+  plan->bond.assign(m + 1, 1);
+  std::vector<int> next2q(gates.size(), -1);  // site of the next two-qubit gate
+  int nxt = -1;
+  for (int gi = int(gates.size()) - 1; gi >= 0; --gi) {
+    next2q[gi] = nxt;
+    if (gates[gi].op != OP_RZ) nxt = gates[gi].site;
+  }
+  // bond[l]: no circuit's bond can be larger here.  A two-site step leaves
+  // at most the rows and columns of its Jacobi matrix, a gate at most chi
+  // and, where the cutoff drops rounding noise (weights near 1e-30), the
+  // rank of its operator (Rxx: 2, SWAP: 4) times the bond before it.
+  std::vector<int> bond(m + 1, 1);
+  auto push = [&](SimStep x, int64_t g) {
+    if (x.kind == STEP_TWO_SITE) {
+      const int Dp = bond[x.p], Dn = bond[x.p + 2];
+      int &Dm = bond[x.p + 1];
+      const bool right = x.mode == GATE_RIGHT || x.mode == MOVE_RIGHT;
+      if (x.mode == MOVE_RIGHT || x.mode == MOVE_LEFT) {
+        size = std::max({size, 2 * Dp, 2 * Dn, Dm});
+        Dm = std::min(Dm, 2 * (right ? Dp : Dn));
+      } else {
+        size = std::max({size, 2 * Dp, 2 * Dn});
+        const int rank = cutoff > 1e-20 ? (x.op == OP_RXX ? 2 : 4) * Dm : chi;
+        Dm = std::min({chi, 2 * Dp, 2 * Dn, rank});
+      }
+      wide |= Dp > kWideFrom || Dn > kWideFrom;
+      x.nr = Dm;
+      plan->bond[x.p + 1] = std::max(plan->bond[x.p + 1], Dm);
+    }
+    steps.push_back(x);
+    gate_no.push_back(g);
+  };
+  int center = 0;
+  int64_t d2q = 0;
+  size_t gi = 0;
+  while (gi < gates.size()) {
+    if (gates[gi].op == OP_RZ) {
+      size_t ge = gi;
+      while (ge < gates.size() && gates[ge].op == OP_RZ) ++ge;
+      push({STEP_RZ, 0, 0, 0, -1, -1, int32_t(gi), int32_t(ge - gi)}, 0);
+      gi = ge;
+      continue;
+    }
+    const int p = gates[gi].site;
+    for (; center < p; ++center) push({STEP_TWO_SITE, center, MOVE_RIGHT, OP_ID, -1, -1, -1, 0}, 0);
+    for (; center > p + 1; --center) push({STEP_TWO_SITE, center - 1, MOVE_LEFT, OP_ID, -1, -1, -1, 0}, 0);
+    const bool absorb_right = next2q[gi] < 0 || next2q[gi] > p;
+    push({STEP_TWO_SITE, p, absorb_right ? GATE_RIGHT : GATE_LEFT, gates[gi].op == 1 ? OP_RXX : OP_SWAP,
+          gates[gi].feat_i, gates[gi].feat_j, int32_t(d2q), 0},
+         d2q + 1);
+    ++d2q;
+    center = absorb_right ? p + 1 : p;
+    ++gi;
+  }
+  for (; center < m - 1; ++center) push({STEP_TWO_SITE, center, MOVE_RIGHT, OP_ID, -1, -1, -1, 0}, 0);
+  return plan;
+}
+void free_sim_plan(SimPlan *plan) { delete plan; }
+const std::vector<int32_t> &sim_plan_bonds(const SimPlan *plan) { return plan->bond; }
+
+qk_status run_simulation(qk_mps_batch *b, const SimPlan *plan, const double *features_dev,
+                         const std::vector<qk_gate> &gates, const qk_circuit_spec &spec, int chi, double cutoff, hipStream_t stream, qk_progress_fn fn,
                          void *user, int64_t every, int64_t graph_circuits, int32_t *trace) {
   const int64_t n = b->n;
   const int m = b->m;
@@ -1630,69 +1708,10 @@ qk_status run_simulation(qk_mps_batch *b, const double *features_dev, const std:
   const int64_t grid = graph ? std::min(n, graph_circuits) : n;
   const int64_t replays = (n + grid - 1) / grid;
 
-  // The step list shared by every circuit: runs of Rz records, centre moves
-  // and two-qubit gates in circuit order, then the final moves to the last
-  // site.  gate_no[i] is the number of two-qubit gates done after step i
-  // when step i is a gate, and 0 otherwise.
-  std::vector<SimStep> steps;
-  std::vector<int64_t> gate_no;
-  int size = 2;        // largest Jacobi matrix the bonds allow
-  bool wide = false;   // some step may lie next to a bond above kWideFrom
-  {
-    std::vector<int> next2q(gates.size(), -1);  // site of the next two-qubit gate
-    int nxt = -1;
-    for (int gi = int(gates.size()) - 1; gi >= 0; --gi) {
-      next2q[gi] = nxt;
-      if (gates[gi].op != OP_RZ) nxt = gates[gi].site;
-    }
-    // bond[l]: no circuit's bond can be larger here.  A two-site step leaves
-    // at most the rows and columns of its Jacobi matrix, a gate at most chi
-    // and, where the cutoff drops rounding noise (weights near 1e-30), the
-    // rank of its operator (Rxx: 2, SWAP: 4) times the bond before it.
-    std::vector<int> bond(m + 1, 1);
-    auto push = [&](SimStep x, int64_t g) {
-      if (x.kind == STEP_TWO_SITE) {
-        const int Dp = bond[x.p], Dn = bond[x.p + 2];
-        int &Dm = bond[x.p + 1];
-        const bool right = x.mode == GATE_RIGHT || x.mode == MOVE_RIGHT;
-        if (x.mode == MOVE_RIGHT || x.mode == MOVE_LEFT) {
-          size = std::max({size, 2 * Dp, 2 * Dn, Dm});
-          Dm = std::min(Dm, 2 * (right ? Dp : Dn));
-        } else {
-          size = std::max({size, 2 * Dp, 2 * Dn});
-          const int rank = cutoff > 1e-20 ? (x.op == OP_RXX ? 2 : 4) * Dm : chi;
-          Dm = std::min({chi, 2 * Dp, 2 * Dn, rank});
-        }
-        wide |= Dp > kWideFrom || Dn > kWideFrom;
-        x.nr = Dm;
-      }
-      steps.push_back(x);
-      gate_no.push_back(g);
-    };
-    int center = 0;
-    int64_t d2q = 0;
-    size_t gi = 0;
-    while (gi < gates.size()) {
-      if (gates[gi].op == OP_RZ) {
-        size_t ge = gi;
-        while (ge < gates.size() && gates[ge].op == OP_RZ) ++ge;
-        push({STEP_RZ, 0, 0, 0, -1, -1, int32_t(gi), int32_t(ge - gi)}, 0);
-        gi = ge;
-        continue;
-      }
-      const int p = gates[gi].site;
-      for (; center < p; ++center) push({STEP_TWO_SITE, center, MOVE_RIGHT, OP_ID, -1, -1, -1, 0}, 0);
-      for (; center > p + 1; --center) push({STEP_TWO_SITE, center - 1, MOVE_LEFT, OP_ID, -1, -1, -1, 0}, 0);
-      const bool absorb_right = next2q[gi] < 0 || next2q[gi] > p;
-      push({STEP_TWO_SITE, p, absorb_right ? GATE_RIGHT : GATE_LEFT, gates[gi].op == 1 ? OP_RXX : OP_SWAP,
-            gates[gi].feat_i, gates[gi].feat_j, int32_t(d2q), 0},
-           d2q + 1);
-      ++d2q;
-      center = absorb_right ? p + 1 : p;
-      ++gi;
-    }
-    for (; center < m - 1; ++center) push({STEP_TWO_SITE, center, MOVE_RIGHT, OP_ID, -1, -1, -1, 0}, 0);
-  }
+  const auto &steps = plan->steps;
+  const auto &gate_no = plan->gate_no;
+  const int size = plan->size;
+  const bool wide = plan->wide;
 
   // Device buffers: gate records, step list, SVD scratch of one slot per
   // workgroup of a launch, and (graph mode) the first circuit of a replay.
