@@ -276,10 +276,13 @@ def circuit_compile(spec: CircuitSpec) -> np.ndarray:
 
 
 class MPSBatch:
-    """Owning handle of a device-resident MPS batch."""
+    """Owning handle of a device-resident MPS batch.  A batch's numbers of
+    states and sites never change; ``n`` and ``m`` give them when they are
+    known without asking the library, whose answer waits for the device."""
 
-    def __init__(self, handle: int):
+    def __init__(self, handle: int, n: Optional[int] = None, m: Optional[int] = None):
         self._h = C.c_void_p(handle)
+        self._n, self._m = n, m
         if _LIVE is not None:
             _LIVE.add(self)
 
@@ -291,6 +294,7 @@ class MPSBatch:
         if self._h and self._h.value:
             _load().mps_batch_free(self._h)
             self._h = C.c_void_p(0)
+            self._n = self._m = None   # a freed batch is refused, not sized
 
     def __del__(self):
         try:
@@ -303,22 +307,28 @@ class MPSBatch:
         _check(_load().mps_batch_info(self._h, C.byref(inf)))
         return {f: getattr(inf, f) for f, _ in _Info._fields_}
 
+    def _size(self):
+        if self._n is None or self._m is None:
+            inf = self.info()
+            self._n, self._m = inf["n"], inf["m"]
+        return self._n, self._m
+
     @property
     def n(self) -> int:
-        return self.info()["n"]
+        return self._size()[0]
 
     @property
     def m(self) -> int:
-        return self.info()["m"]
+        return self._size()[1]
 
     def bond_dims(self) -> np.ndarray:
-        inf = self.info()
-        out = np.zeros((inf["n"], inf["m"] + 1), dtype=np.int32)
+        n, m = self._size()
+        out = np.zeros((n, m + 1), dtype=np.int32)
         _check(_load().mps_batch_bond_dims(self._h, out.ctypes.data))
         return out
 
     def trunc_stats(self):
-        n = self.info()["n"]
+        n = self._size()[0]
         disc = np.zeros(n)
         deg = np.zeros(n, dtype=np.int32)
         _check(_load().mps_batch_trunc_stats(self._h, disc.ctypes.data, deg.ctypes.data))
@@ -360,7 +370,7 @@ class MPSBatch:
         h = C.c_void_p(0)
         _check(_load().mps_batch_gather(self._h, idx.ctypes.data, len(idx), mask, _stream_ptr(stream),
                                         C.byref(h)))
-        return MPSBatch(h.value)
+        return MPSBatch(h.value, len(idx), self._m)
 
 
 def load_batch(path: str, stream=None) -> MPSBatch:
@@ -388,7 +398,7 @@ def import_batch(mps_list: Sequence[Sequence[np.ndarray]], stream=None) -> MPSBa
     flat = np.ascontiguousarray(np.concatenate(parts)).view(np.float64)
     h = C.c_void_p(0)
     _check(_load().mps_batch_import(flat.ctypes.data, dims.ctypes.data, n, m, _stream_ptr(stream), C.byref(h)))
-    return MPSBatch(h.value)
+    return MPSBatch(h.value, n, m)
 
 
 def simulate(features, spec: CircuitSpec, chi: int, cutoff: float, stream=None, progress=None,
@@ -420,7 +430,7 @@ def simulate(features, spec: CircuitSpec, chi: int, cutoff: float, stream=None, 
         _check(_load().mps_simulate_progress(C.c_void_p(x.data_ptr()), x.shape[0], C.byref(cs), int(chi),
                                              float(cutoff), _stream_ptr(stream), cb, None, int(every),
                                              C.byref(h)))
-    return MPSBatch(h.value)
+    return MPSBatch(h.value, x.shape[0], spec.n_qubits)
 
 
 def simulate_trace(features, spec: CircuitSpec, chi: int, cutoff: float, stream=None):
@@ -440,7 +450,7 @@ def simulate_trace(features, spec: CircuitSpec, chi: int, cutoff: float, stream=
     h = C.c_void_p(0)
     _check(_load().mps_simulate_trace(C.c_void_p(x.data_ptr()), x.shape[0], C.byref(cs), int(chi), float(cutoff),
                                       C.c_void_p(trace.data_ptr()), _stream_ptr(stream), C.byref(h)))
-    return MPSBatch(h.value), trace
+    return MPSBatch(h.value, x.shape[0], spec.n_qubits), trace
 
 
 def autotune(batch: MPSBatch, precision="fp64", sample: int = 64, stream=None) -> dict:

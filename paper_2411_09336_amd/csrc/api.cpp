@@ -135,9 +135,7 @@ static void batch_release(qk_mps_batch *b) {
   int cur = 0;
   (void)hipGetDevice(&cur);
   (void)hipSetDevice(b->device);
-  void *ptrs[] = {b->f64,          b->f32,        b->sbf16,       b->si8,       b->dims_dev,
-                  b->pad_dev,      b->bond_dev,    b->site_off_dev, b->split_off_dev, b->i8_off_dev, b->disc_dev,
-                  b->maxdisc_dev,  b->degen_dev,   b->unconv_dev};
+  void *ptrs[] = {b->f64, b->f32, b->sbf16, b->si8, b->meta};
   // the batch may still be in use by enqueued work: wait before the memory
   // goes back to the allocator
   if (b->alloc.custom()) (void)hipDeviceSynchronize();
@@ -159,38 +157,50 @@ qk_status batch_create(int64_t n, int32_t m, const std::vector<int32_t> &pad, co
   b->pad = pad;
   b->bond = bond;
   compute_layout(b);
-  auto alloc = [&](void **p, size_t bytes) -> bool {
-    if (bytes == 0) bytes = 16;
-    *p = dev_alloc(b->alloc, bytes, stream, false);
-    if (!*p) return false;
-    return hipMemsetAsync(*p, 0, bytes, stream) == hipSuccess;
+  // One block for the small arrays: the layout (read-only), then what the
+  // simulation writes, each array at a multiple of 16 bytes.
+  const size_t nn = size_t(std::max<int64_t>(n, 1)), m1 = size_t(m + 1);
+  size_t bytes = 0;
+  auto place = [&](size_t size) {
+    const size_t at = bytes;
+    bytes += (size + 15) / 16 * 16;
+    return at;
   };
-  const size_t nn = size_t(std::max<int64_t>(n, 1));
-  bool good = (!with_f64 || alloc((void **)&b->f64, sizeof(double2) * nn * size_t(b->mps_stride))) &&
-              alloc((void **)&b->dims_dev, sizeof(int32_t) * nn * size_t(m + 1)) &&
-              alloc((void **)&b->pad_dev, sizeof(int32_t) * size_t(m + 1)) &&
-              alloc((void **)&b->bond_dev, sizeof(int32_t) * size_t(m + 1)) &&
-              alloc((void **)&b->site_off_dev, sizeof(int64_t) * size_t(m + 1)) &&
-              alloc((void **)&b->split_off_dev, sizeof(int64_t) * size_t(m + 1)) &&
-              alloc((void **)&b->i8_off_dev, sizeof(int64_t) * size_t(m + 1)) &&
-              alloc((void **)&b->disc_dev, sizeof(double) * nn) &&
-              alloc((void **)&b->maxdisc_dev, sizeof(double) * nn) &&
-              alloc((void **)&b->degen_dev, sizeof(int32_t) * nn) &&
-              alloc((void **)&b->unconv_dev, sizeof(int32_t) * nn);
-  if (!good) {
+  const size_t o_site = place(8 * m1), o_split = place(8 * m1), o_i8 = place(8 * m1), o_pad = place(4 * m1),
+               o_bond = place(4 * m1), layout = bytes;
+  const size_t o_dims = place(4 * nn * m1), o_disc = place(8 * nn), o_maxdisc = place(8 * nn), o_degen = place(4 * nn),
+               o_unconv = place(4 * nn);
+  std::vector<uint8_t> host(layout, 0);
+  std::memcpy(host.data() + o_site, b->site_off.data(), 8 * m1);
+  std::memcpy(host.data() + o_split, b->split_off.data(), 8 * m1);
+  std::memcpy(host.data() + o_i8, b->i8_off.data(), 8 * m1);
+  std::memcpy(host.data() + o_pad, pad.data(), 4 * m1);
+  std::memcpy(host.data() + o_bond, bond.data(), 4 * m1);
+  const size_t f64_bytes = std::max<size_t>(sizeof(double2) * nn * size_t(b->mps_stride), 16);
+  b->meta = static_cast<uint8_t *>(dev_alloc(b->alloc, bytes, stream, false));
+  if (with_f64 && b->meta) b->f64 = static_cast<double2 *>(dev_alloc(b->alloc, f64_bytes, stream, false));
+  if (!b->meta || (with_f64 && !b->f64) ||
+      hipMemsetAsync(b->meta + layout, 0, bytes - layout, stream) != hipSuccess ||
+      (with_f64 && hipMemsetAsync(b->f64, 0, f64_bytes, stream) != hipSuccess)) {
     (void)hipGetLastError();
     batch_release(b);
     return fail(QK_ENOMEM, "device allocation failed for an MPS batch of " + std::to_string(n) +
                                " x " + std::to_string(m) + " sites");
   }
-  if (hipMemcpyAsync(b->pad_dev, pad.data(), sizeof(int32_t) * (m + 1), hipMemcpyHostToDevice, stream) != hipSuccess ||
-      hipMemcpyAsync(b->bond_dev, bond.data(), sizeof(int32_t) * (m + 1), hipMemcpyHostToDevice, stream) != hipSuccess ||
-      hipMemcpyAsync(b->site_off_dev, b->site_off.data(), sizeof(int64_t) * (m + 1), hipMemcpyHostToDevice, stream) != hipSuccess ||
-      hipMemcpyAsync(b->split_off_dev, b->split_off.data(), sizeof(int64_t) * (m + 1), hipMemcpyHostToDevice, stream) != hipSuccess ||
-      hipMemcpyAsync(b->i8_off_dev, b->i8_off.data(), sizeof(int64_t) * (m + 1), hipMemcpyHostToDevice, stream) != hipSuccess ||
-      hipStreamSynchronize(stream) != hipSuccess) {
+  b->site_off_dev = reinterpret_cast<int64_t *>(b->meta + o_site);
+  b->split_off_dev = reinterpret_cast<int64_t *>(b->meta + o_split);
+  b->i8_off_dev = reinterpret_cast<int64_t *>(b->meta + o_i8);
+  b->pad_dev = reinterpret_cast<int32_t *>(b->meta + o_pad);
+  b->bond_dev = reinterpret_cast<int32_t *>(b->meta + o_bond);
+  b->dims_dev = reinterpret_cast<int32_t *>(b->meta + o_dims);
+  b->disc_dev = reinterpret_cast<double *>(b->meta + o_disc);
+  b->maxdisc_dev = reinterpret_cast<double *>(b->meta + o_maxdisc);
+  b->degen_dev = reinterpret_cast<int32_t *>(b->meta + o_degen);
+  b->unconv_dev = reinterpret_cast<int32_t *>(b->meta + o_unconv);
+  const qk_status st = upload(b->meta, host.data(), layout, stream);
+  if (st != QK_OK) {
     batch_release(b);
-    return fail(QK_EDEVICE, "copy of batch layout failed");
+    return st;
   }
   *out = b;
   return QK_OK;
@@ -350,8 +360,9 @@ static qk_status shrink_to_bonds(qk_mps_batch **pb, hipStream_t stream) {
   for (int l = 0; l <= m; ++l) pad[l] = std::min(pad_of(bond[l]), b->pad[l]);
   if (pad == b->pad) {
     b->bond = bond;
-    QK_HIP_CHECK(hipMemcpyAsync(b->bond_dev, b->bond.data(), sizeof(int32_t) * bond.size(), hipMemcpyHostToDevice, stream));
-    QK_HIP_CHECK(hipStreamSynchronize(stream));
+    const qk_status up = upload(b->bond_dev, b->bond.data(), sizeof(int32_t) * bond.size(), stream);
+    if (up != QK_OK) return up;
+    QK_HIP_CHECK(hipStreamSynchronize(stream));   // the batch may be used on any stream
     return QK_OK;
   }
   qk_mps_batch *c = nullptr;

@@ -2152,6 +2152,40 @@ static qk_status launch_wave(const GramJobDev *jobs_dev, const GramTile *tiles_d
   return QK_OK;
 }
 
+// Small host data for the device: carried in the arguments of a kernel,
+// which the runtime copies at the launch, so neither a staging copy nor a
+// wait for the stream is needed (a pageable copy and its wait cost a Gram
+// call about 30 us, and kept the host from running ahead of the device).
+struct HostWords {
+  uint32_t w[896];
+};
+__global__ void write_words_kernel(uint32_t *dst, HostWords v, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) dst[i] = v.w[i];
+}
+
+qk_status upload(void *dst, const void *src, size_t bytes, hipStream_t stream) {
+  constexpr size_t kChunk = sizeof(HostWords), kMost = 6 * kChunk;   // above, one copy is cheaper than the launches
+  if (bytes > kMost || bytes % 4) {
+    // the host buffer must stay alive until the copy has run
+    if (hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, stream) != hipSuccess ||
+        hipStreamSynchronize(stream) != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(QK_EDEVICE, "host-to-device copy failed");
+    }
+    return QK_OK;
+  }
+  for (size_t o = 0; o < bytes; o += kChunk) {
+    HostWords v;
+    const size_t n = std::min(kChunk, bytes - o);
+    std::memcpy(&v, static_cast<const uint8_t *>(src) + o, n);
+    hipLaunchKernelGGL(write_words_kernel, dim3(unsigned((n / 4 + 255) / 256)), dim3(256), 0, stream,
+                       reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(dst) + o), v, int(n / 4));
+    QK_HIP_CHECK(hipGetLastError());
+  }
+  return QK_OK;
+}
+
 qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs_in, int max_pad, qk_precision prec,
                           const GramConfig &cfg, hipStream_t stream, qk_gram_stats *stats, void *ws_given,
                           size_t ws_cap) {
@@ -2212,7 +2246,7 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs_in, int max_pad, q
   const size_t jbytes = sizeof(GramJobDev) * jobs.size();
   const size_t tbytes = sizeof(GramTile) * tiles.size();
   // workspace: [queue counters of every kind | job table | tile list],
-  // uploaded in one copy whose counter bytes are zero (no memset node in the
+  // uploaded as one block whose counter bytes are zero (no memset node in the
   // stream)
   const size_t cbytes = kGramCounterBytes * KERNEL_KINDS;
   const size_t ws_bytes = cbytes + jbytes + tbytes;
@@ -2231,11 +2265,7 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs_in, int max_pad, q
   }
   auto *jobs_dev = reinterpret_cast<GramJobDev *>(ws + cbytes);
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
-  qk_status st = QK_OK;
-  if (hipMemcpyAsync(ws, host.data(), ws_bytes, hipMemcpyHostToDevice, stream) != hipSuccess ||
-      // the host buffer must stay alive until the copy has run
-      hipStreamSynchronize(stream) != hipSuccess)
-    st = fail(QK_EDEVICE, "upload of the Gram work queue failed");
+  qk_status st = upload(ws, host.data(), ws_bytes, stream);
   if (st == QK_OK && stats &&
       (hipEventCreate(&ev0) != hipSuccess || hipEventCreate(&ev1) != hipSuccess ||
        hipEventRecord(ev0, stream) != hipSuccess))

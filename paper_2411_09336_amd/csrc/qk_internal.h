@@ -85,6 +85,10 @@ DevAlloc allocator_for_current_device();
 void *dev_alloc(const DevAlloc &al, size_t bytes, hipStream_t stream, bool scratch);
 void dev_free(const DevAlloc &al, void *p, hipStream_t stream, bool scratch);
 
+// Host bytes to device memory in stream order; the source may be reused when
+// the call returns.
+qk_status upload(void *dst, const void *src, size_t bytes, hipStream_t stream);
+
 }  // namespace qk
 
 // Opaque batch.  Every MPS of a batch has m sites with the pad profile
@@ -112,6 +116,7 @@ struct qk_mps_batch {
   uint8_t *sbf16 = nullptr;        // packed on demand
   uint8_t *si8 = nullptr;          // packed on demand
 
+  uint8_t *meta = nullptr;         // one block that holds the arrays below
   int32_t *dims_dev = nullptr;     // n * (m + 1)
   int32_t *pad_dev = nullptr;      // m + 1
   int32_t *bond_dev = nullptr;     // m + 1

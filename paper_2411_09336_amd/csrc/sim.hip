@@ -40,6 +40,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "qk_internal.h"
@@ -1716,34 +1717,28 @@ qk_status run_simulation(qk_mps_batch *b, const SimPlan *plan, const double *fea
   // Device buffers: gate records, step list, SVD scratch of one slot per
   // workgroup of a launch, and (graph mode) the first circuit of a replay.
   const DevAlloc al = allocator_for_current_device();
-  void *recs_dev = nullptr, *steps_dev = nullptr, *scratch = nullptr, *wscratch = nullptr, *base_dev = nullptr,
-       *params_dev = nullptr;
+  const int nk = size <= 16 ? 16 : size <= 32 ? 32 : size <= 64 ? 64 : kSvMaxN;
+  const size_t steps_bytes = sizeof(SimStep) * steps.size(), recs_bytes = sizeof(qk_gate) * gates.size();
+  // [parameters | steps | gate records | first circuit of a replay]
+  const size_t steps_at = (sizeof(SvParams) + 15) / 16 * 16, recs_at = steps_at + steps_bytes;
+  const size_t base_at = (recs_at + recs_bytes + 15) / 16 * 16, block_bytes = base_at + 16;
+  void *block = nullptr, *scratch = nullptr, *wscratch = nullptr;
   auto release = [&]() {
-    for (void *ptr : {recs_dev, steps_dev, scratch, wscratch, base_dev, params_dev})
+    for (void *ptr : {block, scratch, wscratch})
       if (ptr) dev_free(al, ptr, stream, true);
   };
-  recs_dev = dev_alloc(al, sizeof(qk_gate) * std::max<size_t>(gates.size(), 1), stream, true);
-  steps_dev = dev_alloc(al, sizeof(SimStep) * std::max<size_t>(steps.size(), 1), stream, true);
-  const int nk = size <= 16 ? 16 : size <= 32 ? 32 : size <= 64 ? 64 : kSvMaxN;
+  block = dev_alloc(al, block_bytes, stream, true);
   if (nk > 32) scratch = dev_alloc(al, sizeof(double2) * nk * nk * size_t(grid), stream, true);
   if (wide) wscratch = dev_alloc(al, sizeof(double2) * kWideSlot * size_t(grid), stream, true);
-  if (graph) base_dev = dev_alloc(al, 256, stream, true);
-  params_dev = dev_alloc(al, sizeof(SvParams), stream, true);
-  if (!recs_dev || !steps_dev || !params_dev || (nk > 32 && !scratch) || (wide && !wscratch) || (graph && !base_dev)) {
+  if (!block || (nk > 32 && !scratch) || (wide && !wscratch)) {
     release();
     return fail(QK_ENOMEM, "device allocation of the simulation buffers failed");
   }
-  if ((!gates.empty() && hipMemcpyAsync(recs_dev, gates.data(), sizeof(qk_gate) * gates.size(),
-                                        hipMemcpyHostToDevice, stream) != hipSuccess) ||
-      (!steps.empty() && hipMemcpyAsync(steps_dev, steps.data(), sizeof(SimStep) * steps.size(),
-                                        hipMemcpyHostToDevice, stream) != hipSuccess)) {
-    (void)hipGetLastError();
-    release();
-    return fail(QK_EDEVICE, "copy of the gate and step lists failed");
-  }
-  const auto *recs = static_cast<const qk_gate *>(recs_dev);
-  const auto *steps_d = static_cast<const SimStep *>(steps_dev);
-  auto *base = static_cast<int64_t *>(base_dev);
+  auto *block8 = static_cast<uint8_t *>(block);
+  const auto *params = reinterpret_cast<const SvParams *>(block8);
+  const auto *steps_d = reinterpret_cast<const SimStep *>(block8 + steps_at);
+  const auto *recs = reinterpret_cast<const qk_gate *>(block8 + recs_at);
+  auto *base = graph ? reinterpret_cast<int64_t *>(block8 + base_at) : nullptr;
 
   SvParams P{};
   P.f64 = b->f64;
@@ -1769,12 +1764,17 @@ qk_status run_simulation(qk_mps_batch *b, const SimPlan *plan, const double *fea
   P.trace = trace;
   P.trace_n2q = n2q;
   P.base = base;
-  if (hipMemcpyAsync(params_dev, &P, sizeof(P), hipMemcpyHostToDevice, stream) != hipSuccess) {
-    (void)hipGetLastError();
-    release();
-    return fail(QK_EDEVICE, "copy of the simulation parameters failed");
+  {
+    std::vector<uint8_t> host(block_bytes, 0);
+    std::memcpy(host.data(), &P, sizeof(P));
+    if (steps_bytes) std::memcpy(host.data() + steps_at, steps.data(), steps_bytes);
+    if (recs_bytes) std::memcpy(host.data() + recs_at, gates.data(), recs_bytes);
+    const qk_status up = upload(block, host.data(), block_bytes, stream);
+    if (up != QK_OK) {
+      release();
+      return up;
+    }
   }
-  const auto *params = static_cast<const SvParams *>(params_dev);
 
   // The launches of one pass over `grid` circuits on stream s: the |+>
   // state, the step list in launches of at most kMaxChunkSteps steps (a
