@@ -222,20 +222,27 @@ typedef uint8_t __attribute__((address_space(3))) LdsBytes;
 constexpr int kKC = 16;  // contraction chunk of the pair product staged in LDS
 
 // Two-site steps are compiled for Jacobi matrices up to N x N (N = 16, 32,
-// 64, 128) on W waves.  A wave's lanes are N / 2 column pairs (lane cp of a
-// row group holds column positions 2 cp and 2 cp + 1) times RG row groups of
-// ROWS rows, so small matrices fill the lanes, and one wave needs neither
-// LDS round trips nor barriers between its rows and columns.
+// 64, 128) in workgroups of W waves, of which WA hold the matrix.  A wave's
+// lanes are N / 2 column pairs (lane cp of a row group holds column positions
+// 2 cp and 2 cp + 1) times RG row groups of ROWS rows, so small matrices fill
+// the lanes, and one wave needs neither LDS round trips nor barriers between
+// its rows and columns.  More waves than WA only lengthen the rounds of a
+// small matrix: each reads the round's sums from LDS.
 template <int N, int W>
 struct Layout {
+  static constexpr int WA = N == 32 ? (W < 4 ? W : 4) : N == 64 ? (W < 8 ? W : 8) : W;
   static constexpr int LC = N / 2;                 // column pairs
   static constexpr int RG = 64 / LC;               // row groups of a wave
-  static constexpr int GR = W * RG;                // row groups of the workgroup
+  static constexpr int GR = WA * RG;               // row groups of the matrix
   static constexpr int ROWS = N > GR ? N / GR : 1; // rows per group
   static constexpr int HROWS = N / 2 > GR ? N / 2 / GR : 1;   // of a block of N / 2 rows
   static constexpr int SLOTS = GR * ROWS;
   static constexpr int T = 64 * W;
   static constexpr bool kLds = N <= 32;            // pair product and isometry in LDS
+  // rotations of a round: formed by every wave for its own lanes from the
+  // waves' partial sums, or (N = 128, where every wave would read 16 of them
+  // for each of 64 pairs) by four waves and read back
+  static constexpr bool kOwn = N <= 64;
 };
 
 // Barrier of the W waves that run a step; with one wave, its own order.
@@ -257,16 +264,17 @@ struct StepLds {
       double2 L[kKC][Y::SLOTS];
       double2 R[kKC][N];
     } stage;                       // contraction chunks (dead once the Jacobi matrix is built)
-    double2 red[2][W][Y::LC];      // [0]: (|X|^2, |Y|^2), [1]: <X, Y>; per wave and pair
+    double2 red[2][2][Y::WA][Y::LC];   // per round type: (|X|^2, |Y|^2) and <X, Y> by wave and pair
     double2 U[Y::kLds ? N * N : 1];// isometry (row-major), after the sweeps
   };
   double2 P2[Y::kLds ? N * N : 1]; // pair product
   double2 lqw[N];                  // Householder vector of an LQ step
-  double upd[2][Y::LC][8];         // per round type and lane: cA, sA, -, -, cB, sB (W > 1)
-  double w[N];                     // squared norm of the column at each position (W > 1); row norms during the LQ
+  double rot[2][3][Y::kOwn ? 1 : Y::LC + 1];   // per round type: c, sigma of pair p at p + 1 (N = 128)
+  double w[N];                     // row norms during the LQ, then (N = 128) column norms by position
   double norm[N], sorted[N];
   double part[W];
   double beta, nrm;
+  int flag;
   int rank[N];
   int k;
 };
@@ -343,7 +351,7 @@ __device__ inline void staged_tile_gemm(int K, const FL &ldL, const FR &ldR, Ste
       sh.stage.R[kk][x] = k0 + kk < K ? ldR(k0 + kk, x) : make_double2(0.0, 0.0);
     }
     step_sync<W>();
-    const int kc = min(kKC, K - k0);
+    const int kc = wave < Y::WA ? min(kKC, K - k0) : 0;
     for (int kk = 0; kk < kc; ++kk) {
       const double2 r0 = sh.stage.R[kk][2 * cp], r1 = sh.stage.R[kk][2 * cp + 1];
 #pragma unroll
@@ -406,113 +414,70 @@ __device__ inline Rotation rotation(double a, double b, double x, double y, doub
 
 // One round of the parallel Jacobi sweep.  The pair of a lane is (X, Y) =
 // (A, B) for TYPE 0 and (B_l, A_{l+1}) for TYPE 1; the rotated columns are
-// stored exchanged, Y' in the slot of X and X' in the slot of Y.  Every lane
-// then forms A' = cA P + sA A, B' = cB Q + sB B with the partners (P, Q) =
-// (B, A) for TYPE 0 and (B_{l-1}, A_{l+1}) for TYPE 1 (c real, s complex;
-// columns without a pair: c = 0, s = 1).  Returns whether this wave rotated
-// some pair by more than kJacobiLarge (relative |<X,Y>|).
+// stored exchanged, Y' in the slot of X and X' in the slot of Y: with the
+// pair's (c, sigma), TYPE 0 forms A' = c B + conj(sigma) A, B' = c A - sigma B,
+// TYPE 1 B' = c A_{l+1} + conj(sigma) B and, with the pair of lane l - 1,
+// A' = c B_{l-1} - sigma A.  Where there is no pair, (0, 1) keeps the column
+// up to its sign.  Returns whether some pair seen by this wave was rotated by
+// more than kJacobiLarge (relative |<X,Y>|).
 //
 // Column norms: a FULL round reduces |X|^2 and |Y|^2 with <X, Y> and stores
 // them; the other rounds reduce <X, Y> only and update the stored norms by
 // |X'|^2 = |X|^2 - t |<X,Y>|, |Y'|^2 = |Y|^2 + t |<X,Y>| (t = s / c), which
 // holds exactly for the rotation above.  The first round of every sweep is
 // FULL, so rounding in the updates never outlives a sweep.
+//
+// A round is a chain of dependent FP64 operations (~24 cycles each), LDS
+// accesses and barriers.  Up to 64 x 64 every wave adds up the partial sums
+// and forms the rotations of its own lanes (identical in all waves), which
+// takes one barrier; with four waves forming them for all, two barriers and
+// conflicting reads of the results, a 64 x 64 round took 3,700 cycles and a
+// 32 x 32 one 4,600 (16 waves).
 template <int N, int W>
 struct Columns {
   static constexpr int ROWS = Layout<N, W>::ROWS;
   double Ar[ROWS], Ai[ROWS], Br[ROWS], Bi[ROWS];
-  double wA, wB;   // squared norms (W == 1)
+  double wA, wB;   // squared norms (kOwn)
 };
 
 template <int N, int W, int TYPE, bool FULL>
 __device__ __forceinline__ bool jacobi_round(Columns<N, W> &M, StepLds<N, W> &sh, int wave, int H, double zero_w) {
   using Y = Layout<N, W>;
-  constexpr int ROWS = Y::ROWS, LC = Y::LC;
+  constexpr int ROWS = Y::ROWS, LC = Y::LC, WA = Y::WA;
   // The lane index is formed afresh every round (two instructions the
   // compiler cannot hoist), so the LDS addresses derived from it are not
   // held, or spilled, across the sweep loop.
   int lane;
   asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
-  const int cp = lane % LC;
-  double Nr[ROWS], Ni[ROWS];  // A_{l+1} (TYPE 1)
-  if (TYPE == 1) {
-#pragma unroll
-    for (int rr = 0; rr < ROWS; ++rr) {
-      Nr[rr] = dpp_shl1(M.Ar[rr]);
-      Ni[rr] = dpp_shl1(M.Ai[rr]);
-    }
-  }
-  double al = 0.0, be = 0.0, gr = 0.0, gi = 0.0;
-#pragma unroll
-  for (int rr = 0; rr < ROWS; ++rr) {
-    const double xr = TYPE == 0 ? M.Ar[rr] : M.Br[rr], xi = TYPE == 0 ? M.Ai[rr] : M.Bi[rr];
-    const double yr = TYPE == 0 ? M.Br[rr] : Nr[rr], yi = TYPE == 0 ? M.Bi[rr] : Ni[rr];
-    if (FULL) {
-      al = fma(xr, xr, fma(xi, xi, al));
-      be = fma(yr, yr, fma(yi, yi, be));
-    }
-    gr = fma(xr, yr, fma(xi, yi, gr));
-    gi = fma(xr, yi, fma(-xi, yr, gi));
-  }
+  const int cp = lane & (LC - 1);
   const int npairs = TYPE == 0 ? H : H - 1;
   bool large = false;
-  double ca, sar, sai, cb, sbr, sbi;
-  if constexpr (W == 1) {
-    // every lane forms the rotation of its pair
-    gr = groups_sum<LC>(gr);
-    gi = groups_sum<LC>(gi);
-    double a, b;
-    if (FULL) {
-      a = groups_sum<LC>(al);
-      b = groups_sum<LC>(be);
-    } else {
-      a = TYPE == 0 ? M.wA : M.wB;
-      b = TYPE == 0 ? M.wB : dpp_shl1(M.wA);
-    }
-    const double g2 = fma(gr, gr, gi * gi);
-    const bool act = cp < npairs;
-    const bool rot = act && a > zero_w && b > zero_w && g2 > (kJacobiTol * kJacobiTol) * (a * b);
-    large = rot && g2 > (kJacobiLarge * kJacobiLarge) * (a * b);
-    Rotation r{1.0, 0.0, 0.0, 0.0};
-    if (rot) r = rotation(a, b, gr, gi, g2);
-    const double nX = b + r.tg, nY = fmax(a - r.tg, 0.0);   // exchanged: norms of the slots of X and Y
-    if (TYPE == 0) {
-      ca = r.c; sar = r.sr; sai = -r.si;    // Y' = c B + conj(sigma) A
-      cb = r.c; sbr = -r.sr; sbi = -r.si;   // X' = c A - sigma B
-      if (!act) {
-        ca = cb = sai = sbi = 0.0;
-        sar = sbr = 1.0;
-      } else {
-        M.wA = nX;
-        M.wB = nY;
-      }
-    } else {
-      cb = r.c; sbr = r.sr; sbi = -r.si;    // Y' = c N + conj(sigma) B
-      ca = dpp_shr1(r.c);                   // X' = c B_{l-1} - sigma A
-      sar = -dpp_shr1(r.sr);
-      sai = -dpp_shr1(r.si);
-      const double na = dpp_shr1(nY);
-      if (!act) {
-        cb = sbi = 0.0;
-        sbr = 1.0;
-      } else {
-        M.wB = nX;
-      }
-      if (cp == 0 || cp > npairs) {
-        ca = sai = 0.0;
-        sar = 1.0;
-      } else {
-        M.wA = na;
+  double Nr[ROWS], Ni[ROWS];  // A_{l+1} (TYPE 1)
+  double al = 0.0, be = 0.0, gr = 0.0, gi = 0.0;
+  if (WA == W || wave < WA) {
+    if (TYPE == 1) {
+#pragma unroll
+      for (int rr = 0; rr < ROWS; ++rr) {
+        Nr[rr] = dpp_shl1(M.Ar[rr]);
+        Ni[rr] = dpp_shl1(M.Ai[rr]);
       }
     }
-  } else {
-    // partial sums of the wave: component u of a value pair ends in row
-    // group(s) u, which store it
-    auto put = [&](double2 &slot, double x, double y) {
-      if constexpr (Y::RG == 1) {
-        slot = make_double2(x, y);
-      } else {
-        swap32(x, y);   // lanes 0-31: the sum of x, lanes 32-63: of y
+#pragma unroll
+    for (int rr = 0; rr < ROWS; ++rr) {
+      const double xr = TYPE == 0 ? M.Ar[rr] : M.Br[rr], xi = TYPE == 0 ? M.Ai[rr] : M.Bi[rr];
+      const double yr = TYPE == 0 ? M.Br[rr] : Nr[rr], yi = TYPE == 0 ? M.Bi[rr] : Ni[rr];
+      if (FULL) {
+        al = fma(xr, xr, fma(xi, xi, al));
+        be = fma(yr, yr, fma(yi, yi, be));
+      }
+      gr = fma(xr, yr, fma(xi, yi, gr));
+      gi = fma(xr, yi, fma(-xi, yr, gi));
+    }
+    if constexpr (W > 1 && Y::kOwn) {
+      // partial sums of the wave: lane rows (halves) 0 end with the first
+      // value of a pair, the upper half with the second
+      auto put = [&](double2 &slot, double x, double y) {
+        swap32(x, y);
         x += y;
         if constexpr (Y::RG == 4) {
           double z = x;
@@ -520,14 +485,82 @@ __device__ __forceinline__ bool jacobi_round(Columns<N, W> &M, StepLds<N, W> &sh
           x += z;
         }
         if (Y::RG == 2 || (lane & 16) == 0) (lane < 32 ? slot.x : slot.y) = x;
+      };
+      if (FULL) put(sh.red[TYPE][0][wave][cp], al, be);
+      put(sh.red[TYPE][1][wave][cp], gr, gi);
+    } else if constexpr (W > 1) {
+      if (FULL) sh.red[0][0][wave][cp] = make_double2(al, be);
+      sh.red[0][1][wave][cp] = make_double2(gr, gi);
+    }
+  }
+  if constexpr (W > 1) __syncthreads();
+  double c = 0.0, sr = 1.0, si = 0.0;      // of the lane's pair
+  double cp_ = 0.0, srp = 1.0, sip = 0.0;  // of the pair of lane l - 1 (TYPE 1)
+  if constexpr (Y::kOwn) {
+    if (WA < W && wave >= WA) return false;
+    double a = 0.0, b = 0.0;
+    if constexpr (W == 1) {
+      gr = groups_sum<LC>(gr);
+      gi = groups_sum<LC>(gi);
+      if (FULL) {
+        a = groups_sum<LC>(al);
+        b = groups_sum<LC>(be);
       }
-    };
-    if (FULL) put(sh.red[0][wave][cp], al, be);
-    put(sh.red[1][wave][cp], gr, gi);
-    __syncthreads();
-    // rotation parameters: lane = 4 j + q of the first waves sums the
-    // partials of pair 16 wave + j over waves W/4 q .. W/4 (q + 1) - 1, then
-    // over the quad
+    } else {
+      // row group rg adds the partials of waves rg, rg + RG, ..., then the
+      // row groups together
+      auto get = [&](const double2 (*red)[LC], double &x, double &y) {
+        x = y = 0.0;
+#pragma unroll
+        for (int u = 0; u < WA / Y::RG; ++u) {
+          const double2 v = red[lane / LC + u * Y::RG][cp];
+          x += v.x;
+          y += v.y;
+        }
+        x = groups_sum<LC>(x);
+        y = groups_sum<LC>(y);
+      };
+      get(sh.red[TYPE][1], gr, gi);
+      if (FULL) get(sh.red[TYPE][0], a, b);
+    }
+    if (!FULL) {
+      a = TYPE == 0 ? M.wA : M.wB;
+      b = TYPE == 0 ? M.wB : dpp_shl1(M.wA);
+    }
+    const double g2 = fma(gr, gr, gi * gi);
+    const bool act = cp < npairs;
+    const bool rot = act && a > zero_w && b > zero_w && g2 > (kJacobiTol * kJacobiTol) * (a * b);
+    large = rot && g2 > (kJacobiLarge * kJacobiLarge) * (a * b);
+    double tg = 0.0;
+    if (act) {
+      c = 1.0;
+      sr = 0.0;
+    }
+    if (rot) {
+      const Rotation r = rotation(a, b, gr, gi, g2);
+      c = r.c;
+      sr = r.sr;
+      si = r.si;
+      tg = r.tg;
+    }
+    const double nX = b + tg, nY = fmax(a - tg, 0.0);   // exchanged: norms of the slots of X and Y
+    if (TYPE == 0) {
+      if (act) {
+        M.wA = nX;
+        M.wB = nY;
+      }
+    } else {
+      cp_ = dpp_shr1(c);   // 0 for the first pair's A, which has no partner (the lane before holds none)
+      srp = dpp_shr1(sr);
+      sip = dpp_shr1(si);
+      const double na = dpp_shr1(nY);
+      if (cp == 0) srp = 1.0;
+      if (act) M.wB = nX;
+      if (cp > 0 && cp <= npairs) M.wA = na;
+    }
+  } else {
+    // lane = 4 j + q of the first waves sums the partials of pair
+    // 16 wave + j over waves W/4 q .. W/4 (q + 1) - 1, then over the quad
     if (16 * wave < npairs) {
       const int j = lane >> 2, q = lane & 3, pr = 16 * wave + j;
       // positions of X and Y
@@ -536,11 +569,11 @@ __device__ __forceinline__ bool jacobi_round(Columns<N, W> &M, StepLds<N, W> &sh
 #pragma unroll
       for (int u = 0; u < W / 4; ++u) {
         if (FULL) {
-          const double2 n = sh.red[0][W / 4 * q + u][pr];
+          const double2 n = sh.red[0][0][W / 4 * q + u][pr];
           a += n.x;
           b += n.y;
         }
-        const double2 g = sh.red[1][W / 4 * q + u][pr];
+        const double2 g = sh.red[0][1][W / 4 * q + u][pr];
         x += g.x;
         y += g.y;
       }
@@ -555,36 +588,43 @@ __device__ __forceinline__ bool jacobi_round(Columns<N, W> &M, StepLds<N, W> &sh
       y = quad_sum(y);
       const double g2 = fma(x, x, y * y);
       const bool rot = pr < npairs && a > zero_w && b > zero_w && g2 > (kJacobiTol * kJacobiTol) * (a * b);
-      large = __any(rot && g2 > (kJacobiLarge * kJacobiLarge) * (a * b));
-      if (pr < npairs && q < 2) {
+      large = rot && g2 > (kJacobiLarge * kJacobiLarge) * (a * b);
+      if (pr < npairs && q == 0) {
         Rotation r{1.0, 0.0, 0.0, 0.0};
         if (rot) r = rotation(a, b, x, y, g2);
         // exchanged: the slot of X receives |Y'|^2, the slot of Y |X'|^2
-        if (q == 0) sh.w[px] = b + r.tg;
-        else sh.w[py] = fmax(a - r.tg, 0.0);
-        // q == 0 stores Y' = c Y + conj(sigma) X, q == 1 stores X' = c X - sigma Y
-        const int slot_lane = (TYPE == 1 && q == 1) ? pr + 1 : pr;
-        const int slot = (TYPE == 0) == (q == 0) ? 0 : 4;
-        double *o = sh.upd[TYPE][slot_lane] + slot;
-        o[0] = r.c;
-        o[1] = q == 0 ? r.sr : -r.sr;
-        o[2] = -r.si;
+        sh.w[px] = b + r.tg;
+        sh.w[py] = fmax(a - r.tg, 0.0);
+        sh.rot[TYPE][0][pr + 1] = r.c;
+        sh.rot[TYPE][1][pr + 1] = r.sr;
+        sh.rot[TYPE][2][pr + 1] = r.si;
       }
     }
     __syncthreads();
-    const double *up = sh.upd[TYPE][cp];
-    ca = up[0]; sar = up[1]; sai = up[2];
-    cb = up[4]; sbr = up[5]; sbi = up[6];
+    c = sh.rot[TYPE][0][cp + 1];
+    sr = sh.rot[TYPE][1][cp + 1];
+    si = sh.rot[TYPE][2][cp + 1];
+    if (TYPE == 1) {
+      cp_ = sh.rot[TYPE][0][cp];
+      srp = sh.rot[TYPE][1][cp];
+      sip = sh.rot[TYPE][2][cp];
+    }
   }
 #pragma unroll
   for (int rr = 0; rr < ROWS; ++rr) {
     const double ar = M.Ar[rr], ai = M.Ai[rr], br = M.Br[rr], bi = M.Bi[rr];
-    const double pr_ = TYPE == 0 ? br : dpp_shr1(br), pi_ = TYPE == 0 ? bi : dpp_shr1(bi);
-    const double qr = TYPE == 0 ? ar : Nr[rr], qi = TYPE == 0 ? ai : Ni[rr];
-    M.Ar[rr] = fma(ca, pr_, fma(sar, ar, -sai * ai));
-    M.Ai[rr] = fma(ca, pi_, fma(sar, ai, sai * ar));
-    M.Br[rr] = fma(cb, qr, fma(sbr, br, -sbi * bi));
-    M.Bi[rr] = fma(cb, qi, fma(sbr, bi, sbi * br));
+    if (TYPE == 0) {
+      M.Ar[rr] = fma(c, br, fma(sr, ar, si * ai));
+      M.Ai[rr] = fma(c, bi, fma(sr, ai, -si * ar));
+      M.Br[rr] = fma(c, ar, fma(-sr, br, si * bi));
+      M.Bi[rr] = fma(c, ai, fma(-sr, bi, -si * br));
+    } else {
+      const double pr_ = dpp_shr1(br), pi_ = dpp_shr1(bi);
+      M.Br[rr] = fma(c, Nr[rr], fma(sr, br, si * bi));
+      M.Bi[rr] = fma(c, Ni[rr], fma(sr, bi, -si * br));
+      M.Ar[rr] = fma(cp_, pr_, fma(-srp, ar, sip * ai));
+      M.Ai[rr] = fma(cp_, pi_, fma(-srp, ai, -sip * ar));
+    }
   }
   return large;
 }
@@ -619,10 +659,10 @@ __device__ inline int heaviest_row(const double *rn, int lane) {
 // Two-site step of circuit ci on W waves, for Jacobi matrices up to N x N.
 template <int N, int W>
 __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t ci_, const SimStep *stp,
-                                                   LdsBytes *lds) {
+                                                   int lds) {
   using Y = Layout<N, W>;
   constexpr int ROWS = Y::ROWS, LC = Y::LC;
-  StepLds<N, W> &sh = *reinterpret_cast<StepLds<N, W> *>((uint8_t *)lds);
+  StepLds<N, W> &sh = *reinterpret_cast<StepLds<N, W> *>((uint8_t *)(LdsBytes *)(uintptr_t)uniform(lds));
   const SvParams P = uniform_load(Pp);
   const SimStep st = uniform_load(stp);
   const int64_t ci = uniform(ci_);
@@ -773,7 +813,7 @@ __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t c
         }
       }
       step_sync<W>();
-      if (left > 0 || wave == pg / Y::RG) {
+      if (wave < Y::WA && (left > 0 || wave == pg / Y::RG)) {
         const double2 w0 = sh.lqw[c0], w1 = sh.lqw[c1];
         const double beta = sh.beta;
         double d[2 * ROWS];  // d = r . conj(w) for the rows (re, im)
@@ -814,25 +854,33 @@ __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t c
   // the NP rounds of a sweep.  Positions from NP on keep what they hold.
   const int NP = max(2, nref + (nref & 1));
   const int H = NP / 2;
-  if constexpr (W > 1) {
-    for (int e = tid; e < 2 * LC; e += Y::T) {
-      // identity updates (slots that no pair of the round writes)
-      double *u = sh.upd[e / LC][e % LC];
-      u[0] = u[2] = u[4] = u[6] = 0.0;
-      u[1] = u[5] = 1.0;
+  if constexpr (!Y::kOwn) {
+    // pairs that no round of the type has
+    for (int e = tid; e < 2 * (LC + 1); e += Y::T) {
+      const int type = e / (LC + 1), x = e % (LC + 1);
+      sh.rot[type][0][x] = sh.rot[type][2][x] = 0.0;
+      sh.rot[type][1][x] = 1.0;
     }
     __syncthreads();
   }
   bool converged = false;
   for (int sweep = 0; sweep < kMaxSweeps && !converged; ++sweep) {
-    bool large = jacobi_round<N, W, 0, true>(M, sh, wave, H, zero_w);  // wave-uniform (W > 1)
+    bool large = jacobi_round<N, W, 0, true>(M, sh, wave, H, zero_w);
     if (H > 1) large |= jacobi_round<N, W, 1, false>(M, sh, wave, H, zero_w);
     for (int half = 1; half < H; ++half) {
       large |= jacobi_round<N, W, 0, false>(M, sh, wave, H, zero_w);
       large |= jacobi_round<N, W, 1, false>(M, sh, wave, H, zero_w);
     }
-    if constexpr (W == 1) converged = __any(large) == 0;
-    else converged = __syncthreads_or(large ? 1 : 0) == 0;
+    if constexpr (W == 1) {
+      converged = __any(large) == 0;
+    } else {
+      // large is known to wave 0 (kOwn) or to each of the first four waves
+      if (tid == 0) sh.flag = 0;
+      __syncthreads();
+      if (large) sh.flag = 1;
+      __syncthreads();
+      converged = uniform(sh.flag) == 0;
+    }
   }
 
   // ---------------------------------------------------------- norms, order, k
@@ -846,14 +894,14 @@ __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t c
     na = groups_sum<LC>(na);
     nb = groups_sum<LC>(nb);
     if constexpr (W > 1) {
-      if (lane < LC) sh.red[0][wave][cp] = make_double2(na, nb);
+      if (wave < Y::WA && lane < LC) sh.red[0][0][wave][cp] = make_double2(na, nb);
       __syncthreads();
       if (tid < LC) {
         na = nb = 0.0;
 #pragma unroll 4
-        for (int u = 0; u < W; ++u) {
-          na += sh.red[0][u][tid].x;
-          nb += sh.red[0][u][tid].y;
+        for (int u = 0; u < Y::WA; ++u) {
+          na += sh.red[0][0][u][tid].x;
+          nb += sh.red[0][0][u][tid].y;
         }
       }
     }
@@ -1022,7 +1070,7 @@ __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t c
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
           const int j = j0 + (wave * Y::RG + lane / LC) * Y::HROWS + rr, x = c0 + q;
-          if (j < k && x < ncs) out_at(j, x, acc[rr][q]);
+          if (wave < Y::WA && j < k && x < ncs) out_at(j, x, acc[rr][q]);
         }
     }
   }
@@ -1468,7 +1516,12 @@ __global__ __launch_bounds__(64 * sim_waves(NK), 4) void sim_steps_kernel(const 
                                                                           const qk_gate *recs, double coef_z) {
   constexpr int W = sim_waves(NK);
   extern __shared__ __align__(16) uint8_t lds_bytes[];
-  LdsBytes *lds = (LdsBytes *)lds_bytes;
+  // The LDS address is handed to the steps as a number that the compiler
+  // cannot trace: as a pointer it is taken for the same everywhere, and the
+  // steps (shared by several kernels) fetch it from a table in global memory
+  // again and again, in every Jacobi round.
+  int lds = int(uint32_t(uintptr_t((LdsBytes *)lds_bytes)));
+  asm volatile("" : "+s"(lds));
   const SvParams P = uniform_load(Pp);
   const int64_t ci = uniform(circuit_of(P.base));
   if (ci >= P.n) return;
