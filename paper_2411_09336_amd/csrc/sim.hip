@@ -54,11 +54,11 @@ constexpr int kSvThreads = kSvWaves * 64; // 1024
 constexpr int kSvMaxN = 128;
 constexpr int kMaxSweeps = 30;
 // Two-site steps next to a bond above 64 (bond caps up to 128): Jacobi
-// matrices up to 256 x 256, streamed through a per-circuit slot of global
-// scratch (Jacobi columns and projection source, 1 MiB each).
+// matrices up to 256 x 256 in a per-circuit slot of global scratch (two
+// matrices of 1 MiB and 128 reflection vectors).
 constexpr int kWideN = 256;
 constexpr int kWideFrom = 64;     // a neighbouring bond above this takes the wide step
-constexpr size_t kWideSlot = size_t(2) * kWideN * kWideN;
+constexpr size_t kWideSlot = size_t(2) * kWideN * kWideN + kSvMaxN * kWideN + kSvMaxN;
 constexpr double kJacobiTol = 1e-14;
 // A sweep whose rotations all have |<X,Y>| below kJacobiLarge |X| |Y| ends
 // the iteration: cyclic Jacobi converges quadratically, so the next sweep's
@@ -656,6 +656,294 @@ __device__ inline int heaviest_row(const double *rn, int lane) {
   return 127 - int(wave_max_bits(best) & 127u);
 }
 
+// Squared norms of the rows of M (row r < N to sh.w, -1 beyond nr) and
+// ||M||_F^2, in every lane.
+template <int N, int W>
+__device__ __forceinline__ double row_weights(const Columns<N, W> &M, StepLds<N, W> &sh, int nr, int tid) {
+  using Y = Layout<N, W>;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cp = lane % Y::LC, row0 = (wave * Y::RG + lane / Y::LC) * Y::ROWS;
+  double tot = 0.0;
+#pragma unroll
+  for (int rr = 0; rr < Y::ROWS; ++rr) {
+    const int r = row0 + rr;
+    const double n2 = fma(M.Ar[rr], M.Ar[rr], fma(M.Ai[rr], M.Ai[rr], fma(M.Br[rr], M.Br[rr], M.Bi[rr] * M.Bi[rr])));
+    tot += n2;
+    const double rn = cols_sum<Y::LC>(n2);
+    if (cp == 0 && r < N) sh.w[r] = r < nr ? rn : -1.0;
+  }
+  tot = wave_sum(tot);
+  if constexpr (W > 1) {
+    if (lane == 0) sh.part[wave] = tot;
+    __syncthreads();
+    tot = 0.0;
+#pragma unroll
+    for (int u = 0; u < W; ++u) tot += sh.part[u];
+  }
+  step_sync<W>();
+  return tot;
+}
+
+// LQ preconditioning of M (nr rows, nref = min(rows, columns) reflections);
+// sh.w holds the rows' squared norms.
+//
+// M <- M H_0 H_1 ... (Householder reflections from the right, M = L Q with
+// the heaviest remaining row as the next pivot): the Jacobi columns of
+// M W are U S for any unitary W, so the factors are unchanged, while the
+// triangular factor of these graded matrices needs half the sweeps of M
+// itself and only its first min(nr, nc) columns carry more than rounding.
+// Step i reflects its pivot row onto column i: with x = that row restricted
+// to columns >= i and w = x + e^{i arg x_i} |x| e_i, every row r becomes
+// r - beta (r . conj w) w, beta = 1 / (|x| (|x| + |x_i|)).  Rows stay in
+// place (a row permutation changes no column inner product); their
+// remaining norms are reduced by each new entry.  128 x 128 thetas of a
+// d = 8 circuit: 7.7 sweeps against 8.7 with the rows in order of initial
+// norm (30 x 64 ones of a d = 3 circuit: 6.6 against 7.3).
+template <int N, int W>
+__device__ __forceinline__ void lq_reduce(Columns<N, W> &M, StepLds<N, W> &sh, int nr, int nref, int tid) {
+  using Y = Layout<N, W>;
+  constexpr int ROWS = Y::ROWS, LC = Y::LC;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cp = lane % LC, row0 = (wave * Y::RG + lane / LC) * ROWS;
+  const int c0 = 2 * cp, c1 = 2 * cp + 1;
+  int left = Y::RG * ROWS;   // rows of this wave that are no pivot yet
+  for (int i = 0; i < nref; ++i) {
+    const int pv = __builtin_amdgcn_readfirstlane(heaviest_row<N>(sh.w, lane));
+    const int pg = pv / ROWS, ri = pv % ROWS;   // row group and row of the pivot
+    if (wave == pg / Y::RG) {
+      --left;
+      double xr0 = 0.0, xi0 = 0.0, xr1 = 0.0, xi1 = 0.0;
+#pragma unroll
+      for (int rr = 0; rr < ROWS; ++rr)
+        if (rr == ri) {
+          xr0 = M.Ar[rr];
+          xi0 = M.Ai[rr];
+          xr1 = M.Br[rr];
+          xi1 = M.Bi[rr];
+        }
+      if (c0 < i) xr0 = xi0 = 0.0;
+      if (c1 < i) xr1 = xi1 = 0.0;
+      const double n2 = cols_sum<LC>(fma(xr0, xr0, fma(xi0, xi0, fma(xr1, xr1, xi1 * xi1))));
+      if (lane / LC == pg % Y::RG) {
+        const double dr = (i & 1) ? xr1 : xr0, di = (i & 1) ? xi1 : xi0;
+        const double a2 = fma(dr, dr, di * di);
+        const double rn = n2 > 0.0 ? rsqrt(n2) : 0.0, ra = a2 > 0.0 ? rsqrt(a2) : 0.0;
+        const double nx = n2 * rn, ax = a2 * ra;
+        const double pr = a2 > 0.0 ? dr * ra : 1.0, pi = di * ra;
+        const double2 d = make_double2(pr * (ax + nx), pi * (ax + nx));
+        sh.lqw[c0] = c0 == i ? d : make_double2(xr0, xi0);
+        sh.lqw[c1] = c1 == i ? d : make_double2(xr1, xi1);
+        if (cp == (i >> 1)) sh.beta = n2 > 0.0 ? rn / (nx + ax) : 0.0;
+      }
+    }
+    step_sync<W>();
+    if (wave < Y::WA && (left > 0 || wave == pg / Y::RG)) {
+      const double2 w0 = sh.lqw[c0], w1 = sh.lqw[c1];
+      const double beta = sh.beta;
+      double d[2 * ROWS];  // d = r . conj(w) for the rows (re, im)
+#pragma unroll
+      for (int rr = 0; rr < ROWS; ++rr) {
+        d[2 * rr] = fma(M.Ar[rr], w0.x, fma(M.Ai[rr], w0.y, fma(M.Br[rr], w1.x, M.Bi[rr] * w1.y)));
+        d[2 * rr + 1] = fma(M.Ai[rr], w0.x, fma(-M.Ar[rr], w0.y, fma(M.Bi[rr], w1.x, -M.Br[rr] * w1.y)));
+      }
+      if constexpr (LC == 64 && ROWS == 8) {
+        wave_sum16(d);
+      } else {
+#pragma unroll
+        for (int u = 0; u < 2 * ROWS; ++u) d[u] = cols_sum<LC>(d[u]);
+      }
+#pragma unroll
+      for (int rr = 0; rr < ROWS; ++rr) {
+        const double dr = beta * d[2 * rr], di = beta * d[2 * rr + 1];
+        M.Ar[rr] -= dr * w0.x - di * w0.y;
+        M.Ai[rr] -= dr * w0.y + di * w0.x;
+        M.Br[rr] -= dr * w1.x - di * w1.y;
+        M.Bi[rr] -= dr * w1.y + di * w1.x;
+        if (cp == (i >> 1) && row0 + rr < nr) {
+          const double er = (i & 1) ? M.Br[rr] : M.Ar[rr], ei = (i & 1) ? M.Bi[rr] : M.Ai[rr];
+          const double v = sh.w[row0 + rr];
+          sh.w[row0 + rr] = row0 + rr == pv || v < 0.0 ? -1.0 : fmax(v - fma(er, er, ei * ei), 0.0);
+        }
+      }
+    }
+    step_sync<W>();
+  }
+}
+
+// One-sided Jacobi sweeps over the first 2 H columns of M; returns whether
+// they converged.
+//
+// Odd-even transposition ordering of the positions 0..2H-1 (A_l = 2l,
+// B_l = 2l+1): type-0 rounds pair (A_l, B_l) inside each lane, type-1 rounds
+// pair (B_l, A_{l+1}) across neighbouring lanes, and each pair is exchanged
+// after its rotation, so every two columns meet exactly once in the 2H rounds
+// of a sweep.  Positions beyond keep what they hold.
+template <int N, int W>
+__device__ __forceinline__ bool jacobi_sweeps(Columns<N, W> &M, StepLds<N, W> &sh, int H, double zero_w, int tid) {
+  using Y = Layout<N, W>;
+  constexpr int LC = Y::LC;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if constexpr (!Y::kOwn) {
+    // pairs that no round of the type has
+    for (int e = tid; e < 2 * (LC + 1); e += Y::T) {
+      const int type = e / (LC + 1), x = e % (LC + 1);
+      sh.rot[type][0][x] = sh.rot[type][2][x] = 0.0;
+      sh.rot[type][1][x] = 1.0;
+    }
+    __syncthreads();
+  }
+  bool converged = false;
+  for (int sweep = 0; sweep < kMaxSweeps && !converged; ++sweep) {
+    bool large = jacobi_round<N, W, 0, true>(M, sh, wave, H, zero_w);
+    if (H > 1) large |= jacobi_round<N, W, 1, false>(M, sh, wave, H, zero_w);
+    for (int half = 1; half < H; ++half) {
+      large |= jacobi_round<N, W, 0, false>(M, sh, wave, H, zero_w);
+      large |= jacobi_round<N, W, 1, false>(M, sh, wave, H, zero_w);
+    }
+    if constexpr (W == 1) {
+      converged = __any(large) == 0;
+    } else {
+      // large is known to wave 0 (kOwn) or to each of the first four waves
+      if (tid == 0) sh.flag = 0;
+      __syncthreads();
+      if (large) sh.flag = 1;
+      __syncthreads();
+      converged = uniform(sh.flag) == 0;
+    }
+  }
+  return converged;
+}
+
+// Norms, order and number of the columns kept (Eq. (8)) after the sweeps:
+// sh.norm by position, sh.rank, sh.k and the factor sh.nrm that restores unit
+// weight; the truncation statistics of the circuit.
+template <int N, int W>
+__device__ __forceinline__ void select_columns(const Columns<N, W> &M, StepLds<N, W> &sh, const SvParams &P,
+                                               const SimStep &st, int64_t ci, bool gate, double cg, double sg, int Dm,
+                                               int nref, int NP, double zero_w, bool converged, int tid) {
+  using Y = Layout<N, W>;
+  constexpr int ROWS = Y::ROWS, LC = Y::LC;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cp = lane % LC, c0 = 2 * cp, c1 = 2 * cp + 1;
+  double na = 0.0, nb = 0.0;
+#pragma unroll
+  for (int rr = 0; rr < ROWS; ++rr) {
+    na = fma(M.Ar[rr], M.Ar[rr], fma(M.Ai[rr], M.Ai[rr], na));
+    nb = fma(M.Br[rr], M.Br[rr], fma(M.Bi[rr], M.Bi[rr], nb));
+  }
+  na = groups_sum<LC>(na);
+  nb = groups_sum<LC>(nb);
+  if constexpr (W > 1) {
+    if (wave < Y::WA && lane < LC) sh.red[0][0][wave][cp] = make_double2(na, nb);
+    __syncthreads();
+    if (tid < LC) {
+      na = nb = 0.0;
+#pragma unroll 4
+      for (int u = 0; u < Y::WA; ++u) {
+        na += sh.red[0][0][u][tid].x;
+        nb += sh.red[0][0][u][tid].y;
+      }
+    }
+  }
+  if (tid < LC) {
+    sh.norm[c0] = c0 < NP ? na : 0.0;
+    sh.norm[c1] = c1 < NP ? nb : 0.0;
+  }
+  step_sync<W>();
+  if (tid < 4 * N) {
+    // four threads per position count the columns that precede it
+    const int pos = tid >> 2;
+    const double v = sh.norm[pos];
+    int rank = 0;
+#pragma unroll 8
+    for (int u = 0; u < N / 4; ++u) {
+      const int x = 4 * u + (tid & 3);
+      const double o = sh.norm[x];
+      rank += (o > v || (o == v && x < pos)) ? 1 : 0;
+    }
+    rank += __builtin_amdgcn_mov_dpp(rank, 0xB1, 0xf, 0xf, true);
+    rank += __builtin_amdgcn_mov_dpp(rank, 0x4E, 0xf, 0xf, true);
+    if ((tid & 3) == 0) {
+      sh.rank[pos] = rank;
+      sh.sorted[rank] = v;
+    }
+  }
+  step_sync<W>();
+  if (wave == 0) {
+    // lane l holds the sorted weights PER l .. PER l + PER - 1 and, in suf,
+    // the weight from each on
+    constexpr int PER = N > 64 ? N / 64 : 1;
+    double v[PER], suf[PER], s = 0.0;
+#pragma unroll
+    for (int u = PER - 1; u >= 0; --u) {
+      v[u] = PER * lane + u < N ? sh.sorted[PER * lane + u] : 0.0;
+      s += v[u];
+      suf[u] = s;
+    }
+#pragma unroll
+    for (int o = 1; o < 64 && o * PER < N; o <<= 1) {
+      const double t = __shfl_down(s, o, 64);
+      s += lane + o < 64 ? t : 0.0;
+    }
+    const double rest = __shfl_down(s, 1, 64);
+    const double total = lane0(s);
+    int nnz = 0, above = 0;
+    const int nsv = nref;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      suf[u] += lane < 63 ? rest : 0.0;
+      const bool in = PER * lane + u < nsv;
+      nnz += __popcll(__ballot(PER * lane + u < N && v[u] > zero_w));
+      above += __popcll(__ballot(in && suf[u] > P.cutoff * total));
+    }
+    int k;
+    double nrm = 1.0;
+    if (gate) {
+      // smallest k with sum_{r >= k} w_r <= cutoff * total
+      const int kcut = P.cutoff > 0.0 ? above : nsv;
+      k = max(1, min(min(P.chi, kcut), max(nnz, 1)));
+      if (P.gate_split) {
+        // theta = sum_r (L_r A_p)(R_r A_{p+1}) over the rank(G) terms of
+        // the gate's operator-Schmidt decomposition: rank <= rank(G) Dm.
+        // Rxx(phi) = cos(phi/2) II - i sin(phi/2) XX: a term counts when its
+        // coefficient exceeds 1e-12 of the larger one (cos(pi/2) rounds to
+        // ~6e-17, not zero); SWAP has four terms
+        const double cmax = fmax(fabs(cg), fabs(sg));
+        const int rg = st.op == OP_RXX
+                           ? (fabs(cg) > 1e-12 * cmax ? 1 : 0) + (fabs(sg) > 1e-12 * cmax ? 1 : 0)
+                           : 4;
+        k = max(1, min(k, rg * Dm));
+      }
+      k = min(k, st.nr);
+      double kept = 0.0, tail = 0.0;
+#pragma unroll
+      for (int u = 0; u < PER; ++u) {
+        kept += PER * lane + u < k ? v[u] : 0.0;
+        tail += PER * lane + u < k ? 0.0 : v[u];
+      }
+      kept = lane0(wave_sum(kept));
+      tail = lane0(wave_sum(tail));
+      nrm = kept > 0.0 ? 1.0 / sqrt(kept) : 1.0;
+      if (lane == 0) {
+        const double disc = total > 0.0 ? tail / total : 0.0;
+        P.disc[ci] += disc;
+        P.maxdisc[ci] = fmax(P.maxdisc[ci], disc);
+        if (k < nsv && sh.sorted[0] > 0.0 &&
+            (sqrt(sh.sorted[k - 1]) - sqrt(sh.sorted[k])) / sqrt(sh.sorted[0]) < kDegenerateGap)
+          P.degen[ci] += 1;
+      }
+    } else {
+      k = min(max(1, min(nsv, max(nnz, 1))), st.nr);
+    }
+    if (lane == 0) {
+      if (!converged) P.unconv[ci] += 1;
+      sh.k = k;
+      sh.nrm = nrm;
+    }
+  }
+  step_sync<W>();
+}
+
 // Two-site step of circuit ci on W waves, for Jacobi matrices up to N x N.
 template <int N, int W>
 __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t ci_, const SimStep *stp,
@@ -731,7 +1019,6 @@ __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t c
     return right ? v : cconj(v);
   };
   Columns<N, W> M;
-  double tot = 0.0;
 #pragma unroll
   for (int rr = 0; rr < ROWS; ++rr) {
     const int r = row0 + rr;
@@ -749,260 +1036,13 @@ __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t c
     M.Ai[rr] = v[0].y;
     M.Br[rr] = v[1].x;
     M.Bi[rr] = v[1].y;
-    const double n2 = fma(v[0].x, v[0].x, fma(v[0].y, v[0].y, fma(v[1].x, v[1].x, v[1].y * v[1].y)));
-    tot += n2;
-    const double rn = cols_sum<LC>(n2);
-    if (cp == 0 && r < N) sh.w[r] = r < nr ? rn : -1.0;
   }
-  // ||M||_F^2 (invariant under the rotations)
-  tot = wave_sum(tot);
-  if constexpr (W > 1) {
-    if (lane == 0) sh.part[wave] = tot;
-    __syncthreads();
-    tot = 0.0;
-#pragma unroll
-    for (int u = 0; u < W; ++u) tot += sh.part[u];
-  }
-  // wave-uniform: kept in scalar registers
-  const double zero_w = lane0(kZeroWeight * tot);
-  step_sync<W>();
-
-  // ---------------------------------------------------------- LQ preconditioning
-  // M <- M H_0 H_1 ... (Householder reflections from the right, M = L Q with
-  // the heaviest remaining row as the next pivot): the Jacobi columns of
-  // M W are U S for any unitary W, so the factors are unchanged, while the
-  // triangular factor of these graded matrices needs half the sweeps of M
-  // itself and only its first min(nr, nc) columns carry more than rounding.
-  // Step i reflects its pivot row onto column i: with x = that row restricted
-  // to columns >= i and w = x + e^{i arg x_i} |x| e_i, every row r becomes
-  // r - beta (r . conj w) w, beta = 1 / (|x| (|x| + |x_i|)).  Rows stay in
-  // place (a row permutation changes no column inner product); their
-  // remaining norms are reduced by each new entry.  128 x 128 thetas of a
-  // d = 8 circuit: 7.7 sweeps against 8.7 with the rows in order of initial
-  // norm (30 x 64 ones of a d = 3 circuit: 6.6 against 7.3).
+  const double zero_w = lane0(kZeroWeight * row_weights<N, W>(M, sh, nr, tid));   // wave-uniform
   const int nref = min(nr, nc);
-  {
-    int left = Y::RG * ROWS;   // rows of this wave that are no pivot yet
-    for (int i = 0; i < nref; ++i) {
-      const int pv = __builtin_amdgcn_readfirstlane(heaviest_row<N>(sh.w, lane));
-      const int pg = pv / ROWS, ri = pv % ROWS;   // row group and row of the pivot
-      if (wave == pg / Y::RG) {
-        --left;
-        double xr0 = 0.0, xi0 = 0.0, xr1 = 0.0, xi1 = 0.0;
-#pragma unroll
-        for (int rr = 0; rr < ROWS; ++rr)
-          if (rr == ri) {
-            xr0 = M.Ar[rr];
-            xi0 = M.Ai[rr];
-            xr1 = M.Br[rr];
-            xi1 = M.Bi[rr];
-          }
-        if (c0 < i) xr0 = xi0 = 0.0;
-        if (c1 < i) xr1 = xi1 = 0.0;
-        const double n2 = cols_sum<LC>(fma(xr0, xr0, fma(xi0, xi0, fma(xr1, xr1, xi1 * xi1))));
-        if (lane / LC == pg % Y::RG) {
-          const double dr = (i & 1) ? xr1 : xr0, di = (i & 1) ? xi1 : xi0;
-          const double a2 = fma(dr, dr, di * di);
-          const double rn = n2 > 0.0 ? rsqrt(n2) : 0.0, ra = a2 > 0.0 ? rsqrt(a2) : 0.0;
-          const double nx = n2 * rn, ax = a2 * ra;
-          const double pr = a2 > 0.0 ? dr * ra : 1.0, pi = di * ra;
-          const double2 d = make_double2(pr * (ax + nx), pi * (ax + nx));
-          sh.lqw[c0] = c0 == i ? d : make_double2(xr0, xi0);
-          sh.lqw[c1] = c1 == i ? d : make_double2(xr1, xi1);
-          if (cp == (i >> 1)) sh.beta = n2 > 0.0 ? rn / (nx + ax) : 0.0;
-        }
-      }
-      step_sync<W>();
-      if (wave < Y::WA && (left > 0 || wave == pg / Y::RG)) {
-        const double2 w0 = sh.lqw[c0], w1 = sh.lqw[c1];
-        const double beta = sh.beta;
-        double d[2 * ROWS];  // d = r . conj(w) for the rows (re, im)
-#pragma unroll
-        for (int rr = 0; rr < ROWS; ++rr) {
-          d[2 * rr] = fma(M.Ar[rr], w0.x, fma(M.Ai[rr], w0.y, fma(M.Br[rr], w1.x, M.Bi[rr] * w1.y)));
-          d[2 * rr + 1] = fma(M.Ai[rr], w0.x, fma(-M.Ar[rr], w0.y, fma(M.Bi[rr], w1.x, -M.Br[rr] * w1.y)));
-        }
-        if constexpr (LC == 64 && ROWS == 8) {
-          wave_sum16(d);
-        } else {
-#pragma unroll
-          for (int u = 0; u < 2 * ROWS; ++u) d[u] = cols_sum<LC>(d[u]);
-        }
-#pragma unroll
-        for (int rr = 0; rr < ROWS; ++rr) {
-          const double dr = beta * d[2 * rr], di = beta * d[2 * rr + 1];
-          M.Ar[rr] -= dr * w0.x - di * w0.y;
-          M.Ai[rr] -= dr * w0.y + di * w0.x;
-          M.Br[rr] -= dr * w1.x - di * w1.y;
-          M.Bi[rr] -= dr * w1.y + di * w1.x;
-          if (cp == (i >> 1) && row0 + rr < nr) {
-            const double er = (i & 1) ? M.Br[rr] : M.Ar[rr], ei = (i & 1) ? M.Bi[rr] : M.Ai[rr];
-            const double v = sh.w[row0 + rr];
-            sh.w[row0 + rr] = row0 + rr == pv || v < 0.0 ? -1.0 : fmax(v - fma(er, er, ei * ei), 0.0);
-          }
-        }
-      }
-      step_sync<W>();
-    }
-  }
-
-  // ---------------------------------------------------------- Jacobi sweeps
-  // Odd-even transposition ordering of the positions 0..NP-1 (A_l = 2l,
-  // B_l = 2l+1): type-0 rounds pair (A_l, B_l) inside each lane, type-1
-  // rounds pair (B_l, A_{l+1}) across neighbouring lanes, and each pair is
-  // exchanged after its rotation, so every two columns meet exactly once in
-  // the NP rounds of a sweep.  Positions from NP on keep what they hold.
+  lq_reduce<N, W>(M, sh, nr, nref, tid);
   const int NP = max(2, nref + (nref & 1));
-  const int H = NP / 2;
-  if constexpr (!Y::kOwn) {
-    // pairs that no round of the type has
-    for (int e = tid; e < 2 * (LC + 1); e += Y::T) {
-      const int type = e / (LC + 1), x = e % (LC + 1);
-      sh.rot[type][0][x] = sh.rot[type][2][x] = 0.0;
-      sh.rot[type][1][x] = 1.0;
-    }
-    __syncthreads();
-  }
-  bool converged = false;
-  for (int sweep = 0; sweep < kMaxSweeps && !converged; ++sweep) {
-    bool large = jacobi_round<N, W, 0, true>(M, sh, wave, H, zero_w);
-    if (H > 1) large |= jacobi_round<N, W, 1, false>(M, sh, wave, H, zero_w);
-    for (int half = 1; half < H; ++half) {
-      large |= jacobi_round<N, W, 0, false>(M, sh, wave, H, zero_w);
-      large |= jacobi_round<N, W, 1, false>(M, sh, wave, H, zero_w);
-    }
-    if constexpr (W == 1) {
-      converged = __any(large) == 0;
-    } else {
-      // large is known to wave 0 (kOwn) or to each of the first four waves
-      if (tid == 0) sh.flag = 0;
-      __syncthreads();
-      if (large) sh.flag = 1;
-      __syncthreads();
-      converged = uniform(sh.flag) == 0;
-    }
-  }
-
-  // ---------------------------------------------------------- norms, order, k
-  {
-    double na = 0.0, nb = 0.0;
-#pragma unroll
-    for (int rr = 0; rr < ROWS; ++rr) {
-      na = fma(M.Ar[rr], M.Ar[rr], fma(M.Ai[rr], M.Ai[rr], na));
-      nb = fma(M.Br[rr], M.Br[rr], fma(M.Bi[rr], M.Bi[rr], nb));
-    }
-    na = groups_sum<LC>(na);
-    nb = groups_sum<LC>(nb);
-    if constexpr (W > 1) {
-      if (wave < Y::WA && lane < LC) sh.red[0][0][wave][cp] = make_double2(na, nb);
-      __syncthreads();
-      if (tid < LC) {
-        na = nb = 0.0;
-#pragma unroll 4
-        for (int u = 0; u < Y::WA; ++u) {
-          na += sh.red[0][0][u][tid].x;
-          nb += sh.red[0][0][u][tid].y;
-        }
-      }
-    }
-    if (tid < LC) {
-      sh.norm[c0] = c0 < NP ? na : 0.0;
-      sh.norm[c1] = c1 < NP ? nb : 0.0;
-    }
-    step_sync<W>();
-    if (tid < 4 * N) {
-      // four threads per position count the columns that precede it
-      const int pos = tid >> 2;
-      const double v = sh.norm[pos];
-      int rank = 0;
-#pragma unroll 8
-      for (int u = 0; u < N / 4; ++u) {
-        const int x = 4 * u + (tid & 3);
-        const double o = sh.norm[x];
-        rank += (o > v || (o == v && x < pos)) ? 1 : 0;
-      }
-      rank += __builtin_amdgcn_mov_dpp(rank, 0xB1, 0xf, 0xf, true);
-      rank += __builtin_amdgcn_mov_dpp(rank, 0x4E, 0xf, 0xf, true);
-      if ((tid & 3) == 0) {
-        sh.rank[pos] = rank;
-        sh.sorted[rank] = v;
-      }
-    }
-    step_sync<W>();
-    if (wave == 0) {
-      // lane l holds the sorted weights PER l .. PER l + PER - 1 and, in suf,
-      // the weight from each on
-      constexpr int PER = N > 64 ? N / 64 : 1;
-      double v[PER], suf[PER], s = 0.0;
-#pragma unroll
-      for (int u = PER - 1; u >= 0; --u) {
-        v[u] = PER * lane + u < N ? sh.sorted[PER * lane + u] : 0.0;
-        s += v[u];
-        suf[u] = s;
-      }
-#pragma unroll
-      for (int o = 1; o < 64 && o * PER < N; o <<= 1) {
-        const double t = __shfl_down(s, o, 64);
-        s += lane + o < 64 ? t : 0.0;
-      }
-      const double rest = __shfl_down(s, 1, 64);
-      const double total = lane0(s);
-      int nnz = 0, above = 0;
-      const int nsv = nref;
-#pragma unroll
-      for (int u = 0; u < PER; ++u) {
-        suf[u] += lane < 63 ? rest : 0.0;
-        const bool in = PER * lane + u < nsv;
-        nnz += __popcll(__ballot(PER * lane + u < N && v[u] > zero_w));
-        above += __popcll(__ballot(in && suf[u] > P.cutoff * total));
-      }
-      int k;
-      double nrm = 1.0;
-      if (gate) {
-        // smallest k with sum_{r >= k} w_r <= cutoff * total
-        const int kcut = P.cutoff > 0.0 ? above : nsv;
-        k = max(1, min(min(P.chi, kcut), max(nnz, 1)));
-        if (P.gate_split) {
-          // theta = sum_r (L_r A_p)(R_r A_{p+1}) over the rank(G) terms of
-          // the gate's operator-Schmidt decomposition: rank <= rank(G) Dm.
-          // Rxx(phi) = cos(phi/2) II - i sin(phi/2) XX: a term counts when its
-          // coefficient exceeds 1e-12 of the larger one (cos(pi/2) rounds to
-          // ~6e-17, not zero); SWAP has four terms
-          const double cmax = fmax(fabs(cg), fabs(sg));
-          const int rg = st.op == OP_RXX
-                             ? (fabs(cg) > 1e-12 * cmax ? 1 : 0) + (fabs(sg) > 1e-12 * cmax ? 1 : 0)
-                             : 4;
-          k = max(1, min(k, rg * Dm));
-        }
-        k = min(k, st.nr);
-        double kept = 0.0, tail = 0.0;
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-          kept += PER * lane + u < k ? v[u] : 0.0;
-          tail += PER * lane + u < k ? 0.0 : v[u];
-        }
-        kept = lane0(wave_sum(kept));
-        tail = lane0(wave_sum(tail));
-        nrm = kept > 0.0 ? 1.0 / sqrt(kept) : 1.0;
-        if (lane == 0) {
-          const double disc = total > 0.0 ? tail / total : 0.0;
-          P.disc[ci] += disc;
-          P.maxdisc[ci] = fmax(P.maxdisc[ci], disc);
-          if (k < nsv && sh.sorted[0] > 0.0 &&
-              (sqrt(sh.sorted[k - 1]) - sqrt(sh.sorted[k])) / sqrt(sh.sorted[0]) < kDegenerateGap)
-            P.degen[ci] += 1;
-        }
-      } else {
-        k = min(max(1, min(nsv, max(nnz, 1))), st.nr);
-      }
-      if (lane == 0) {
-        if (!converged) P.unconv[ci] += 1;
-        sh.k = k;
-        sh.nrm = nrm;
-      }
-    }
-    step_sync<W>();
-  }
+  const bool converged = jacobi_sweeps<N, W>(M, sh, NP / 2, zero_w, tid);
+  select_columns<N, W>(M, sh, P, st, ci, gate, cg, sg, Dm, nref, NP, zero_w, converged, tid);
   const int k = sh.k;
   const double nrm = sh.nrm;
 
@@ -1086,8 +1126,8 @@ __device__ inline double half_sum(double x, int hf) {
   return __shfl(x, hf << 5, 64);
 }
 
-// Two-site step of circuit ci whose Jacobi matrix may exceed 128 x 128 (a
-// neighbouring bond above 64; one 1024-thread workgroup).  The same
+// Two-site step of circuit ci whose Jacobi matrix has more than 128 rows and
+// columns (both neighbouring bonds above 64; one 1024-thread workgroup).  The same
 // operation as svd_step -- pair product, theta, one-sided Jacobi on the
 // columns, truncation by Eq. (8) with the bond cap, isometric factor from the
 // normalised columns and the other factor as an exact projection -- with the
@@ -1103,7 +1143,7 @@ __device__ inline double half_sum(double x, int hf) {
 // (NP - 1 rounds of NP/2 disjoint pairs: every pair once per sweep).  Wave w
 // rotates pairs w, w + 16, ... of a round, two at a time (one per lane half,
 // each lane holding 8 rows of both columns), with one barrier per round.
-__device__ __attribute__((noinline)) void svd_step_wide(const SvParams *Pq, int64_t ci_, const SimStep *stp) {
+__device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, int64_t ci_, const SimStep *stp) {
   const SvParams P = uniform_load(Pq);
   const SimStep st = uniform_load(stp);
   const int64_t ci = uniform(ci_);
@@ -1460,6 +1500,320 @@ __device__ __attribute__((noinline)) void svd_step_wide(const SvParams *Pq, int6
   if (tid == 0) dims[p + 1] = k;
 }
 
+// Two-site step of circuit ci next to a bond above 64 whose Jacobi matrix M
+// (nr x nc, up to 256 either way) has at most 128 rows or at most 128
+// columns (one 1024-thread workgroup).  The shorter side fits the registers
+// of svd_step once the longer one is reduced, in the circuit's global scratch
+// slot (L2-resident): with B = M (wide) or M^H (tall) of at most 128 rows,
+//   B H_0 H_1 ... = L  (Householder reflections from the right as in
+// lq_reduce), of which only the first columns are not zero.  A wide M has the
+// singular vectors of L.  A tall M is H_0 H_1 ... L^H: the columns of L^H go
+// through lq_reduce and the sweeps, and the reflections, in reverse, turn
+// their orthogonal columns into those of M.
+// Scratch slot: B column-major (column c at W + c kWideN), the pair product
+// (row-major, kWideN), and the reflection vectors of a tall M with their
+// factors.
+// With the sweeps streaming the columns from L2 instead (every round of 256 x
+// 128 columns ~7 us): 4 points x 16 qubits, d = 5, chi 128, 594 ms against 270.
+struct WideLds {
+  double2 vec[kWideN];          // pivot row of a reflection
+  double2 dot[8][kSvMaxN];      // partial products row . conj(w)
+  double rn[kSvMaxN];           // remaining row norms
+  double part[kSvWaves];
+};
+
+__device__ __attribute__((noinline)) void svd_step_wide(const SvParams *Pq, int64_t ci_, const SimStep *stp, int lds) {
+  constexpr int N = kSvMaxN, W = kSvWaves;
+  using Y = Layout<N, W>;
+  constexpr int ROWS = Y::ROWS;
+  StepLds<N, W> &sh = *reinterpret_cast<StepLds<N, W> *>((uint8_t *)(LdsBytes *)(uintptr_t)uniform(lds));
+  static_assert(sizeof(WideLds) <= sizeof(sh.stage), "the reflection buffers lie over the staging buffers");
+  WideLds &wl = *reinterpret_cast<WideLds *>(&sh.stage);
+  const SvParams P = uniform_load(Pq);
+  const SimStep st = uniform_load(stp);
+  const int64_t ci = uniform(ci_);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  int32_t *dims = P.dims + ci * (P.m + 1);
+  const int p = st.p;
+  const int Dp = uniform(dims[p]), Dm = uniform(dims[p + 1]), Dn = uniform(dims[p + 2]);
+  const int Pw = uniform(P.pad[p]), Pm = uniform(P.pad[p + 1]), Pn = uniform(P.pad[p + 2]);
+  double2 *Ap = P.f64 + ci * P.mps_stride + uniform(P.site_off[p]);
+  double2 *Aq = P.f64 + ci * P.mps_stride + uniform(P.site_off[p + 1]);
+  double2 *B = P.wscratch + int64_t(blockIdx.x) * kWideSlot;
+  double2 *P2 = B + kWideN * kWideN;
+  double2 *V = P2 + kWideN * kWideN;                                   // reflection i at V + i kWideN
+  double *betas = reinterpret_cast<double *>(V + kSvMaxN * kWideN);
+
+  double cg = 1.0, sg = 0.0;
+  if (st.op == OP_RXX) {
+    const double xi = P.X[ci * P.ldx + st.fi], xj = P.X[ci * P.ldx + st.fj];
+    const double phi = P.coef_xx * (1.0 - xi) * (1.0 - xj);
+    sincos(0.5 * phi, &sg, &cg);
+  }
+  const bool right = (st.mode == GATE_RIGHT || st.mode == MOVE_RIGHT);
+  const bool gate = (st.mode == GATE_RIGHT || st.mode == GATE_LEFT);
+  int nr, nc, ncs;
+  if (st.mode == GATE_RIGHT) { nr = 2 * Dp; nc = 2 * Dn; ncs = nc; }
+  else if (st.mode == GATE_LEFT) { nr = 2 * Dn; nc = 2 * Dp; ncs = nc; }
+  else if (st.mode == MOVE_RIGHT) { nr = 2 * Dp; nc = Dm; ncs = 2 * Dn; }
+  else { nr = 2 * Dn; nc = Dm; ncs = 2 * Dp; }
+  auto ap_at = [&](int y, int c) -> double2 & {
+    const int s = phys_of(y, Dp);
+    return Ap[(s * Pw + y - s * Dp) * Pm + c];
+  };
+  auto aq_at = [&](int c, int x) -> double2 & {
+    const int t = phys_of(x, Dn);
+    return Aq[(t * Pm + c) * Pn + x - t * Dn];
+  };
+
+  // ---------------------------------------------------------- pair product
+  for (int y0 = 0; y0 < 2 * Dp; y0 += N)
+    for (int x0 = 0; x0 < 2 * Dn; x0 += N) {
+      double2 pt[ROWS][2];
+      staged_tile_gemm<N, W, ROWS>(
+          Dm, [&](int y, int c) { return y0 + y < 2 * Dp ? ap_at(y0 + y, c) : make_double2(0.0, 0.0); },
+          [&](int c, int x) { return x0 + x < 2 * Dn ? aq_at(c, x0 + x) : make_double2(0.0, 0.0); }, sh, pt);
+#pragma unroll
+      for (int rr = 0; rr < ROWS; ++rr)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int y = y0 + wave * ROWS + rr, x = x0 + 2 * lane + q;
+          if (y < 2 * Dp && x < 2 * Dn) P2[y * kWideN + x] = pt[rr][q];
+        }
+    }
+  __syncthreads();
+  auto source = [&](int y, int x) {
+    const int r = right ? y : x, c = right ? x : y;
+    const int s = phys_of(r, Dp), t = phys_of(c, Dn);
+    const double2 v =
+        theta_from_pair(P2, gate ? st.op : int(OP_ID), cg, sg, Dp, Dn, s, r - s * Dp, t, c - t * Dn, kWideN);
+    return right ? v : cconj(v);
+  };
+  auto matrix = [&](int r, int c) {   // M
+    return gate ? source(r, c) : right ? ap_at(r, c) : cconj(aq_at(c, r));
+  };
+
+  // ---------------------------------------------------------- the longer side
+  const bool tall = nr > N;
+  const int rb = tall ? nc : nr, cb = tall ? nr : nc;   // B: rb <= 128 rows
+  if (cb > N) {
+    const int r = tid & (N - 1), q = tid >> 7;   // row and columns q, q + 8, ... of this thread
+    double w2 = 0.0;
+    for (int c = q; c < cb; c += 8) {
+      double2 v = make_double2(0.0, 0.0);
+      if (r < rb) v = tall ? cconj(matrix(c, r)) : matrix(r, c);
+      B[c * kWideN + r] = v;
+      w2 = fma(v.x, v.x, fma(v.y, v.y, w2));
+    }
+    wl.dot[q][r] = make_double2(w2, 0.0);
+    __syncthreads();
+    if (tid < N) {
+      double t = 0.0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) t += wl.dot[u][tid].x;
+      wl.rn[tid] = tid < rb ? t : -1.0;
+    }
+    __syncthreads();
+    for (int i = 0; i < rb; ++i) {
+      const int pv = __builtin_amdgcn_readfirstlane(heaviest_row<N>(wl.rn, lane));
+      if (tid < kWideN) {
+        const double2 x = (tid >= i && tid < cb) ? B[tid * kWideN + pv] : make_double2(0.0, 0.0);
+        wl.vec[tid] = x;
+        const double n2 = wave_sum(fma(x.x, x.x, x.y * x.y));
+        if (lane == 0) wl.part[wave] = n2;
+      }
+      __syncthreads();
+      const double n2 = (wl.part[0] + wl.part[1]) + (wl.part[2] + wl.part[3]);
+      const double2 xi = wl.vec[i];
+      const double a2 = fma(xi.x, xi.x, xi.y * xi.y);
+      const double rx = n2 > 0.0 ? rsqrt(n2) : 0.0, ra = a2 > 0.0 ? rsqrt(a2) : 0.0;
+      const double nx = n2 * rx, ax = a2 * ra;
+      const double2 wi = make_double2((a2 > 0.0 ? xi.x * ra : 1.0) * (ax + nx), xi.y * ra * (ax + nx));
+      const double beta = n2 > 0.0 ? rx / (nx + ax) : 0.0;
+      if (tall) {
+        if (tid < kWideN) V[i * kWideN + tid] = tid == i ? wi : wl.vec[tid];
+        if (tid == 0) betas[i] = beta;
+      }
+      // this thread's columns from i on; the first 12 of them stay in registers
+      constexpr int kHeld = 12;
+      const int cf = i + ((q - i) & 7);
+      double2 held[kHeld];
+      double dr = 0.0, di = 0.0;
+      auto add = [&](const double2 &v, const double2 &w) {
+        dr = fma(v.x, w.x, fma(v.y, w.y, dr));
+        di = fma(v.y, w.x, fma(-v.x, w.y, di));
+      };
+#pragma unroll
+      for (int u = 0; u < kHeld; ++u) {
+        const int c = cf + 8 * u;
+        held[u] = c < cb ? B[c * kWideN + r] : make_double2(0.0, 0.0);
+      }
+#pragma unroll
+      for (int u = 0; u < kHeld; ++u) {
+        const int c = cf + 8 * u;
+        if (c < cb) add(held[u], c == i ? wi : wl.vec[c]);
+      }
+      for (int c = cf + 8 * kHeld; c < cb; c += 8) add(B[c * kWideN + r], wl.vec[c]);
+      wl.dot[q][r] = make_double2(dr, di);
+      __syncthreads();
+      dr = di = 0.0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const double2 v = wl.dot[u][r];
+        dr += v.x;
+        di += v.y;
+      }
+      dr *= beta;
+      di *= beta;
+      auto less = [&](const double2 &v, const double2 &w) {
+        return make_double2(v.x - (dr * w.x - di * w.y), v.y - (dr * w.y + di * w.x));
+      };
+#pragma unroll
+      for (int u = 0; u < kHeld; ++u) {
+        const int c = cf + 8 * u;
+        if (c < cb) {
+          const double2 v = less(held[u], c == i ? wi : wl.vec[c]);
+          B[c * kWideN + r] = v;
+          if (c == i && r < rb) {
+            const double w = wl.rn[r];
+            wl.rn[r] = r == pv || w < 0.0 ? -1.0 : fmax(w - fma(v.x, v.x, v.y * v.y), 0.0);
+          }
+        }
+      }
+      for (int c = cf + 8 * kHeld; c < cb; c += 8) {
+        double2 *m = B + c * kWideN + r;
+        *m = less(*m, wl.vec[c]);
+      }
+      __syncthreads();   // the next pivot row is complete
+    }
+  }
+
+  // ---------------------------------------------------------- sweeps in registers
+  const int row0 = wave * ROWS, c0 = 2 * lane;
+  const int nref = min(nr, nc);
+  Columns<N, W> M;
+#pragma unroll
+  for (int rr = 0; rr < ROWS; ++rr) {
+    const int r = row0 + rr;
+    double2 v[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int c = c0 + q;
+      v[q] = make_double2(0.0, 0.0);
+      if (cb <= N) {
+        if (r < nr && c < nc) v[q] = matrix(r, c);
+      } else if (r < nref && c < nref) {
+        v[q] = tall ? cconj(B[r * kWideN + c]) : B[c * kWideN + r];
+      }
+    }
+    M.Ar[rr] = v[0].x;
+    M.Ai[rr] = v[0].y;
+    M.Br[rr] = v[1].x;
+    M.Bi[rr] = v[1].y;
+  }
+  __syncthreads();   // the reflection buffers are free
+  const int rows = tall ? nref : nr;
+  const double zero_w = lane0(kZeroWeight * row_weights<N, W>(M, sh, rows, tid));   // wave-uniform
+  if (tall || cb <= N) lq_reduce<N, W>(M, sh, rows, nref, tid);   // (a wide M is L already)
+  const int NP = max(2, nref + (nref & 1));
+  const bool converged = jacobi_sweeps<N, W>(M, sh, NP / 2, zero_w, tid);
+  select_columns<N, W>(M, sh, P, st, ci, gate, cg, sg, Dm, nref, NP, zero_w, converged, tid);
+  const int k = sh.k;
+  const double nrm = sh.nrm;
+
+  // ---------------------------------------------------------- write factors
+  auto iso_at = [&](int r, int j) -> double2 & { return right ? ap_at(r, j) : aq_at(j, r); };
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int pos = c0 + q;
+    const int j = sh.rank[pos];
+    const bool keep = pos < NP && j < k;
+    const double inv = keep ? 1.0 / sqrt(sh.norm[pos]) : 0.0;
+#pragma unroll
+    for (int rr = 0; rr < ROWS; ++rr) {
+      const int r = row0 + rr;
+      if (keep && r < rows) {
+        const double vr = (q == 0 ? M.Ar[rr] : M.Br[rr]) * inv;
+        const double vi = (q == 0 ? M.Ai[rr] : M.Bi[rr]) * inv;
+        if (tall) B[j * kWideN + r] = make_double2(vr, vi);
+        else iso_at(r, j) = make_double2(vr, right ? vi : -vi);
+      }
+    }
+  }
+  if (tall) {
+    __syncthreads();
+    // column j <- H_0 ... H_{nref-1} (column, 0): 32 lanes per column, lane hl
+    // rows hl + 32 q
+    const int hl = lane & 31;
+    for (int j = 2 * wave + (lane >> 5); j < k + (k & 1); j += 2 * W) {
+      double2 u[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int r = hl + 32 * q;
+        u[q] = r < nref && j < k ? B[j * kWideN + r] : make_double2(0.0, 0.0);
+      }
+      for (int i = nref - 1; i >= 0; --i) {
+        const double beta = betas[i];
+        double2 w[8];
+        double dr = 0.0, di = 0.0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) w[q] = V[i * kWideN + hl + 32 * q];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {   // H = 1 - beta conj(w) w^T
+          dr = fma(w[q].x, u[q].x, fma(-w[q].y, u[q].y, dr));
+          di = fma(w[q].x, u[q].y, fma(w[q].y, u[q].x, di));
+        }
+        dr = beta * cols_sum<32>(dr);
+        di = beta * cols_sum<32>(di);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          u[q].x -= w[q].x * dr + w[q].y * di;
+          u[q].y -= w[q].x * di - w[q].y * dr;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int r = hl + 32 * q;
+        if (j < k && r < nr) iso_at(r, j) = make_double2(u[q].x, right ? u[q].y : -u[q].y);
+      }
+    }
+  }
+  if (k < Dm) {
+    const int w = Dm - k;
+    for (int e = tid; e < 2 * Dp * w; e += Y::T) ap_at(e / w, k + e % w) = make_double2(0.0, 0.0);
+    for (int e = tid; e < 2 * Dn * w; e += Y::T) aq_at(k + e / (2 * Dn), e % (2 * Dn)) = make_double2(0.0, 0.0);
+  }
+  __syncthreads();
+  // projection: out[j][x] = nrm sum_y conj(U[y][j]) S[y][x] (j < k, x < ncs)
+  for (int x0 = 0; x0 < ncs; x0 += N)
+    for (int j0 = 0; j0 < k; j0 += N / 2) {
+      double2 acc[Y::HROWS][2];
+      staged_tile_gemm<N, W, Y::HROWS>(
+          nr,
+          [&](int jj, int y) {
+            const int j = j0 + jj;
+            if (j >= k) return make_double2(0.0, 0.0);
+            const double2 u = iso_at(y, j);
+            return right ? cconj(u) : u;
+          },
+          [&](int y, int x) { return x0 + x < ncs ? source(y, x0 + x) : make_double2(0.0, 0.0); }, sh, acc);
+#pragma unroll
+      for (int rr = 0; rr < Y::HROWS; ++rr)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int j = j0 + wave * Y::HROWS + rr, x = x0 + c0 + q;
+          const double2 v = acc[rr][q];
+          if (j < k && x < ncs) {
+            if (right) aq_at(j, x) = make_double2(nrm * v.x, nrm * v.y);
+            else ap_at(x, j) = make_double2(nrm * v.x, -nrm * v.y);
+          }
+        }
+    }
+  if (tid == 0) dims[p + 1] = k;
+}
+
 // Rz on a run of gate records (Fig. 1a) for circuit ci: A[site][s] *=
 // exp(-/+ i theta / 2), one record per wave.  The records of a run act on
 // distinct sites.
@@ -1549,8 +1903,15 @@ __global__ __launch_bounds__(64 * sim_waves(NK), 4) void sim_steps_kernel(const 
               svd_step<64, W>(Pp, ci, stp, lds);
             } else {
               if constexpr (NK >= 128) {
-                if (P.wscratch && (Dp > kWideFrom || Dn > kWideFrom)) svd_step_wide(Pp, ci, stp);
-                else svd_step<128, W>(Pp, ci, stp, lds);
+                if (P.wscratch && (Dp > kWideFrom || Dn > kWideFrom)) {
+                  // rows and columns of the Jacobi matrix
+                  const int rows = 2 * (st.mode == GATE_RIGHT || st.mode == MOVE_RIGHT ? Dp : Dn);
+                  const int cols = st.mode == GATE_RIGHT ? 2 * Dn : st.mode == GATE_LEFT ? 2 * Dp : uniform(dims[1]);
+                  if (min(rows, cols) <= kSvMaxN) svd_step_wide(Pp, ci, stp, lds);
+                  else svd_step_stream(Pp, ci, stp);
+                } else {
+                  svd_step<128, W>(Pp, ci, stp, lds);
+                }
               }
             }
           }

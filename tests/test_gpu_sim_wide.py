@@ -136,3 +136,29 @@ def test_chi_above_128_not_supported():
     with pytest.raises(q.QKError) as e:
         q.simulate(torch.tensor(X, device="cuda"), _spec(q, M_SLICE, w), 129, w.cutoff)
     assert e.value.status == QK_ENOTSUP
+
+
+@pytest.mark.parametrize("m,d,chi", [(15, 5, 70), (16, 5, 96), (16, 6, 128), (15, 7, 128)])
+@pytest.mark.parametrize("routing", [0, 1])
+def test_steps_next_to_bonds_above_64(m, d, chi, routing):
+    """Chains whose middle bond lies above 64: two-site steps with more than
+    128 rows or columns (tall and wide Jacobi matrices, centre moves among
+    them), truncated, against the oracle: bonds, discarded weights, fidelity
+    and the kernel matrix."""
+    import paper_2411_09336_amd as q
+    import synthdata as sd
+    torch = require_gpu()
+    X = sd.make_uniform(2, m, seed=m + d)
+    spec = q.CircuitSpec(m, d, 2, 2.0, 2.0, routing)
+    b = q.simulate(torch.tensor(X, device="cuda"), spec, chi, 1e-12)
+    assert b.info()["unconverged_svds"] == 0
+    dims = b.bond_dims()
+    disc, deg = b.trunc_stats()
+    ref = [omps.simulate(x, d, 2, chi, 1e-12, 2.0, 2.0, routing=routing) for x in X]
+    print("largest bonds seen", [r.max_bond_seen for r in ref])
+    assert max(r.max_bond_seen for r in ref) > 64
+    for i, r in enumerate(ref):
+        if r.degenerate_cuts == 0 and deg[i] == 0:
+            assert list(dims[i]) == r.bond_dims
+            assert fidelity(b.export(i), r.tensors) > 1 - 1e-10
+            assert abs(disc[i] - r.discarded) <= 1e-9 * max(1.0, r.discarded)
