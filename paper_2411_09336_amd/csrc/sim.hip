@@ -128,14 +128,6 @@ __device__ inline double row_sum16(double x) {
 
 __device__ inline double2 cconj(double2 a) { return make_double2(a.x, -a.y); }
 
-// Sum over the 64 lanes of the wave (every lane receives the total).
-__device__ inline double wave_sum(double x) {
-  x = row_sum16(x);
-  x += __shfl_xor(x, 16, 64);
-  x += __shfl_xor(x, 32, 64);
-  return x;
-}
-
 // Lane-half and row exchanges of two doubles (gfx950 permlane swaps):
 // swap32 leaves a = [a_lo, b_lo], b = [a_hi, b_hi] (32-lane halves);
 // swap16 leaves a = [a_0, b_0, a_2, b_2], b = [a_1, b_1, a_3, b_3] (rows).
@@ -150,6 +142,24 @@ __device__ inline void swap16(double &a, double &b) {
   const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
   a = __hiloint2double(int(hi[0]), int(lo[0]));
   b = __hiloint2double(int(hi[1]), int(lo[1]));
+}
+
+// Sum over the 64 lanes of the wave (every lane receives the total).
+__device__ inline double wave_sum(double x) {
+  x = row_sum16(x);
+  double y = x;
+  swap16(x, y);
+  x += y;
+  y = x;
+  swap32(x, y);
+  return x + y;
+}
+
+// 1 / x for x > 0 (hardware estimate and two Newton steps).
+__device__ inline double reciprocal(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(r, fma(-x, r, 1.0), r);
 }
 
 // Largest of the wave's unsigned values, in every lane.
@@ -219,6 +229,20 @@ __device__ inline S uniform_load(const S *p) {
 }
 typedef uint8_t __attribute__((address_space(3))) LdsBytes;
 
+// What a launch keeps of its circuit at the start of the dynamic LDS: the
+// truncation statistics, read from and written to global memory once per
+// launch (a read-modify-write in every step would hold up its end).
+struct CircuitLds {
+  double disc, maxdisc;
+  int degen, unconv;
+  int64_t unused;
+};
+
+template <typename T>
+__device__ inline T *lds_at(int offset) {
+  return reinterpret_cast<T *>((uint8_t *)(LdsBytes *)(uintptr_t)uniform(offset));
+}
+
 constexpr int kKC = 16;  // contraction chunk of the pair product staged in LDS
 
 // Two-site steps are compiled for Jacobi matrices up to N x N (N = 16, 32,
@@ -245,11 +269,13 @@ struct Layout {
   static constexpr bool kOwn = N <= 64;
 };
 
-// Barrier of the W waves that run a step; with one wave, its own order.
+// Barrier of the W waves that run a step; with one wave, its own order (LDS
+// and memory accesses of one wave take effect in program order, so nothing
+// waits for the stores).
 template <int W>
 __device__ inline void step_sync() {
   if constexpr (W == 1) {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   } else {
     __syncthreads();
@@ -341,14 +367,29 @@ __device__ inline void staged_tile_gemm(int K, const FL &ldL, const FR &ldR, Ste
   }
   for (int k0 = 0; k0 < K; k0 += kKC) {
     step_sync<W>();  // the previous chunk (or earlier use of the buffers) is done
-    for (int e = tid; e < kKC * kRowsAll; e += Y::T) {
+    // every load of the chunk is in flight before the first is stored
+    constexpr int NL = (kKC * kRowsAll + Y::T - 1) / Y::T, NR2 = (kKC * N + Y::T - 1) / Y::T;
+    double2 vl[NL], vr[NR2];
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
       // consecutive threads walk the contraction index of one row
-      const int kk = e % kKC, y = e / kKC;
-      sh.stage.L[kk][y] = k0 + kk < K ? ldL(y, k0 + kk) : make_double2(0.0, 0.0);
+      const int e = tid + u * Y::T, kk = e % kKC, y = e / kKC;
+      vl[u] = y < kRowsAll && k0 + kk < K ? ldL(y, k0 + kk) : make_double2(0.0, 0.0);
     }
-    for (int e = tid; e < kKC * N; e += Y::T) {
-      const int x = e % N, kk = e / N;
-      sh.stage.R[kk][x] = k0 + kk < K ? ldR(k0 + kk, x) : make_double2(0.0, 0.0);
+#pragma unroll
+    for (int u = 0; u < NR2; ++u) {
+      const int e = tid + u * Y::T, x = e % N, kk = e / N;
+      vr[u] = kk < kKC && k0 + kk < K ? ldR(k0 + kk, x) : make_double2(0.0, 0.0);
+    }
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+      const int e = tid + u * Y::T;
+      if (e < kKC * kRowsAll) sh.stage.L[e % kKC][e / kKC] = vl[u];
+    }
+#pragma unroll
+    for (int u = 0; u < NR2; ++u) {
+      const int e = tid + u * Y::T;
+      if (e < kKC * N) sh.stage.R[e / N][e % N] = vr[u];
     }
     step_sync<W>();
     const int kc = wave < Y::WA ? min(kKC, K - k0) : 0;
@@ -639,6 +680,9 @@ struct SimStep {
                                 // gate among the circuit's (-1 for a centre move)
   int32_t nr;                   // Rz run: gate records [r0, r0 + nr); two-site step: largest bond
                                 // that can result (the kernel is chosen for these)
+  int32_t Pp, Pm, Pn;           // two-site step: pads of the three bonds, and the offsets of both
+  int32_t unused;               // sites in an MPS (with the step, so that no step waits for them)
+  int64_t off_p, off_q;
 };
 
 // Largest row norm of the rows that are no pivot yet: the sign-less upper
@@ -733,7 +777,7 @@ __device__ __forceinline__ void lq_reduce(Columns<N, W> &M, StepLds<N, W> &sh, i
         const double2 d = make_double2(pr * (ax + nx), pi * (ax + nx));
         sh.lqw[c0] = c0 == i ? d : make_double2(xr0, xi0);
         sh.lqw[c1] = c1 == i ? d : make_double2(xr1, xi1);
-        if (cp == (i >> 1)) sh.beta = n2 > 0.0 ? rn / (nx + ax) : 0.0;
+        if (cp == (i >> 1)) sh.beta = n2 > 0.0 ? rn * reciprocal(nx + ax) : 0.0;
       }
     }
     step_sync<W>();
@@ -818,8 +862,8 @@ __device__ __forceinline__ bool jacobi_sweeps(Columns<N, W> &M, StepLds<N, W> &s
 // sh.norm by position, sh.rank, sh.k and the factor sh.nrm that restores unit
 // weight; the truncation statistics of the circuit.
 template <int N, int W>
-__device__ __forceinline__ void select_columns(const Columns<N, W> &M, StepLds<N, W> &sh, const SvParams &P,
-                                               const SimStep &st, int64_t ci, bool gate, double cg, double sg, int Dm,
+__device__ __forceinline__ void select_columns(const Columns<N, W> &M, StepLds<N, W> &sh, CircuitLds &cl,
+                                               const SvParams &P, const SimStep &st, bool gate, double cg, double sg, int Dm,
                                                int nref, int NP, double zero_w, bool converged, int tid) {
   using Y = Layout<N, W>;
   constexpr int ROWS = Y::ROWS, LC = Y::LC;
@@ -926,17 +970,17 @@ __device__ __forceinline__ void select_columns(const Columns<N, W> &M, StepLds<N
       nrm = kept > 0.0 ? 1.0 / sqrt(kept) : 1.0;
       if (lane == 0) {
         const double disc = total > 0.0 ? tail / total : 0.0;
-        P.disc[ci] += disc;
-        P.maxdisc[ci] = fmax(P.maxdisc[ci], disc);
+        cl.disc += disc;
+        cl.maxdisc = fmax(cl.maxdisc, disc);
         if (k < nsv && sh.sorted[0] > 0.0 &&
             (sqrt(sh.sorted[k - 1]) - sqrt(sh.sorted[k])) / sqrt(sh.sorted[0]) < kDegenerateGap)
-          P.degen[ci] += 1;
+          cl.degen += 1;
       }
     } else {
       k = min(max(1, min(nsv, max(nnz, 1))), st.nr);
     }
     if (lane == 0) {
-      if (!converged) P.unconv[ci] += 1;
+      if (!converged) cl.unconv += 1;
       sh.k = k;
       sh.nrm = nrm;
     }
@@ -947,10 +991,11 @@ __device__ __forceinline__ void select_columns(const Columns<N, W> &M, StepLds<N
 // Two-site step of circuit ci on W waves, for Jacobi matrices up to N x N.
 template <int N, int W>
 __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t ci_, const SimStep *stp,
-                                                   int lds) {
+                                                   int lds, int Dp_, int Dm_, int Dn_) {
   using Y = Layout<N, W>;
   constexpr int ROWS = Y::ROWS, LC = Y::LC;
-  StepLds<N, W> &sh = *reinterpret_cast<StepLds<N, W> *>((uint8_t *)(LdsBytes *)(uintptr_t)uniform(lds));
+  CircuitLds &cl = *lds_at<CircuitLds>(lds);
+  StepLds<N, W> &sh = *lds_at<StepLds<N, W>>(lds + int(sizeof(CircuitLds)));
   const SvParams P = uniform_load(Pp);
   const SimStep st = uniform_load(stp);
   const int64_t ci = uniform(ci_);
@@ -961,10 +1006,10 @@ __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t c
 
   int32_t *dims = P.dims + ci * (P.m + 1);
   const int p = st.p;
-  const int Dp = uniform(dims[p]), Dm = uniform(dims[p + 1]), Dn = uniform(dims[p + 2]);
-  const int Pw = uniform(P.pad[p]), Pm = uniform(P.pad[p + 1]), Pn = uniform(P.pad[p + 2]);
-  double2 *Ap = P.f64 + ci * P.mps_stride + uniform(P.site_off[p]);
-  double2 *Aq = P.f64 + ci * P.mps_stride + uniform(P.site_off[p + 1]);
+  const int Dp = uniform(Dp_), Dm = uniform(Dm_), Dn = uniform(Dn_);
+  const int Pw = st.Pp, Pm = st.Pm, Pn = st.Pn;
+  double2 *Ap = P.f64 + ci * P.mps_stride + st.off_p;
+  double2 *Aq = P.f64 + ci * P.mps_stride + st.off_q;
   double2 *P2 = Y::kLds ? sh.P2 : P.scratch + int64_t(blockIdx.x) * P.scratch_stride;
 
   double cg = 1.0, sg = 0.0;
@@ -1042,7 +1087,7 @@ __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t c
   lq_reduce<N, W>(M, sh, nr, nref, tid);
   const int NP = max(2, nref + (nref & 1));
   const bool converged = jacobi_sweeps<N, W>(M, sh, NP / 2, zero_w, tid);
-  select_columns<N, W>(M, sh, P, st, ci, gate, cg, sg, Dm, nref, NP, zero_w, converged, tid);
+  select_columns<N, W>(M, sh, cl, P, st, gate, cg, sg, Dm, nref, NP, zero_w, converged, tid);
   const int k = sh.k;
   const double nrm = sh.nrm;
 
@@ -1143,7 +1188,8 @@ __device__ inline double half_sum(double x, int hf) {
 // (NP - 1 rounds of NP/2 disjoint pairs: every pair once per sweep).  Wave w
 // rotates pairs w, w + 16, ... of a round, two at a time (one per lane half,
 // each lane holding 8 rows of both columns), with one barrier per round.
-__device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, int64_t ci_, const SimStep *stp) {
+__device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, int64_t ci_, const SimStep *stp, int lds) {
+  CircuitLds &cl = *lds_at<CircuitLds>(lds);
   const SvParams P = uniform_load(Pq);
   const SimStep st = uniform_load(stp);
   const int64_t ci = uniform(ci_);
@@ -1450,16 +1496,16 @@ __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, in
       for (int u = kWideN - 1; u >= k; --u) tail += w_sorted[u];
       const double disc = total > 0.0 ? tail / total : 0.0;
       w_nrm = kept > 0.0 ? 1.0 / sqrt(kept) : 1.0;
-      P.disc[ci] += disc;
-      P.maxdisc[ci] = fmax(P.maxdisc[ci], disc);
+      cl.disc += disc;
+      cl.maxdisc = fmax(cl.maxdisc, disc);
       if (k < nsv && w_sorted[0] > 0.0 &&
           (sqrt(w_sorted[k - 1]) - sqrt(w_sorted[k])) / sqrt(w_sorted[0]) < kDegenerateGap)
-        P.degen[ci] += 1;
+        cl.degen += 1;
     } else {
       k = min(max(1, min(nsv, max(nnz, 1))), st.nr);
       w_nrm = 1.0;
     }
-    if (!converged) P.unconv[ci] += 1;
+    if (!converged) cl.unconv += 1;
     w_k = k;
   }
   __syncthreads();
@@ -1522,11 +1568,13 @@ struct WideLds {
   double part[kSvWaves];
 };
 
-__device__ __attribute__((noinline)) void svd_step_wide(const SvParams *Pq, int64_t ci_, const SimStep *stp, int lds) {
+__device__ __attribute__((noinline)) void svd_step_wide(const SvParams *Pq, int64_t ci_, const SimStep *stp, int lds,
+                                                        int Dp_, int Dm_, int Dn_) {
   constexpr int N = kSvMaxN, W = kSvWaves;
   using Y = Layout<N, W>;
   constexpr int ROWS = Y::ROWS;
-  StepLds<N, W> &sh = *reinterpret_cast<StepLds<N, W> *>((uint8_t *)(LdsBytes *)(uintptr_t)uniform(lds));
+  CircuitLds &cl = *lds_at<CircuitLds>(lds);
+  StepLds<N, W> &sh = *lds_at<StepLds<N, W>>(lds + int(sizeof(CircuitLds)));
   static_assert(sizeof(WideLds) <= sizeof(sh.stage), "the reflection buffers lie over the staging buffers");
   WideLds &wl = *reinterpret_cast<WideLds *>(&sh.stage);
   const SvParams P = uniform_load(Pq);
@@ -1537,10 +1585,10 @@ __device__ __attribute__((noinline)) void svd_step_wide(const SvParams *Pq, int6
 
   int32_t *dims = P.dims + ci * (P.m + 1);
   const int p = st.p;
-  const int Dp = uniform(dims[p]), Dm = uniform(dims[p + 1]), Dn = uniform(dims[p + 2]);
-  const int Pw = uniform(P.pad[p]), Pm = uniform(P.pad[p + 1]), Pn = uniform(P.pad[p + 2]);
-  double2 *Ap = P.f64 + ci * P.mps_stride + uniform(P.site_off[p]);
-  double2 *Aq = P.f64 + ci * P.mps_stride + uniform(P.site_off[p + 1]);
+  const int Dp = uniform(Dp_), Dm = uniform(Dm_), Dn = uniform(Dn_);
+  const int Pw = st.Pp, Pm = st.Pm, Pn = st.Pn;
+  double2 *Ap = P.f64 + ci * P.mps_stride + st.off_p;
+  double2 *Aq = P.f64 + ci * P.mps_stride + st.off_q;
   double2 *B = P.wscratch + int64_t(blockIdx.x) * kWideSlot;
   double2 *P2 = B + kWideN * kWideN;
   double2 *V = P2 + kWideN * kWideN;                                   // reflection i at V + i kWideN
@@ -1631,7 +1679,7 @@ __device__ __attribute__((noinline)) void svd_step_wide(const SvParams *Pq, int6
       const double rx = n2 > 0.0 ? rsqrt(n2) : 0.0, ra = a2 > 0.0 ? rsqrt(a2) : 0.0;
       const double nx = n2 * rx, ax = a2 * ra;
       const double2 wi = make_double2((a2 > 0.0 ? xi.x * ra : 1.0) * (ax + nx), xi.y * ra * (ax + nx));
-      const double beta = n2 > 0.0 ? rx / (nx + ax) : 0.0;
+      const double beta = n2 > 0.0 ? rx * reciprocal(nx + ax) : 0.0;
       if (tall) {
         if (tid < kWideN) V[i * kWideN + tid] = tid == i ? wi : wl.vec[tid];
         if (tid == 0) betas[i] = beta;
@@ -1719,7 +1767,7 @@ __device__ __attribute__((noinline)) void svd_step_wide(const SvParams *Pq, int6
   if (tall || cb <= N) lq_reduce<N, W>(M, sh, rows, nref, tid);   // (a wide M is L already)
   const int NP = max(2, nref + (nref & 1));
   const bool converged = jacobi_sweeps<N, W>(M, sh, NP / 2, zero_w, tid);
-  select_columns<N, W>(M, sh, P, st, ci, gate, cg, sg, Dm, nref, NP, zero_w, converged, tid);
+  select_columns<N, W>(M, sh, cl, P, st, gate, cg, sg, Dm, nref, NP, zero_w, converged, tid);
   const int k = sh.k;
   const double nrm = sh.nrm;
 
@@ -1861,7 +1909,7 @@ constexpr size_t sim_lds_bytes() {
   if constexpr (NK >= 32) b = std::max(b, sizeof(StepLds<32, W>));
   if constexpr (NK >= 64) b = std::max(b, sizeof(StepLds<64, W>));
   if constexpr (NK >= 128) b = std::max(b, sizeof(StepLds<128, W>));
-  return b;
+  return sizeof(CircuitLds) + b;
 }
 
 template <int NK>
@@ -1879,6 +1927,8 @@ __global__ __launch_bounds__(64 * sim_waves(NK), 4) void sim_steps_kernel(const 
   const SvParams P = uniform_load(Pp);
   const int64_t ci = uniform(circuit_of(P.base));
   if (ci >= P.n) return;
+  CircuitLds &cl = *lds_at<CircuitLds>(lds);   // read and written by thread 0 alone
+  if (threadIdx.x == 0) cl = CircuitLds{P.disc[ci], P.maxdisc[ci], P.degen[ci], P.unconv[ci], 0};
   for (int s = s0; s < s1; ++s) {
     const SimStep *stp = steps + s;
     const SimStep st = uniform_load(stp);
@@ -1886,31 +1936,34 @@ __global__ __launch_bounds__(64 * sim_waves(NK), 4) void sim_steps_kernel(const 
       rz_run<W>(P, ci, recs + st.r0, st.nr, coef_z);
     } else {
       const int32_t *dims = P.dims + ci * (P.m + 1) + st.p;
-      const int Dp = __builtin_amdgcn_readfirstlane(dims[0]), Dn = __builtin_amdgcn_readfirstlane(dims[2]);
+      const int Dp = uniform(dims[0]), Dm = uniform(dims[1]), Dn = uniform(dims[2]);
+      // every wave has read the bonds, by which it takes its kernel, before
+      // one (a step of one wave) rewrites them
+      if constexpr (NK > 16) __syncthreads();
       // rows and columns of the Jacobi matrix and of the projection source
       int size = 2 * max(Dp, Dn);
-      if (st.mode == MOVE_RIGHT || st.mode == MOVE_LEFT) size = max(size, __builtin_amdgcn_readfirstlane(dims[1]));
+      if (st.mode == MOVE_RIGHT || st.mode == MOVE_LEFT) size = max(size, Dm);
       if constexpr (NK == 16) {
-        svd_step<16, 1>(Pp, ci, stp, lds);
+        svd_step<16, 1>(Pp, ci, stp, lds, Dp, Dm, Dn);
       } else {
         if (size <= 16) {
-          if (threadIdx.x < 64) svd_step<16, 1>(Pp, ci, stp, lds);
+          if (threadIdx.x < 64) svd_step<16, 1>(Pp, ci, stp, lds, Dp, Dm, Dn);
         } else if (NK == 32 || size <= 32) {
-          svd_step<32, W>(Pp, ci, stp, lds);
+          svd_step<32, W>(Pp, ci, stp, lds, Dp, Dm, Dn);
         } else {
           if constexpr (NK >= 64) {
             if (NK == 64 || size <= 64) {
-              svd_step<64, W>(Pp, ci, stp, lds);
+              svd_step<64, W>(Pp, ci, stp, lds, Dp, Dm, Dn);
             } else {
               if constexpr (NK >= 128) {
                 if (P.wscratch && (Dp > kWideFrom || Dn > kWideFrom)) {
                   // rows and columns of the Jacobi matrix
                   const int rows = 2 * (st.mode == GATE_RIGHT || st.mode == MOVE_RIGHT ? Dp : Dn);
-                  const int cols = st.mode == GATE_RIGHT ? 2 * Dn : st.mode == GATE_LEFT ? 2 * Dp : uniform(dims[1]);
-                  if (min(rows, cols) <= kSvMaxN) svd_step_wide(Pp, ci, stp, lds);
-                  else svd_step_stream(Pp, ci, stp);
+                  const int cols = st.mode == GATE_RIGHT ? 2 * Dn : st.mode == GATE_LEFT ? 2 * Dp : Dm;
+                  if (min(rows, cols) <= kSvMaxN) svd_step_wide(Pp, ci, stp, lds, Dp, Dm, Dn);
+                  else svd_step_stream(Pp, ci, stp, lds);
                 } else {
-                  svd_step<128, W>(Pp, ci, stp, lds);
+                  svd_step<128, W>(Pp, ci, stp, lds, Dp, Dm, Dn);
                 }
               }
             }
@@ -1918,7 +1971,7 @@ __global__ __launch_bounds__(64 * sim_waves(NK), 4) void sim_steps_kernel(const 
         }
       }
     }
-    __syncthreads();  // the next step reads the tensors and bond dims this one wrote
+    step_sync<W>();  // the next step reads the tensors and bond dims this one wrote
     if (P.trace && st.kind == STEP_TWO_SITE && st.r0 >= 0 && threadIdx.x < 64) {
       // memory trace after a two-qubit gate: the bond at its cut and
       // sum_l D_l D_{l+1} (complex entries per physical index) over the MPS.
@@ -1934,6 +1987,12 @@ __global__ __launch_bounds__(64 * sim_waves(NK), 4) void sim_steps_kernel(const 
         t[1] = acc;
       }
     }
+  }
+  if (threadIdx.x == 0) {
+    P.disc[ci] = cl.disc;
+    P.maxdisc[ci] = cl.maxdisc;
+    P.degen[ci] = cl.degen;
+    P.unconv[ci] = cl.unconv;
   }
 }
 
@@ -2074,22 +2133,22 @@ SimPlan *make_sim_plan(const std::vector<qk_gate> &gates, int m, int chi, double
     if (gates[gi].op == OP_RZ) {
       size_t ge = gi;
       while (ge < gates.size() && gates[ge].op == OP_RZ) ++ge;
-      push({STEP_RZ, 0, 0, 0, -1, -1, int32_t(gi), int32_t(ge - gi)}, 0);
+      push({STEP_RZ, 0, 0, 0, -1, -1, int32_t(gi), int32_t(ge - gi), 0, 0, 0, 0, 0, 0}, 0);
       gi = ge;
       continue;
     }
     const int p = gates[gi].site;
-    for (; center < p; ++center) push({STEP_TWO_SITE, center, MOVE_RIGHT, OP_ID, -1, -1, -1, 0}, 0);
-    for (; center > p + 1; --center) push({STEP_TWO_SITE, center - 1, MOVE_LEFT, OP_ID, -1, -1, -1, 0}, 0);
+    for (; center < p; ++center) push({STEP_TWO_SITE, center, MOVE_RIGHT, OP_ID, -1, -1, -1, 0, 0, 0, 0, 0, 0, 0}, 0);
+    for (; center > p + 1; --center) push({STEP_TWO_SITE, center - 1, MOVE_LEFT, OP_ID, -1, -1, -1, 0, 0, 0, 0, 0, 0, 0}, 0);
     const bool absorb_right = next2q[gi] < 0 || next2q[gi] > p;
     push({STEP_TWO_SITE, p, absorb_right ? GATE_RIGHT : GATE_LEFT, gates[gi].op == 1 ? OP_RXX : OP_SWAP,
-          gates[gi].feat_i, gates[gi].feat_j, int32_t(d2q), 0},
+          gates[gi].feat_i, gates[gi].feat_j, int32_t(d2q), 0, 0, 0, 0, 0, 0, 0},
          d2q + 1);
     ++d2q;
     center = absorb_right ? p + 1 : p;
     ++gi;
   }
-  for (; center < m - 1; ++center) push({STEP_TWO_SITE, center, MOVE_RIGHT, OP_ID, -1, -1, -1, 0}, 0);
+  for (; center < m - 1; ++center) push({STEP_TWO_SITE, center, MOVE_RIGHT, OP_ID, -1, -1, -1, 0, 0, 0, 0, 0, 0, 0}, 0);
   return plan;
 }
 void free_sim_plan(SimPlan *plan) { delete plan; }
@@ -2123,7 +2182,15 @@ qk_status run_simulation(qk_mps_batch *b, const SimPlan *plan, const double *fea
   const int64_t grid = graph ? std::min(n, graph_circuits) : n;
   const int64_t replays = (n + grid - 1) / grid;
 
-  const auto &steps = plan->steps;
+  std::vector<SimStep> steps = plan->steps;
+  for (SimStep &x : steps)
+    if (x.kind == STEP_TWO_SITE) {
+      x.Pp = b->pad[x.p];
+      x.Pm = b->pad[x.p + 1];
+      x.Pn = b->pad[x.p + 2];
+      x.off_p = b->site_off[x.p];
+      x.off_q = b->site_off[x.p + 1];
+    }
   const auto &gate_no = plan->gate_no;
   const int size = plan->size;
   const bool wide = plan->wide;
