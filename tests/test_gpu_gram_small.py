@@ -137,3 +137,23 @@ def test_jobs_of_several_kernels():
         for k, b in enumerate(batches):
             assert torch.equal(jobs[2 * k]["out"], q.gram(b, precision=prec))
             assert torch.equal(jobs[2 * k + 1]["out"], q.gram_block(b, 1, 2, b, 0, 5, precision=prec))
+
+
+@pytest.mark.parametrize("bonds", [(33, 33), (64, 64), (17, 64), (64, 3), (48, 33), (49, 63)])
+def test_split_edge_tiles(bonds):
+    """The split forms' workgroup kernels leave out the tiles beyond the bonds
+    of either operand: bras and kets of other bonds than each other."""
+    import paper_2411_09336_amd as q
+    require_gpu()
+    rng = np.random.default_rng(64 * bonds[0] + bonds[1])
+    m = 13
+    base = random_mps(rng, m, min(bonds))
+    wide = random_mps(rng, m, max(bonds))
+    bras, kets = ([(random_mps(rng, m, bd, base) if bd == min(bonds) else random_mps(rng, m, bd, wide))
+                   for _ in range(3)] for bd in bonds)
+    K_ref = np.array([[abs(ogram.overlap(a, c)) ** 2 for c in kets] for a in bras])
+    a, b = q.import_batch(bras), q.import_batch(kets)
+    for prec, tol in SPLIT_TOL.items():
+        err = np.abs(q.gram(a, b, precision=prec).cpu().numpy() - K_ref).max()
+        print(bonds, prec, "max|dK|", err)
+        assert err < tol
