@@ -1366,26 +1366,38 @@ __device__ inline void i8_digit(const uint4 &x0, const uint4 &x1, int a, const u
   }
 }
 
-// Same products with the LDS operand read one digit at a time (tile base tg:
-// fragments (digit a, plane 0 / 1) at (2 a + q) KiB).  CPL1: complement plane 1
+// Same products with the LDS operand read one digit ahead of its MFMAs (tile
+// base tg: fragments (digit a, plane 0 / 1) at (2 a + q) KiB; x holds digit 0
+// on entry and, on return, digit 0 of the tile at tn, so that no MFMA waits
+// for LDS).  CPL1: complement plane 1
 // in the real part (GEMM1: re += X0 Y0 + (~X1) Y1, im += X0 Y1 + X1 Y0);
 // otherwise complement plane 0 in the imaginary part (GEMM2: re += X0 Y0 +
 // X1 Y1, im += (~X0) Y1 + X1 Y0).  The part with the complemented operand
 // starts from the class corrections `corr` (so its sums come out exact), the
 // other from zero.  P22_RE: include the (2, 2) pair (class 4) in the real
-// part.  Only one digit's operands are live.
+// part.
+__device__ inline void i8_first(const uint8_t *tg, uint4 (&x)[2]) {
+  x[0] = *reinterpret_cast<const uint4 *>(tg);
+  x[1] = *reinterpret_cast<const uint4 *>(tg + kI8FragBytes);
+}
+
 template <bool CPL1, bool P22_RE>
-__device__ inline void i8_block_lds(const uint8_t *tg, const uint4 (&Y0)[4], const uint4 (&Y1)[4],
-                                    const i32x4 (&corr)[4], I8Acc &acc) {
+__device__ inline void i8_block_lds(const uint8_t *tg, const uint8_t *tn, uint4 (&x)[2], const uint4 (&Y0)[4],
+                                    const uint4 (&Y1)[4], const i32x4 (&corr)[4], I8Acc &acc) {
 #pragma unroll
   for (int c = 0; c < 5; ++c) {
     acc.re[c] = (CPL1 && c < 4) ? corr[c] : i32x4{0, 0, 0, 0};
     acc.im[c] = (!CPL1 && c < 4) ? corr[c] : i32x4{0, 0, 0, 0};
   }
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
-    i8_digit<CPL1, P22_RE>(*reinterpret_cast<const uint4 *>(tg + (a * 2 + 0) * kI8FragBytes),
-                           *reinterpret_cast<const uint4 *>(tg + (a * 2 + 1) * kI8FragBytes), a, Y0, Y1, acc);
+  for (int a = 0; a < 4; ++a) {
+    uint4 n[2];
+    i8_first(a < 3 ? tg + (a + 1) * 2 * kI8FragBytes : tn, n);
+    __builtin_amdgcn_sched_barrier(0);   // the reads stay before this digit's MFMAs
+    i8_digit<CPL1, P22_RE>(x[0], x[1], a, Y0, Y1, acc);
+    x[0] = n[0];
+    x[1] = n[1];
+  }
 }
 
 // Exact digit sum of element e of a class accumulator set (corrections
@@ -1415,6 +1427,10 @@ __device__ inline void i8_corrections(const int (&cs)[4], i32x4 (&corr)[4]) {
 // Tiles beyond the bonds at a site are left out (5,050 pairs of 14 sites, chi
 // 64: 2.66 -> 1.53 ms; 1,830 of 100 sites, chi 45: 8.5 -> 6.4 ms; 61 x 301 of
 // 100 sites, chi 64: 65.4 -> 63.1 ms).
+// Digits of E and T are read one digit ahead of their MFMAs, site digit sums
+// with the fragments a GEMM ahead and offsets a site ahead: 63.1 -> 62.2 ms, so
+// little of what is left is latency: int8 products issue at 2.2 POP/s at the
+// clock of about 2.0 GHz that they leave the card.
 // Work split of the int8 kernel: workgroups of four waves, two per CU, each
 // workgroup on its own pair, so the two workgroups of a CU interleave their
 // MFMA and VALU phases.  Wave w owns column block c = w of every 64 x 64
@@ -1425,19 +1441,19 @@ __device__ inline void i8_corrections(const int (&cs)[4], i32x4 (&corr)[4]) {
 //   III. GEMM2(s=1) reads X ; E' -> Y (T0 consumed), which is the next E
 constexpr int kI8Threads = 256;
 
+__device__ inline int pick(const int4 &v, int e) { return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w; }
+
 struct I8Ctx {
   int lane, j, g, cb;
 };
 
 // This lane's digit fragments of column block c of one physical index of a
 // packed site block (real plane, then imaginary plane), loaded one GEMM
-// ahead of their use so that global latency overlaps the current GEMM; the
-// column exponent and digit sums are read at the start of the GEMM itself
-// (first needed after its first tile of MFMAs).
+// ahead of their use so that global latency overlaps the current GEMM, with
+// the column exponent and the digit sums that seed the accumulators.
 struct I8Operand {
   uint4 f[8];
-  const uint8_t *site;
-  int s;
+  int e, cs[4];
 };
 
 __device__ inline void i8_load(const I8Ctx &C, const uint8_t *site, int s, I8Operand &o) {
@@ -1447,28 +1463,21 @@ __device__ inline void i8_load(const I8Ctx &C, const uint8_t *site, int s, I8Ope
     o.f[k] = i8_frag(r, s, k, 0, C.cb, C.lane);
     o.f[4 + k] = i8_frag(r, s, k, 1, C.cb, C.lane);
   }
-  o.site = site;
-  o.s = s;
-}
-
-__device__ inline void i8_column_meta(const I8Ctx &C, const I8Operand &o, int &e, int (&cs)[4]) {
   const int col = 16 * C.cb + C.j;
-  e = int(gview(reinterpret_cast<const int8_t *>(o.site))[o.s * 128 + col]);
-  const auto p = gview(reinterpret_cast<const int *>(o.site + kI8ExpBytes) + o.s * 256 + col);
+  o.e = int(gview(reinterpret_cast<const int8_t *>(site))[s * 128 + col]);
+  const auto p = gview(reinterpret_cast<const int *>(site + kI8ExpBytes) + s * 256 + col);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) cs[k] = p[64 * k];
+  for (int k = 0; k < 4; ++k) o.cs[k] = p[64 * k];
 }
 
 // GEMM1: T_s[a][b'] for all rows a (tiles rt = 0..3) and b' in block c;
 // tmax = max |T| over the whole column b' = 16 c + j.
-__device__ inline void i8_gemm1(const I8Ctx &C, const I8Operand &Bs, const uint8_t *Ebuf, const int *s_ea, int nrt,
+__device__ inline void i8_gemm1(const I8Ctx &C, const I8Operand &Bs, const uint8_t *Ebuf, const int *s_ea, int nrt, uint4 (&x)[2],
                                 double (&Td)[4][2][4], double &tmax) {
   const uint4(&Br)[4] = *reinterpret_cast<const uint4(*)[4]>(&Bs.f[0]);
   const uint4(&Bi)[4] = *reinterpret_cast<const uint4(*)[4]>(&Bs.f[4]);
-  int ebc, cs[4];
-  i8_column_meta(C, Bs, ebc, cs);
   i32x4 corr[4];
-  i8_corrections(cs, corr);
+  i8_corrections(Bs.cs, corr);
   tmax = 0.0;
 #pragma unroll
   for (int rt = 0; rt < 4; ++rt) {
@@ -1480,12 +1489,14 @@ __device__ inline void i8_gemm1(const I8Ctx &C, const I8Operand &Bs, const uint8
     // re = Er Br - Ei Bi = Er Br + (~Ei) Bi + colsum(Bi) ; im = Er Bi + Ei Br
     I8Acc acc;
     __builtin_amdgcn_s_setprio(1);
-    i8_block_lds<true, false>(Ebuf + size_t(rt * 8) * kI8FragBytes + C.lane * 16, Br, Bi, corr, acc);
+    const uint8_t *E0 = Ebuf + C.lane * 16, *tg = E0 + size_t(rt * 8) * kI8FragBytes;
+    const int4 ea = *reinterpret_cast<const int4 *>(s_ea + 16 * rt + 4 * C.g);
+    i8_block_lds<true, false>(tg, rt + 1 < nrt ? tg + 8 * kI8FragBytes : E0, x, Br, Bi, corr, acc);
     __builtin_amdgcn_s_setprio(0);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       // a code product is x_E x_B 2^(62 - ea - eb); i8_value counts units of 2^24 of it
-      const int ex = s_ea[16 * rt + 4 * C.g + e] + ebc - 38;
+      const int ex = pick(ea, e) + Bs.e - 38;
       const double vr = ldexp(i8_value<false>(acc.re, e), ex);
       const double vi = ldexp(i8_value<false>(acc.im, e), ex);
       Td[rt][0][e] = vr;
@@ -1520,24 +1531,24 @@ __device__ inline void i8_store(const I8Ctx &C, uint8_t *buf, const double (&V)[
 // GEMM2: E'^T[b'][a'] += sum_a T_s[a][b'] conj(A_s[a][a']) for all b' (tiles
 // bt = 0..3) and a' in block c.
 __device__ inline void i8_gemm2(const I8Ctx &C, const I8Operand &As, const uint8_t *Tbuf, const int *s_eTs, int nbt,
-                                double (&Ep)[4][2][4]) {
+                                uint4 (&x)[2], double (&Ep)[4][2][4]) {
   const uint4(&Ar)[4] = *reinterpret_cast<const uint4(*)[4]>(&As.f[0]);
   const uint4(&Ai)[4] = *reinterpret_cast<const uint4(*)[4]>(&As.f[4]);
-  int eac, cs[4];
-  i8_column_meta(C, As, eac, cs);
   i32x4 corr[4];
-  i8_corrections(cs, corr);
+  i8_corrections(As.cs, corr);
 #pragma unroll
   for (int bt = 0; bt < 4; ++bt) {
     if (bt >= nbt) continue;   // columns beyond the bond
     // re = Tr Ar + Ti Ai ; im = Ti Ar - Tr Ai = Ti Ar + (~Tr) Ai + colsum(Ai)
     I8Acc acc;
     __builtin_amdgcn_s_setprio(1);
-    i8_block_lds<false, QK_I8_PAIR22>(Tbuf + size_t(bt * 8) * kI8FragBytes + C.lane * 16, Ar, Ai, corr, acc);
+    const uint8_t *T0 = Tbuf + C.lane * 16, *tg = T0 + size_t(bt * 8) * kI8FragBytes;
+    const int4 eT = *reinterpret_cast<const int4 *>(s_eTs + 16 * bt + 4 * C.g);
+    i8_block_lds<false, QK_I8_PAIR22>(tg, bt + 1 < nbt ? tg + 8 * kI8FragBytes : T0, x, Ar, Ai, corr, acc);
     __builtin_amdgcn_s_setprio(0);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int ex = s_eTs[16 * bt + 4 * C.g + e] + eac - 38;
+      const int ex = pick(eT, e) + As.e - 38;
       Ep[bt][0][e] += ldexp(i8_value<QK_I8_PAIR22>(acc.re, e), ex);
       Ep[bt][1][e] += ldexp(i8_value<false>(acc.im, e), ex);
     }
@@ -1570,29 +1581,36 @@ __device__ void overlap_i8(const GramJobDev &J, int64_t ia, int64_t ib, uint8_t 
   }
   const int col = 16 * C.cb + C.j;
   I8Operand P0, P1;   // operands of the current and the next GEMM
-  i8_load(C, uniform_ptr(bbase + gview(J.b_off)[0]), 0, P0);
-  int na = 1;
+  uint4 x[2];         // first digit of the next tile
+  const uint8_t *A = uniform_ptr(abase + gview(J.a_off)[0]), *B = uniform_ptr(bbase + gview(J.b_off)[0]);
+  i8_load(C, B, 0, P0);
+  // the next site's offsets and the bonds on its left are read a site ahead
+  int na = 1, ca = gview(J.a_bond)[1], cbd = gview(J.b_bond)[1];
   for (int l = 0; l < J.m; ++l) {
-    const uint8_t *A = uniform_ptr(abase + gview(J.a_off)[l]);
-    const uint8_t *B = uniform_ptr(bbase + gview(J.b_off)[l]);
+    const int l1 = min(l + 1, J.m - 1);
+    const int64_t aoff = gview(J.a_off)[l1], boff = gview(J.b_off)[l1];
     double Td[4][2][4], Ep[4][2][4];
     double tmax;
     // I
     i8_load(C, B, 1, P1);
     // 16-row tiles of the bra's left bond and 16-column tiles of the right bonds;
     // a wave whose column block lies beyond a bond has no tile there
-    const int nan = (gview(J.a_bond)[l + 1] + 15) >> 4, nbn = (gview(J.b_bond)[l + 1] + 15) >> 4;
+    const int nan = (__builtin_amdgcn_readfirstlane(ca) + 15) >> 4, nbn = (__builtin_amdgcn_readfirstlane(cbd) + 15) >> 4;
     const int n1 = C.cb < nbn ? na : 0, n2 = C.cb < nan ? nbn : 0;
-    i8_gemm1(C, P0, X, s_ea, n1, Td, tmax);
+    ca = gview(J.a_bond)[l1 + 1];
+    cbd = gview(J.b_bond)[l1 + 1];
+    i8_first(X + C.lane * 16, x);
+    i8_gemm1(C, P0, X, s_ea, n1, x, Td, tmax);
     {
       const int eT0 = exp_above_i8(tmax);
       if (C.g == 0) s_eT[col] = eT0;
       i8_store(C, Y, Td, eT0);
     }
     i8_load(C, A, 0, P0);
-    i8_gemm1(C, P1, X, s_ea, n1, Td, tmax);
+    i8_gemm1(C, P1, X, s_ea, n1, x, Td, tmax);
     __syncthreads();
     // II
+    i8_first(Y + C.lane * 16, x);
     i8_load(C, A, 1, P1);
     {
       const int eT1 = exp_above_i8(tmax);
@@ -1605,11 +1623,14 @@ __device__ void overlap_i8(const GramJobDev &J, int64_t ia, int64_t ib, uint8_t 
       for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int e = 0; e < 4; ++e) Ep[bt][q][e] = 0.0;
-    i8_gemm2(C, P0, Y, s_eT, n2, Ep);
+    i8_gemm2(C, P0, Y, s_eT, n2, x, Ep);
     __syncthreads();
     // III
-    if (l + 1 < J.m) i8_load(C, uniform_ptr(bbase + gview(J.b_off)[l + 1]), 0, P0);
-    i8_gemm2(C, P1, X, s_eT + kSP, n2, Ep);
+    i8_first(X + C.lane * 16, x);
+    A = uniform_ptr(abase + aoff);
+    B = uniform_ptr(bbase + boff);
+    if (l + 1 < J.m) i8_load(C, B, 0, P0);
+    i8_gemm2(C, P1, X, s_eT + kSP, n2, x, Ep);
     if (l + 1 == J.m) {
       // E_m[0][0] = E'^T[0][0]: wave 0, lane 0, tile 0, e = 0
       if (tid == 0) {
@@ -1671,7 +1692,6 @@ __device__ inline int4 rows_of_lanes(int *s_e, int lane, int e) {
   __builtin_amdgcn_wave_barrier();
   return r;
 }
-__device__ inline int pick(const int4 &v, int e) { return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w; }
 
 // What the two forms do with a 16-row operand (four digits of two planes), a
 // column block of a site and a tile of FP64 values.
@@ -1983,8 +2003,8 @@ __global__ __launch_bounds__(threads_of<PREC>(), PREC == QK_FP32 ? 3 : 2) void g
   __shared__ int64_t s_slot;
   __shared__ double s_red[4];
   __shared__ double s_ov[2];
-  __shared__ int s_ea[MAXP];
-  __shared__ int s_eT[2 * MAXP];
+  __shared__ __align__(16) int s_ea[MAXP];
+  __shared__ __align__(16) int s_eT[2 * MAXP];
   __shared__ double s_mx[4 * MAXP];
   int job;
   int64_t i, j;
