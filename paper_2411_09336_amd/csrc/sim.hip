@@ -750,12 +750,24 @@ __device__ __forceinline__ void lq_reduce(Columns<N, W> &M, StepLds<N, W> &sh, i
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cp = lane % LC, row0 = (wave * Y::RG + lane / LC) * ROWS;
   const int c0 = 2 * cp, c1 = 2 * cp + 1;
-  int left = Y::RG * ROWS;   // rows of this wave that are no pivot yet
+  constexpr bool kSkip = N >= 64;   // the branches cost small matrices more than the rows
+  // Bits 4 rr .. of `fin`: how many row groups of this wave have row rr done (a
+  // pivot, or beyond nr); a row that all have done is left out of the updates
+  // (128 x 128: 520,000 -> 463,000 cycles per LQ)
+  uint32_t fin = 0;
+  if constexpr (kSkip) {
+#pragma unroll
+    for (int g = 0; g < Y::RG; ++g)
+#pragma unroll
+      for (int rr = 0; rr < ROWS; ++rr) fin += (wave * Y::RG + g) * ROWS + rr < nr ? 0u : 1u << (4 * rr);
+  }
+  constexpr uint32_t kAll = 0x11111111u * Y::RG & uint32_t((1ull << (4 * ROWS)) - 1);
   for (int i = 0; i < nref; ++i) {
+    const uint32_t before = fin;
     const int pv = __builtin_amdgcn_readfirstlane(heaviest_row<N>(sh.w, lane));
     const int pg = pv / ROWS, ri = pv % ROWS;   // row group and row of the pivot
     if (wave == pg / Y::RG) {
-      --left;
+      fin += 1u << (4 * ri);
       double xr0 = 0.0, xi0 = 0.0, xr1 = 0.0, xi1 = 0.0;
 #pragma unroll
       for (int rr = 0; rr < ROWS; ++rr)
@@ -781,12 +793,14 @@ __device__ __forceinline__ void lq_reduce(Columns<N, W> &M, StepLds<N, W> &sh, i
       }
     }
     step_sync<W>();
-    if (wave < Y::WA && (left > 0 || wave == pg / Y::RG)) {
+    if (wave < Y::WA && before != kAll) {
       const double2 w0 = sh.lqw[c0], w1 = sh.lqw[c1];
       const double beta = sh.beta;
       double d[2 * ROWS];  // d = r . conj(w) for the rows (re, im)
 #pragma unroll
       for (int rr = 0; rr < ROWS; ++rr) {
+        d[2 * rr] = d[2 * rr + 1] = 0.0;
+        if (kSkip && ((before >> (4 * rr)) & 15u) == Y::RG) continue;
         d[2 * rr] = fma(M.Ar[rr], w0.x, fma(M.Ai[rr], w0.y, fma(M.Br[rr], w1.x, M.Bi[rr] * w1.y)));
         d[2 * rr + 1] = fma(M.Ai[rr], w0.x, fma(-M.Ar[rr], w0.y, fma(M.Bi[rr], w1.x, -M.Br[rr] * w1.y)));
       }
@@ -798,6 +812,7 @@ __device__ __forceinline__ void lq_reduce(Columns<N, W> &M, StepLds<N, W> &sh, i
       }
 #pragma unroll
       for (int rr = 0; rr < ROWS; ++rr) {
+        if (kSkip && ((before >> (4 * rr)) & 15u) == Y::RG) continue;
         const double dr = beta * d[2 * rr], di = beta * d[2 * rr + 1];
         M.Ar[rr] -= dr * w0.x - di * w0.y;
         M.Ai[rr] -= dr * w0.y + di * w0.x;
@@ -808,6 +823,14 @@ __device__ __forceinline__ void lq_reduce(Columns<N, W> &M, StepLds<N, W> &sh, i
           const double v = sh.w[row0 + rr];
           sh.w[row0 + rr] = row0 + rr == pv || v < 0.0 ? -1.0 : fmax(v - fma(er, er, ei * ei), 0.0);
         }
+      }
+      if (kSkip && wave == pg / Y::RG) {   // the pivot row ends at column i
+#pragma unroll
+        for (int rr = 0; rr < ROWS; ++rr)
+          if (rr == ri && lane / LC == pg % Y::RG) {
+            if (c0 > i) M.Ar[rr] = M.Ai[rr] = 0.0;
+            if (c1 > i) M.Br[rr] = M.Bi[rr] = 0.0;
+          }
       }
     }
     step_sync<W>();
@@ -1895,12 +1918,17 @@ __device__ inline void rz_run(const SvParams &P, int64_t ci, const qk_gate *recs
 // rounds of a sweep are bound by the latency of their reduction, rotation
 // and barriers until the matrix nears 128 x 128 (there by the FP64 VALU), so
 // what counts is fewer lanes on empty rows, fewer waves to wait for, and
-// several circuits per CU: NK = 16 takes one wave per circuit, 32 four, 64
-// eight.  Against one 128 x 128 kernel of 16 waves for every step: 8 points
+// several circuits per CU: NK = 16 takes one wave per circuit, 32 four (two:
+// 9.6 -> 11.3 ms for 128 x 50, d = 2), 64 four with 256 registers per lane
+// (eight with 128 take the same alone, but every wave forms the rotations of
+// a round, and two circuits on a CU then share its issue slots: 300 x 60,
+// d = 3: 168 -> 147 ms; 300 x 40 103.6 -> 90.8), 128 sixteen (eight with 256
+// registers gain nothing on 16 x 18, d = 8, and lose a tenth next to bonds
+// above 64).  Against one 128 x 128 kernel of 16 waves for every step: 8 points
 // x 20 qubits, d = 1: 5.5 -> 0.65 ms; 512 x 165, d = 1: 112 -> 6 ms; 128 x 50,
-// d = 2: 82 -> 11 ms; 300 x 60, d = 3 (two circuits per CU on 44 of 256 CUs):
-// 885 -> 180 ms; 16 x 18, d = 8 (saturated at 64): 663 -> 445 ms.
-constexpr int sim_waves(int nk) { return nk == 16 ? 1 : nk == 32 ? 4 : nk == 64 ? 8 : 16; }
+// d = 2: 82 -> 9.6 ms; 300 x 60, d = 3 (two circuits per CU on 44 of 256 CUs):
+// 885 -> 147 ms; 16 x 18, d = 8 (saturated at 64): 663 -> 325 ms.
+constexpr int sim_waves(int nk) { return nk == 16 ? 1 : nk == 32 ? 4 : nk == 64 ? 4 : 16; }
 
 template <int NK>
 constexpr size_t sim_lds_bytes() {
@@ -1913,7 +1941,7 @@ constexpr size_t sim_lds_bytes() {
 }
 
 template <int NK>
-__global__ __launch_bounds__(64 * sim_waves(NK), 4) void sim_steps_kernel(const SvParams *Pp,
+__global__ __launch_bounds__(64 * sim_waves(NK), NK == 64 ? 2 : 4) void sim_steps_kernel(const SvParams *Pp,
                                                                           const SimStep *steps, int s0, int s1,
                                                                           const qk_gate *recs, double coef_z) {
   constexpr int W = sim_waves(NK);
