@@ -206,6 +206,19 @@ __device__ inline void wave_sum16(double (&v)[16]) {
   }
 }
 
+// Sixteen sums over the 32 lanes of each half, by one exchange between its
+// rows: eight row sums instead of sixteen.
+__device__ inline void half_sum16(double (&v)[16]) {
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    swap16(v[2 * k], v[2 * k + 1]);
+    double a = row_sum16(v[2 * k] + v[2 * k + 1]), b = a;   // rows 0, 2: value 2k, rows 1, 3: 2k + 1
+    swap16(a, b);
+    v[2 * k] = a;
+    v[2 * k + 1] = b;
+  }
+}
+
 // A value of lane 0, in every lane (wave-uniform control flow and
 // identical rotation parameters across the rows of a column pair).
 __device__ inline double lane0(double x) {
@@ -806,6 +819,8 @@ __device__ __forceinline__ void lq_reduce(Columns<N, W> &M, StepLds<N, W> &sh, i
       }
       if constexpr (LC == 64 && ROWS == 8) {
         wave_sum16(d);
+      } else if constexpr (LC == 32 && ROWS == 8) {
+        half_sum16(d);
       } else {
 #pragma unroll
         for (int u = 0; u < 2 * ROWS; ++u) d[u] = cols_sum<LC>(d[u]);
@@ -947,12 +962,21 @@ __device__ __forceinline__ void select_columns(const Columns<N, W> &M, StepLds<N
       s += v[u];
       suf[u] = s;
     }
+    double rest;
+    if constexpr (N == 16) {   // within the first row of lanes (the others hold zeros)
+      s += dpp_mov<0x101>(s);  // row_shl
+      s += dpp_mov<0x102>(s);
+      s += dpp_mov<0x104>(s);
+      s += dpp_mov<0x108>(s);
+      rest = dpp_mov<0x101>(s);
+    } else {
 #pragma unroll
-    for (int o = 1; o < 64 && o * PER < N; o <<= 1) {
-      const double t = __shfl_down(s, o, 64);
-      s += lane + o < 64 ? t : 0.0;
+      for (int o = 1; o < 64 && o * PER < N; o <<= 1) {
+        const double t = __shfl_down(s, o, 64);
+        s += lane + o < 64 ? t : 0.0;
+      }
+      rest = __shfl_down(s, 1, 64);
     }
-    const double rest = __shfl_down(s, 1, 64);
     const double total = lane0(s);
     int nnz = 0, above = 0;
     const int nsv = nref;
@@ -982,22 +1006,29 @@ __device__ __forceinline__ void select_columns(const Columns<N, W> &M, StepLds<N
         k = max(1, min(k, rg * Dm));
       }
       k = min(k, st.nr);
-      double kept = 0.0, tail = 0.0;
+      k = uniform(k);
+      // weight of the columns left out: the suffix sum from column k on
+      double tail = 0.0;
 #pragma unroll
       for (int u = 0; u < PER; ++u) {
-        kept += PER * lane + u < k ? v[u] : 0.0;
-        tail += PER * lane + u < k ? 0.0 : v[u];
+        const double t = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(suf[u]), (k / PER) & 63),
+                                          __builtin_amdgcn_readlane(__double2loint(suf[u]), (k / PER) & 63));
+        if (k < N && k % PER == u) tail = t;
       }
-      kept = lane0(wave_sum(kept));
-      tail = lane0(wave_sum(tail));
-      nrm = kept > 0.0 ? 1.0 / sqrt(kept) : 1.0;
+      const double kept = total - tail;
+      nrm = kept > 0.0 ? rsqrt(kept) : 1.0;
       if (lane == 0) {
-        const double disc = total > 0.0 ? tail / total : 0.0;
+        const double disc = total > 0.0 ? tail * reciprocal(total) : 0.0;
         cl.disc += disc;
         cl.maxdisc = fmax(cl.maxdisc, disc);
-        if (k < nsv && sh.sorted[0] > 0.0 &&
-            (sqrt(sh.sorted[k - 1]) - sqrt(sh.sorted[k])) / sqrt(sh.sorted[0]) < kDegenerateGap)
-          cl.degen += 1;
+        // (sqrt(w_k-1) - sqrt(w_k)) / sqrt(w_0) below the gap: the difference
+        // of the roots is at least that of the weights over 2 sqrt(w_k-1)
+        if (k < nsv && sh.sorted[0] > 0.0) {
+          const double wa = sh.sorted[k - 1], wb = sh.sorted[k], w0 = sh.sorted[0];
+          if ((wa - wb) * (wa - wb) <= (8.0 * kDegenerateGap * kDegenerateGap) * (wa * w0) &&
+              (sqrt(wa) - sqrt(wb)) / sqrt(w0) < kDegenerateGap)
+            cl.degen += 1;
+        }
       }
     } else {
       k = min(max(1, min(nsv, max(nnz, 1))), st.nr);
@@ -1107,8 +1138,13 @@ __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t c
   }
   const double zero_w = lane0(kZeroWeight * row_weights<N, W>(M, sh, nr, tid));   // wave-uniform
   const int nref = min(nr, nc);
-  lq_reduce<N, W>(M, sh, nr, nref, tid);
-  const int NP = max(2, nref + (nref & 1));
+  // Up to four columns take fewer sweeps than reflections are worth: of a
+  // 20,000-cycle step at bonds up to 2, 5,000 were the LQ and 5,400 the sweeps
+  // after it (8 points x 20 qubits, d = 1: 640 -> 555 us without)
+  const bool few = N == 16 && nc <= 4;
+  if (!few) lq_reduce<N, W>(M, sh, nr, nref, tid);
+  const int cols = few ? nc : nref;
+  const int NP = max(2, cols + (cols & 1));
   const bool converged = jacobi_sweeps<N, W>(M, sh, NP / 2, zero_w, tid);
   select_columns<N, W>(M, sh, cl, P, st, gate, cg, sg, Dm, nref, NP, zero_w, converged, tid);
   const int k = sh.k;
@@ -1123,7 +1159,7 @@ __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t c
     const int pos = 2 * cp + q;
     const int j = sh.rank[pos];
     const bool keep = pos < NP && j < k;
-    const double inv = keep ? 1.0 / sqrt(sh.norm[pos]) : 0.0;
+    const double inv = keep ? rsqrt(sh.norm[pos]) : 0.0;
 #pragma unroll
     for (int rr = 0; rr < ROWS; ++rr) {
       const int r = row0 + rr;
@@ -1136,9 +1172,17 @@ __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t c
     }
   }
   if (k < Dm) {
-    const int w = Dm - k;
-    for (int e = tid; e < 2 * Dp * w; e += Y::T) ap_at(e / w, k + e % w) = make_double2(0.0, 0.0);
-    for (int e = tid; e < 2 * Dn * w; e += Y::T) aq_at(k + e / (2 * Dn), e % (2 * Dn)) = make_double2(0.0, 0.0);
+    // e / w by reciprocal, exact here: (e + 1/2) / w is at least 1 / (2 w) from any integer
+    const int w = Dm - k, w2 = 2 * Dn;
+    const float rw = __builtin_amdgcn_rcpf(float(w)), rw2 = __builtin_amdgcn_rcpf(float(w2));
+    for (int e = tid; e < 2 * Dp * w; e += Y::T) {
+      const int y = int((float(e) + 0.5f) * rw);
+      ap_at(y, k + e - y * w) = make_double2(0.0, 0.0);
+    }
+    for (int e = tid; e < w2 * w; e += Y::T) {
+      const int c = int((float(e) + 0.5f) * rw2);
+      aq_at(k + c, e - c * w2) = make_double2(0.0, 0.0);
+    }
   }
   step_sync<W>();
   // projection: out[j][x] = nrm sum_y conj(U[y][j]) S[y][x] (j < k, x < ncs)
@@ -1801,7 +1845,7 @@ __device__ __attribute__((noinline)) void svd_step_wide(const SvParams *Pq, int6
     const int pos = c0 + q;
     const int j = sh.rank[pos];
     const bool keep = pos < NP && j < k;
-    const double inv = keep ? 1.0 / sqrt(sh.norm[pos]) : 0.0;
+    const double inv = keep ? rsqrt(sh.norm[pos]) : 0.0;
 #pragma unroll
     for (int rr = 0; rr < ROWS; ++rr) {
       const int r = row0 + rr;
@@ -1852,9 +1896,17 @@ __device__ __attribute__((noinline)) void svd_step_wide(const SvParams *Pq, int6
     }
   }
   if (k < Dm) {
-    const int w = Dm - k;
-    for (int e = tid; e < 2 * Dp * w; e += Y::T) ap_at(e / w, k + e % w) = make_double2(0.0, 0.0);
-    for (int e = tid; e < 2 * Dn * w; e += Y::T) aq_at(k + e / (2 * Dn), e % (2 * Dn)) = make_double2(0.0, 0.0);
+    // e / w by reciprocal, exact here: (e + 1/2) / w is at least 1 / (2 w) from any integer
+    const int w = Dm - k, w2 = 2 * Dn;
+    const float rw = __builtin_amdgcn_rcpf(float(w)), rw2 = __builtin_amdgcn_rcpf(float(w2));
+    for (int e = tid; e < 2 * Dp * w; e += Y::T) {
+      const int y = int((float(e) + 0.5f) * rw);
+      ap_at(y, k + e - y * w) = make_double2(0.0, 0.0);
+    }
+    for (int e = tid; e < w2 * w; e += Y::T) {
+      const int c = int((float(e) + 0.5f) * rw2);
+      aq_at(k + c, e - c * w2) = make_double2(0.0, 0.0);
+    }
   }
   __syncthreads();
   // projection: out[j][x] = nrm sum_y conj(U[y][j]) S[y][x] (j < k, x < ncs)
@@ -1925,9 +1977,9 @@ __device__ inline void rz_run(const SvParams &P, int64_t ci, const qk_gate *recs
 // d = 3: 168 -> 147 ms; 300 x 40 103.6 -> 90.8), 128 sixteen (eight with 256
 // registers gain nothing on 16 x 18, d = 8, and lose a tenth next to bonds
 // above 64).  Against one 128 x 128 kernel of 16 waves for every step: 8 points
-// x 20 qubits, d = 1: 5.5 -> 0.65 ms; 512 x 165, d = 1: 112 -> 6 ms; 128 x 50,
-// d = 2: 82 -> 9.6 ms; 300 x 60, d = 3 (two circuits per CU on 44 of 256 CUs):
-// 885 -> 147 ms; 16 x 18, d = 8 (saturated at 64): 663 -> 325 ms.
+// x 20 qubits, d = 1: 5.5 -> 0.54 ms; 512 x 165, d = 1: 112 -> 3.5 ms; 128 x 50,
+// d = 2: 82 -> 9.0 ms; 300 x 60, d = 3 (two circuits per CU on 44 of 256 CUs):
+// 885 -> 143 ms; 16 x 18, d = 8 (saturated at 64): 663 -> 325 ms.
 constexpr int sim_waves(int nk) { return nk == 16 ? 1 : nk == 32 ? 4 : nk == 64 ? 4 : 16; }
 
 template <int NK>
