@@ -219,6 +219,21 @@ __device__ inline void half_sum16(double (&v)[16]) {
   }
 }
 
+// Four wave sums at once, as wave_sum16; identical in every lane.
+__device__ inline void wave_sum4(double (&v)[4]) {
+  swap32(v[0], v[1]);
+  swap32(v[2], v[3]);
+  double a = v[0] + v[1], b = v[2] + v[3];
+  swap16(a, b);
+  a = row_sum16(a + b);   // rows 0, 1, 2, 3: values 0, 2, 1, 3
+  b = a;
+  swap16(a, b);
+  v[0] = v[1] = a;
+  v[2] = v[3] = b;
+  swap32(v[0], v[1]);
+  swap32(v[2], v[3]);
+}
+
 // A value of lane 0, in every lane (wave-uniform control flow and
 // identical rotation parameters across the rows of a column pair).
 __device__ inline double lane0(double x) {
@@ -702,15 +717,16 @@ struct SimStep {
 // halves order like the norms; the low bits carry the row (complemented).
 template <int N>
 __device__ inline int heaviest_row(const double *rn, int lane) {
+  constexpr uint32_t kRow = N > 128 ? 255 : 127;
   uint32_t best = 0;
 #pragma unroll
   for (int u = 0; u < (N + 63) / 64; ++u) {
     const int row = lane + 64 * u;
     const double v = row < N ? rn[row] : -1.0;
-    const uint32_t key = v < 0.0 ? 0u : (uint32_t(__double2hiint(v)) & ~127u) | uint32_t(127 - row);
+    const uint32_t key = v < 0.0 ? 0u : (uint32_t(__double2hiint(v)) & ~kRow) | (kRow - row);
     best = max(best, key);
   }
-  return 127 - int(wave_max_bits(best) & 127u);
+  return int(kRow - (wave_max_bits(best) & kRow));
 }
 
 // Squared norms of the rows of M (row r < N to sh.w, -1 beyond nr) and
@@ -1229,15 +1245,6 @@ __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t c
   if (tid == 0) dims[p + 1] = k;
 }
 
-// Sum over the 32 lanes of lane half hf (rows 2 hf, 2 hf + 1), as the value
-// of the half's first lane in every lane of the half: identical rotation
-// parameters for all rows of a column pair.
-__device__ inline double half_sum(double x, int hf) {
-  x = row_sum16(x);
-  x += __shfl_xor(x, 16, 64);
-  return __shfl(x, hf << 5, 64);
-}
-
 // Two-site step of circuit ci whose Jacobi matrix has more than 128 rows and
 // columns (both neighbouring bonds above 64; one 1024-thread workgroup).  The same
 // operation as svd_step -- pair product, theta, one-sided Jacobi on the
@@ -1249,12 +1256,18 @@ __device__ inline double half_sum(double x, int hf) {
 //      (column c at W + c kWideN, rows 0..255, zero beyond nr);
 //   S: the projection source (row-major, row stride kWideN).
 // M is first reduced as in svd_step (M <- M H_0 H_1 ..., Householder
-// reflections from the right with the rows in order of decreasing norm), so
+// reflections from the right, the heaviest remaining row next), so
 // that only its first min(nr, nc) columns carry more than rounding-level
-// weight; the Jacobi sweeps then pair those columns in round-robin order
-// (NP - 1 rounds of NP/2 disjoint pairs: every pair once per sweep).  Wave w
-// rotates pairs w, w + 16, ... of a round, two at a time (one per lane half,
-// each lane holding 8 rows of both columns), with one barrier per round.
+// weight; the Jacobi sweeps then pair those columns, two to a block, in
+// round-robin order of the blocks.  Wave w takes block pairs w, w + 16, ... of
+// a round with their four columns in registers and rotates the four pairs
+// across the blocks (in the first round also the two inside them), so every
+// two columns meet once per sweep and a round moves each column through L2
+// once for two rotations: single columns made a round of 256 x 256 a transfer
+// of 2 MiB at the 125 bytes a cycle that one CU reaches.
+// 4 points x 16 qubits, d = 5, chi 128 (saturated): 814 -> 664 ms, with the
+// heaviest remaining row as the next pivot and the pair product and projection
+// staged through LDS 617.
 __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, int64_t ci_, const SimStep *stp, int lds) {
   CircuitLds &cl = *lds_at<CircuitLds>(lds);
   const SvParams P = uniform_load(Pq);
@@ -1264,11 +1277,10 @@ __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, in
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   __shared__ double w_norm[kWideN];   // squared norm of each Jacobi column (row norms during the LQ)
   __shared__ double w_sorted[kWideN]; // norms in decreasing order
-  __shared__ int w_col[kWideN];       // column of each rank (pivot row of each LQ step)
+  __shared__ int w_col[kWideN];       // column of each rank
   __shared__ double2 w_vec[kWideN];   // Householder vector of an LQ step
   __shared__ double2 w_dot[4][kWideN];// partial products row . conj(w)
   __shared__ double w_part[kSvWaves];
-  __shared__ double w_beta;
   __shared__ int w_k;
   __shared__ double w_nrm, w_tot;
 
@@ -1296,20 +1308,31 @@ __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, in
   else { nr = 2 * Dn; nc = Dm; ncs = 2 * Dp; }
 
   // ---------------------------------------------------------- pair product -> W
-  // P[(s', a)][(t', b)] = sum_c A_p[s'][a][c] A_{p+1}[t'][c][b]; consecutive
-  // threads take consecutive b (coalesced reads of A_{p+1})
-  for (int e = tid; e < 4 * Dp * Dn; e += kSvThreads) {
-    const int y = e / (2 * Dn), x = e % (2 * Dn);
-    const double2 *ar = Ap + (size_t(y / Dp) * Pp + y % Dp) * Pm;
-    const double2 *bc = Aq + size_t(x / Dn) * Pm * Pn + x % Dn;
-    double re = 0.0, im = 0.0;
-    for (int c = 0; c < Dm; ++c) {
-      const double2 u = ar[c], v = bc[size_t(c) * Pn];
-      re = fma(u.x, v.x, fma(-u.y, v.y, re));
-      im = fma(u.x, v.y, fma(u.y, v.x, im));
+  // P[(s', a)][(t', b)] = sum_c A_p[s'][a][c] A_{p+1}[t'][c][b]
+  using T = Layout<kSvMaxN, kSvWaves>;
+  StepLds<kSvMaxN, kSvWaves> &sh = *lds_at<StepLds<kSvMaxN, kSvWaves>>(lds + int(sizeof(CircuitLds)));
+  auto ap_at = [&](int y, int c) -> double2 & {
+    const int s = phys_of(y, Dp);
+    return Ap[(s * Pp + y - s * Dp) * Pm + c];
+  };
+  auto aq_at = [&](int c, int x) -> double2 & {
+    const int t = phys_of(x, Dn);
+    return Aq[(t * Pm + c) * Pn + x - t * Dn];
+  };
+  for (int y0 = 0; y0 < 2 * Dp; y0 += kSvMaxN)
+    for (int x0 = 0; x0 < 2 * Dn; x0 += kSvMaxN) {
+      double2 pt[T::ROWS][2];
+      staged_tile_gemm<kSvMaxN, kSvWaves, T::ROWS>(
+          Dm, [&](int y, int c) { return y0 + y < 2 * Dp ? ap_at(y0 + y, c) : make_double2(0.0, 0.0); },
+          [&](int c, int x) { return x0 + x < 2 * Dn ? aq_at(c, x0 + x) : make_double2(0.0, 0.0); }, sh, pt);
+#pragma unroll
+      for (int rr = 0; rr < T::ROWS; ++rr)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int y = y0 + wave * T::ROWS + rr, x = x0 + 2 * lane + q;
+          if (y < 2 * Dp && x < 2 * Dn) W[y * kWideN + x] = pt[rr][q];
+        }
     }
-    W[size_t(y) * kWideN + x] = make_double2(re, im);
-  }
   __syncthreads();
   // ---------------------------------------------------------- projection source -> S
   // gates: theta (absorb right) or theta^H (absorb left), which is also the
@@ -1363,10 +1386,11 @@ __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, in
   const double zero_w = lane0(kZeroWeight * w_tot);
 
   // ---------------------------------------------------------- LQ preconditioning
-  // Step i reflects the i-th heaviest row x (restricted to columns >= i) onto
-  // column i: w = x + e^{i arg x_i} |x| e_i, beta = 1 / (|x| (|x| + |x_i|)),
+  // Step i reflects the heaviest remaining row x (restricted to columns >= i)
+  // onto column i: w = x + e^{i arg x_i} |x| e_i, beta = 1 / (|x| (|x| + |x_i|)),
   // every row r <- r - beta (r . conj w) w.  Thread (r, q) = (tid % 256,
-  // tid / 256) takes row r and the columns c = q mod 4.
+  // tid / 256) takes row r and the columns c = i + q mod 4, the first of them
+  // held in registers between the product and the update.
   const int nref = min(nr, nc);
   {
     if (tid < kWideN) {
@@ -1376,23 +1400,12 @@ __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, in
           const double2 v = W[size_t(c) * kWideN + tid];
           t = fma(v.x, v.x, fma(v.y, v.y, t));
         }
-      w_norm[tid] = t;
-    }
-    __syncthreads();
-    if (tid < kWideN) {
-      const double v = w_norm[tid];
-      int rank = 0;
-#pragma unroll 1
-      for (int u = 0; u < kWideN; ++u) {
-        const double o = w_norm[u];
-        rank += (o > v || (o == v && u < tid)) ? 1 : 0;
-      }
-      w_col[rank] = tid;
+      w_norm[tid] = tid < nr ? t : -1.0;
     }
     __syncthreads();
     const int r = tid & (kWideN - 1), q = tid >> 8;
     for (int i = 0; i < nref; ++i) {
-      const int pv = w_col[i];
+      const int pv = __builtin_amdgcn_readfirstlane(heaviest_row<kWideN>(w_norm, lane));
       if (tid < kWideN) {
         // the pivot row restricted to columns >= i, and |x|
         const double2 x = (tid >= i && tid < nc) ? W[size_t(tid) * kWideN + pv] : make_double2(0.0, 0.0);
@@ -1401,34 +1414,55 @@ __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, in
         if (lane == 0) w_part[wave] = n2;
       }
       __syncthreads();
-      if (tid == 0) {
-        const double nx = sqrt(w_part[0] + w_part[1] + w_part[2] + w_part[3]);
-        const double2 xi = w_vec[i];
-        const double ax = sqrt(fma(xi.x, xi.x, xi.y * xi.y));
-        const double pr = ax > 0.0 ? xi.x / ax : 1.0, pi = ax > 0.0 ? xi.y / ax : 0.0;
-        w_vec[i] = make_double2(pr * (ax + nx), pi * (ax + nx));
-        w_beta = nx > 0.0 ? 1.0 / (nx * (nx + ax)) : 0.0;
-      }
-      __syncthreads();
+      const double n2 = (w_part[0] + w_part[1]) + (w_part[2] + w_part[3]);
+      const double2 xi = w_vec[i];
+      const double a2 = fma(xi.x, xi.x, xi.y * xi.y);
+      const double rx = n2 > 0.0 ? rsqrt(n2) : 0.0, ra = a2 > 0.0 ? rsqrt(a2) : 0.0;
+      const double nx = n2 * rx, ax = a2 * ra;
+      const double2 wi = make_double2((a2 > 0.0 ? xi.x * ra : 1.0) * (ax + nx), xi.y * ra * (ax + nx));
+      const double beta = n2 > 0.0 ? rx * reciprocal(nx + ax) : 0.0;
+      constexpr int kHeld = 12;
+      double2 held[kHeld];
       double dr = 0.0, di = 0.0;
+      auto add = [&](const double2 &v, const double2 &w) {
+        dr = fma(v.x, w.x, fma(v.y, w.y, dr));
+        di = fma(v.y, w.x, fma(-v.x, w.y, di));
+      };
+      double2 *mine = W + r;
+#pragma unroll
+      for (int u = 0; u < kHeld; ++u) {
+        const int c = i + q + 4 * u;
+        held[u] = c < nc && r < nr ? mine[c * kWideN] : make_double2(0.0, 0.0);
+      }
+#pragma unroll
+      for (int u = 0; u < kHeld; ++u) {
+        const int c = i + q + 4 * u;
+        if (c < nc) add(held[u], c == i ? wi : w_vec[c]);
+      }
       if (r < nr)
-        for (int c = i + q; c < nc; c += 4) {
-          const double2 v = W[size_t(c) * kWideN + r], w = w_vec[c];
-          dr = fma(v.x, w.x, fma(v.y, w.y, dr));
-          di = fma(v.y, w.x, fma(-v.x, w.y, di));
-        }
+        for (int c = i + q + 4 * kHeld; c < nc; c += 4) add(mine[c * kWideN], w_vec[c]);
       w_dot[q][r] = make_double2(dr, di);
       __syncthreads();
       if (r < nr) {
-        const double beta = w_beta;
         const double2 d0 = w_dot[0][r], d1 = w_dot[1][r], d2 = w_dot[2][r], d3 = w_dot[3][r];
-        const double br = beta * ((d0.x + d1.x) + (d2.x + d3.x)), bi = beta * ((d0.y + d1.y) + (d2.y + d3.y));
-        for (int c = i + q; c < nc; c += 4) {
-          const double2 w = w_vec[c];
-          double2 *m = W + size_t(c) * kWideN + r;
-          const double2 v = *m;
-          *m = make_double2(v.x - (br * w.x - bi * w.y), v.y - (br * w.y + bi * w.x));
+        dr = beta * ((d0.x + d1.x) + (d2.x + d3.x));
+        di = beta * ((d0.y + d1.y) + (d2.y + d3.y));
+        auto less = [&](const double2 &v, const double2 &w) {
+          return make_double2(v.x - (dr * w.x - di * w.y), v.y - (dr * w.y + di * w.x));
+        };
+#pragma unroll
+        for (int u = 0; u < kHeld; ++u) {
+          const int c = i + q + 4 * u;
+          if (c < nc) {
+            const double2 v = less(held[u], c == i ? wi : w_vec[c]);
+            mine[c * kWideN] = v;
+            if (c == i) {
+              const double w = w_norm[r];
+              w_norm[r] = r == pv || w < 0.0 ? -1.0 : fmax(w - fma(v.x, v.x, v.y * v.y), 0.0);
+            }
+          }
         }
+        for (int c = i + q + 4 * kHeld; c < nc; c += 4) mine[c * kWideN] = less(mine[c * kWideN], w_vec[c]);
       }
       __syncthreads();  // the next step reads its pivot row and rewrites the LDS vectors
     }
@@ -1437,63 +1471,78 @@ __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, in
   // ---------------------------------------------------------- Jacobi sweeps
   const int NP = max(2, nref + (nref & 1));
   bool converged = false;
-  const int half = NP / 2, rounds = NP - 1;
-  // two pairs in flight per wave: lane half hf takes pair k0 + 16 hf, its
-  // lane hl rows hl + 32 q (q < 8); sums over a half, then the value of the
-  // half's first lane in all its lanes (the same rotation for every row)
-  const int hf = lane >> 5, hl = lane & 31;
+  // columns in blocks of two (an even number of them, the last perhaps empty)
+  const int blocks = NP / 2, even = blocks + (blocks & 1), rounds = even - 1;
+  using Column = double2[4];   // rows lane + 64 q
   for (int sweep = 0; sweep < kMaxSweeps && !converged; ++sweep) {
     bool large = false;
     for (int rd = 0; rd < rounds; ++rd) {
-      for (int k0 = wave; k0 < half; k0 += 2 * kSvWaves) {
-        // round-robin pairing: column NP-1 meets column rd, the others pair
-        // symmetrically around rd (indices mod NP-1)
-        const int k = k0 + hf * kSvWaves;
-        const bool act = k < half;
-        const int i = !act ? 0 : k == 0 ? NP - 1 : (rd + k) % rounds;
-        const int j = !act ? 0 : k == 0 ? rd : (rd - k + rounds) % rounds;
-        double2 *X = W + size_t(i) * kWideN + hl;
-        double2 *Y = W + size_t(j) * kWideN + hl;
-        double2 x[8], y[8];
-        double a = 0.0, b = 0.0, gr = 0.0, gi = 0.0;
+      for (int k = wave; k < even / 2; k += kSvWaves) {
+        // round-robin pairing: the last block meets block rd, the others pair
+        // symmetrically around rd (indices mod even - 1)
+        const int i = k == 0 ? even - 1 : (rd + k) % rounds;
+        const int j = k == 0 ? rd : (rd - k + rounds) % rounds;
+        Column x[2], y[2];
+        double w[4] = {0.0, 0.0, 0.0, 0.0};   // squared norms of x, y
+        double2 *X = W + size_t(2 * i) * kWideN + lane, *Y = W + size_t(2 * j) * kWideN + lane;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          x[q] = act ? X[32 * q] : make_double2(0.0, 0.0);
-          y[q] = act ? Y[32 * q] : make_double2(0.0, 0.0);
-          a = fma(x[q].x, x[q].x, fma(x[q].y, x[q].y, a));
-          b = fma(y[q].x, y[q].x, fma(y[q].y, y[q].y, b));
-          gr = fma(x[q].x, y[q].x, fma(x[q].y, y[q].y, gr));
-          gi = fma(x[q].x, y[q].y, fma(-x[q].y, y[q].x, gi));
-        }
-        a = half_sum(a, hf);
-        b = half_sum(b, hf);
-        gr = half_sum(gr, hf);
-        gi = half_sum(gi, hf);
-        const double g2 = fma(gr, gr, gi * gi);
-        if (act && a > zero_w && b > zero_w && g2 > (kJacobiTol * kJacobiTol) * (a * b)) {
-          if (g2 > (kJacobiLarge * kJacobiLarge) * (a * b)) large = true;
-          // the Hermitian 2 x 2 rotation of the pair's Gram block (as in
-          // jacobi_round): X' = c X - s u Y, Y' = s X + c u Y,
-          // u = conj<X,Y> / |<X,Y>|
-          const double rg = rsqrt(g2);
-          const double zeta = 0.5 * (b - a) * rg;
-          const double den = fabs(zeta) + sqrt(fma(zeta, zeta, 1.0));
-          double rdn = __builtin_amdgcn_rcp(den);
-          rdn = fma(rdn, fma(-den, rdn, 1.0), rdn);
-          rdn = fma(rdn, fma(-den, rdn, 1.0), rdn);
-          const double t = zeta >= 0.0 ? rdn : -rdn;
-          const double c = rsqrt(fma(t, t, 1.0));
-          const double sn = c * t;
-          const double ur = gr * rg, ui = -gi * rg;
-          const double xr_ = -sn * ur, xi_ = -sn * ui;   // -s u
-          const double yr_ = c * ur, yi_ = c * ui;       //  c u
+        for (int c = 0; c < 2; ++c)
 #pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const double2 xo = x[q], yo = y[q];
-            X[32 * q] = make_double2(fma(c, xo.x, fma(xr_, yo.x, -xi_ * yo.y)), fma(c, xo.y, fma(xr_, yo.y, xi_ * yo.x)));
-            Y[32 * q] = make_double2(fma(sn, xo.x, fma(yr_, yo.x, -yi_ * yo.y)),
-                                     fma(sn, xo.y, fma(yr_, yo.y, yi_ * yo.x)));
+          for (int q = 0; q < 4; ++q) {
+            x[c][q] = i < blocks ? X[c * kWideN + 64 * q] : make_double2(0.0, 0.0);
+            y[c][q] = j < blocks ? Y[c * kWideN + 64 * q] : make_double2(0.0, 0.0);
           }
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            w[c] = fma(x[c][q].x, x[c][q].x, fma(x[c][q].y, x[c][q].y, w[c]));
+            w[2 + c] = fma(y[c][q].x, y[c][q].x, fma(y[c][q].y, y[c][q].y, w[2 + c]));
+          }
+        wave_sum4(w);
+        bool moved = false;
+        auto rotate = [&](Column &u, Column &v, double &nu, double &nv, double gr, double gi) {
+          const double g2 = fma(gr, gr, gi * gi);
+          if (nu > zero_w && nv > zero_w && g2 > (kJacobiTol * kJacobiTol) * (nu * nv)) {
+            if (g2 > (kJacobiLarge * kJacobiLarge) * (nu * nv)) large = true;
+            moved = true;
+            const Rotation r = rotation(nu, nv, gr, gi, g2);
+            nu = fmax(nu - r.tg, 0.0);
+            nv += r.tg;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const double2 a = u[q], b = v[q];
+              u[q] = make_double2(fma(r.c, a.x, fma(-r.sr, b.x, r.si * b.y)), fma(r.c, a.y, fma(-r.sr, b.y, -r.si * b.x)));
+              v[q] = make_double2(fma(r.c, b.x, fma(r.sr, a.x, r.si * a.y)), fma(r.c, b.y, fma(r.sr, a.y, -r.si * a.x)));
+            }
+          }
+        };
+        // two disjoint pairs at once
+        auto rotate2 = [&](Column &u0, Column &v0, double &nu0, double &nv0, Column &u1, Column &v1, double &nu1,
+                           double &nv1) {
+          double g[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            g[0] = fma(u0[q].x, v0[q].x, fma(u0[q].y, v0[q].y, g[0]));
+            g[1] = fma(u0[q].x, v0[q].y, fma(-u0[q].y, v0[q].x, g[1]));
+            g[2] = fma(u1[q].x, v1[q].x, fma(u1[q].y, v1[q].y, g[2]));
+            g[3] = fma(u1[q].x, v1[q].y, fma(-u1[q].y, v1[q].x, g[3]));
+          }
+          wave_sum4(g);
+          rotate(u0, v0, nu0, nv0, g[0], g[1]);
+          rotate(u1, v1, nu1, nv1, g[2], g[3]);
+        };
+        if (rd == 0) rotate2(x[0], x[1], w[0], w[1], y[0], y[1], w[2], w[3]);   // inside the blocks
+        rotate2(x[0], y[0], w[0], w[2], x[1], y[1], w[1], w[3]);
+        rotate2(x[0], y[1], w[0], w[3], x[1], y[0], w[1], w[2]);
+        if (moved) {
+#pragma unroll
+          for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              if (i < blocks) X[c * kWideN + 64 * q] = x[c][q];
+              if (j < blocks) Y[c * kWideN + 64 * q] = y[c][q];
+            }
         }
       }
       __syncthreads();  // the next round reads the columns this one wrote
@@ -1593,23 +1642,32 @@ __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, in
     if (right) Ap[(size_t(r / Dp) * Pp + r % Dp) * Pm + j] = make_double2(vr, vi);
     else Aq[(size_t(r / Dn) * Pm + j) * Pn + r % Dn] = make_double2(vr, -vi);
   }
-  // projection: out[j][x] = nrm sum_y conj(U[y][j]) S[y][x]; consecutive
-  // threads take consecutive x (one column of W per wave, coalesced rows of S)
-  for (int e = tid; e < k * ncs; e += kSvThreads) {
-    const int j = e / ncs, x = e % ncs;
-    const int c = w_col[j];
-    const double inv = 1.0 / sqrt(w_norm[c]);
-    const double2 *u = W + size_t(c) * kWideN;
-    double re = 0.0, im = 0.0;
-    for (int y = 0; y < nr; ++y) {
-      const double2 uv = u[y], sv = S[size_t(y) * kWideN + x];
-      const double ur = uv.x * inv, ui = uv.y * inv;
-      re = fma(ur, sv.x, fma(ui, sv.y, re));
-      im = fma(ur, sv.y, fma(-ui, sv.x, im));
+  // projection: out[j][x] = nrm sum_y conj(U[y][j]) S[y][x]
+  for (int x0 = 0; x0 < ncs; x0 += kSvMaxN)
+    for (int j0 = 0; j0 < k; j0 += kSvMaxN / 2) {
+      double2 acc[T::HROWS][2];
+      staged_tile_gemm<kSvMaxN, kSvWaves, T::HROWS>(
+          nr,
+          [&](int jj, int y) {
+            if (j0 + jj >= k) return make_double2(0.0, 0.0);
+            const int c = w_col[j0 + jj];
+            const double inv = rsqrt(w_norm[c]);
+            const double2 u = W[c * kWideN + y];
+            return make_double2(inv * u.x, -inv * u.y);
+          },
+          [&](int y, int x) { return x0 + x < ncs ? S[y * kWideN + x0 + x] : make_double2(0.0, 0.0); }, sh, acc);
+#pragma unroll
+      for (int rr = 0; rr < T::HROWS; ++rr)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int j = j0 + wave * T::HROWS + rr, x = x0 + 2 * lane + q;
+          const double2 v = acc[rr][q];
+          if (j < k && x < ncs) {
+            if (right) aq_at(j, x) = make_double2(nrm * v.x, nrm * v.y);
+            else ap_at(x, j) = make_double2(nrm * v.x, -nrm * v.y);
+          }
+        }
     }
-    if (right) Aq[(size_t(x / Dn) * Pm + j) * Pn + x % Dn] = make_double2(nrm * re, nrm * im);
-    else Ap[(size_t(x / Dp) * Pp + x % Dp) * Pm + j] = make_double2(nrm * re, -nrm * im);
-  }
   if (tid == 0) dims[p + 1] = k;
 }
 
