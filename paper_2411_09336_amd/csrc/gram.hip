@@ -596,12 +596,116 @@ __device__ inline void rows_to_regs(f32x4 &v) {
 // fewer MFMAs on the bound resource; FP32 keeps the four products in the
 // order of the kernel for larger bonds, whose results it reproduces bit for
 // bit.
-template <typename T, typename V4, typename T2, int NT>
-__device__ inline void overlap_wave(const GramJobDev &J, int64_t ia, int64_t ib, T &ov_re, T &ov_im, int &ov_exp) {
+template <bool FULL, typename T, typename V4, typename T2, int NT>
+__device__ __forceinline__ uint32_t wave_site(const T2 *A, const T2 *B, const V4 (&E)[NT][NT][2], int pa, int pan, int pb,
+                                              int pbn, int na, int nan, int nb, int nbn, V4 (&En)[NT][NT][2]) {
   constexpr bool k3 = sizeof(T) == 8;
   constexpr int NP = k3 ? 3 : 2;   // accumulators of a complex tile
   const int lane = threadIdx.x & 63;
   const int j = lane & 15, g = lane >> 4;
+  const V4 zero = V4{0, 0, 0, 0};
+  uint32_t mx = 0;
+#pragma unroll
+  for (int ct = 0; ct < NT; ++ct) {
+    V4 P[NT][NP];
+#pragma unroll
+    for (int at = 0; at < NT; ++at)
+#pragma unroll
+      for (int u = 0; u < NP; ++u) P[at][u] = zero;
+    if (FULL || ct < nbn) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        V4 Q[NT][NP];
+#pragma unroll
+        for (int rt = 0; rt < NT; ++rt)
+#pragma unroll
+          for (int u = 0; u < NP; ++u) Q[rt][u] = zero;
+        // GEMM1: T_s[a][b'] = sum_b E[a][b] B_s[b][b']
+#pragma unroll
+        for (int kt = 0; kt < NT; ++kt) {
+          if (FULL || kt < nb) {
+            T2 bv[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) bv[q] = gload_c(B + (s * pb + 16 * kt + 4 * q + g) * pbn + 16 * ct + j);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+#pragma unroll
+              for (int rt = 0; rt < NT; ++rt) {
+                if (FULL || rt < na) {
+                  const T er = E[rt][kt][0][q], ei = E[rt][kt][1][q];
+                  if constexpr (k3) {
+                    Q[rt][0] = mma(er, bv[q].x, Q[rt][0]);
+                    Q[rt][1] = mma(ei, bv[q].y, Q[rt][1]);
+                    Q[rt][NP - 1] = mma(er + ei, bv[q].x + bv[q].y, Q[rt][NP - 1]);
+                  } else {
+                    Q[rt][0] = mma(er, bv[q].x, Q[rt][0]);
+                    Q[rt][0] = mma(ei, -bv[q].y, Q[rt][0]);
+                    Q[rt][1] = mma(er, bv[q].y, Q[rt][1]);
+                    Q[rt][1] = mma(ei, bv[q].x, Q[rt][1]);
+                  }
+                }
+              }
+            }
+          }
+        }
+        // GEMM2: E'^T[b'][a'] += sum_a T_s[a][b'] conj(A_s[a][a'])
+#pragma unroll
+        for (int rt = 0; rt < NT; ++rt) {
+          if (FULL || rt < na) {
+#pragma unroll
+            for (int at = 0; at < NT; ++at) {
+              if (FULL || at < nan) {
+                T2 av[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                  av[e] = gload_c(A + (s * pa + 16 * rt + acc_row<T>(g, e)) * pan + 16 * at + j);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  if constexpr (k3) {
+                    const T tr = Q[rt][0][e] - Q[rt][1][e];
+                    const T ti = Q[rt][NP - 1][e] - Q[rt][0][e] - Q[rt][1][e];
+                    // re = Tr Ar + Ti Ai; im = (Tr + Ti)(Ar - Ai) - Tr Ar + Ti Ai
+                    P[at][0] = mma(tr, av[e].x, P[at][0]);
+                    P[at][1] = mma(ti, av[e].y, P[at][1]);
+                    P[at][NP - 1] = mma(tr + ti, av[e].x - av[e].y, P[at][NP - 1]);
+                  } else {
+                    const T tr = Q[rt][0][e], ti = Q[rt][1][e];
+                    P[at][0] = mma(tr, av[e].x, P[at][0]);
+                    P[at][0] = mma(ti, av[e].y, P[at][0]);
+                    P[at][1] = mma(ti, av[e].x, P[at][1]);
+                    P[at][1] = mma(-tr, av[e].y, P[at][1]);
+                  }
+                }
+              }
+            }
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int at = 0; at < NT; ++at) {
+      if constexpr (k3) {
+        En[ct][at][0] = P[at][0] + P[at][1];
+        En[ct][at][1] = P[at][NP - 1] - P[at][0] + P[at][1];
+      } else {
+        En[ct][at][0] = P[at][0];
+        En[ct][at][1] = P[at][1];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t x = mag_bits(En[ct][at][0][e]), y = mag_bits(En[ct][at][1][e]);
+        mx = mx > x ? mx : x;
+        mx = mx > y ? mx : y;
+      }
+    }
+  }
+  return mx;
+}
+
+template <typename T, typename V4, typename T2, int NT>
+__device__ inline void overlap_wave(const GramJobDev &J, int64_t ia, int64_t ib, T &ov_re, T &ov_im, int &ov_exp) {
+  constexpr bool k3 = sizeof(T) == 8;
+  const int lane = threadIdx.x & 63;
   const T2 *A = reinterpret_cast<const T2 *>(J.a_base) + ia * J.a_stride;
   const T2 *B = reinterpret_cast<const T2 *>(J.b_base) + ib * J.b_stride;
   const auto apad = gview(J.a_pad), bpad = gview(J.b_pad), abond = gview(J.a_bond), bbond = gview(J.b_bond);
@@ -619,101 +723,18 @@ __device__ inline void overlap_wave(const GramJobDev &J, int64_t ia, int64_t ib,
     const int pan = apad[l + 1], pbn = bpad[l + 1];
     const int nan = NT == 1 ? 1 : (abond[l + 1] + 15) >> 4, nbn = NT == 1 ? 1 : (bbond[l + 1] + 15) >> 4;
     V4 En[NT][NT][2];   // E'^T: [ket column block][bra column block]
-    uint32_t mx = 0;
-#pragma unroll
-    for (int ct = 0; ct < NT; ++ct) {
-      V4 P[NT][NP];
-#pragma unroll
-      for (int at = 0; at < NT; ++at)
-#pragma unroll
-        for (int u = 0; u < NP; ++u) P[at][u] = zero;
-      if (ct < nbn) {
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          V4 Q[NT][NP];
-#pragma unroll
-          for (int rt = 0; rt < NT; ++rt)
-#pragma unroll
-            for (int u = 0; u < NP; ++u) Q[rt][u] = zero;
-          // GEMM1: T_s[a][b'] = sum_b E[a][b] B_s[b][b']
-#pragma unroll
-          for (int kt = 0; kt < NT; ++kt) {
-            if (kt < nb) {
-              T2 bv[4];
-#pragma unroll
-              for (int q = 0; q < 4; ++q) bv[q] = gload_c(B + (s * pb + 16 * kt + 4 * q + g) * pbn + 16 * ct + j);
-#pragma unroll
-              for (int q = 0; q < 4; ++q) {
-#pragma unroll
-                for (int rt = 0; rt < NT; ++rt) {
-                  if (rt < na) {
-                    const T er = E[rt][kt][0][q], ei = E[rt][kt][1][q];
-                    if constexpr (k3) {
-                      Q[rt][0] = mma(er, bv[q].x, Q[rt][0]);
-                      Q[rt][1] = mma(ei, bv[q].y, Q[rt][1]);
-                      Q[rt][NP - 1] = mma(er + ei, bv[q].x + bv[q].y, Q[rt][NP - 1]);
-                    } else {
-                      Q[rt][0] = mma(er, bv[q].x, Q[rt][0]);
-                      Q[rt][0] = mma(ei, -bv[q].y, Q[rt][0]);
-                      Q[rt][1] = mma(er, bv[q].y, Q[rt][1]);
-                      Q[rt][1] = mma(ei, bv[q].x, Q[rt][1]);
-                    }
-                  }
-                }
-              }
-            }
-          }
-          // GEMM2: E'^T[b'][a'] += sum_a T_s[a][b'] conj(A_s[a][a'])
-#pragma unroll
-          for (int rt = 0; rt < NT; ++rt) {
-            if (rt < na) {
-#pragma unroll
-              for (int at = 0; at < NT; ++at) {
-                if (at < nan) {
-                  T2 av[4];
-#pragma unroll
-                  for (int e = 0; e < 4; ++e)
-                    av[e] = gload_c(A + (s * pa + 16 * rt + acc_row<T>(g, e)) * pan + 16 * at + j);
-#pragma unroll
-                  for (int e = 0; e < 4; ++e) {
-                    if constexpr (k3) {
-                      const T tr = Q[rt][0][e] - Q[rt][1][e];
-                      const T ti = Q[rt][NP - 1][e] - Q[rt][0][e] - Q[rt][1][e];
-                      // re = Tr Ar + Ti Ai; im = (Tr + Ti)(Ar - Ai) - Tr Ar + Ti Ai
-                      P[at][0] = mma(tr, av[e].x, P[at][0]);
-                      P[at][1] = mma(ti, av[e].y, P[at][1]);
-                      P[at][NP - 1] = mma(tr + ti, av[e].x - av[e].y, P[at][NP - 1]);
-                    } else {
-                      const T tr = Q[rt][0][e], ti = Q[rt][1][e];
-                      P[at][0] = mma(tr, av[e].x, P[at][0]);
-                      P[at][0] = mma(ti, av[e].y, P[at][0]);
-                      P[at][1] = mma(ti, av[e].x, P[at][1]);
-                      P[at][1] = mma(-tr, av[e].y, P[at][1]);
-                    }
-                  }
-                }
-              }
-            }
-          }
-        }
-      }
-#pragma unroll
-      for (int at = 0; at < NT; ++at) {
-        if constexpr (k3) {
-          En[ct][at][0] = P[at][0] + P[at][1];
-          En[ct][at][1] = P[at][NP - 1] - P[at][0] + P[at][1];
-        } else {
-          En[ct][at][0] = P[at][0];
-          En[ct][at][1] = P[at][1];
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t x = mag_bits(En[ct][at][0][e]), y = mag_bits(En[ct][at][1][e]);
-          mx = mx > x ? mx : x;
-          mx = mx > y ? mx : y;
-        }
-      }
-    }
+    // FP32: where every block is filled, one body without branches, whose loads
+    // the compiler moves far ahead of their MFMAs (194 registers, two waves per
+    // SIMD).  With a load's wait in front of every eight MFMAs, four waves per
+    // SIMD kept the matrix cores 53 % busy: 12,880 pairs of 50 sites, chi 32,
+    // 6.79 -> 5.19 ms (81 -> 106 TFLOP/s; a large FP32 product reaches 143), and
+    // spilling at four waves 6.3.  FP64 (72 % busy) needs all its registers for
+    // the accumulators of three products: the same body spills (7.5 -> 13.9 ms).
+    uint32_t mx;
+    if (!k3 && NT > 1 && na == NT && nb == NT && nan == NT && nbn == NT)
+      mx = wave_site<!k3, T, V4, T2, NT>(A, B, E, pa, pan, pb, pbn, na, nan, nb, nbn, En);
+    else
+      mx = wave_site<false, T, V4, T2, NT>(A, B, E, pa, pan, pb, pbn, na, nan, nb, nbn, En);
     // rescale by a power of two (exact) and turn E'^T into the next E
     const int e2 = exp_of_bits(wave_max_bits(mx), T(0));
     const T scale = ldexp(T(1), -e2);
@@ -1939,7 +1960,7 @@ __device__ inline void overlap_split_wave(const GramJobDev &J, int64_t ia, int64
 // neighbouring columns of one row at bonds up to 4) from the atomic queue;
 // the next unit's index is fetched while the current one is contracted.
 template <int PREC, int NT>
-__global__ __launch_bounds__(64, NT == 2 && PREC != QK_FP32 ? 2 : PREC == QK_SPLIT_BF16 || PREC == QK_SPLIT_I8 ? 3 : 4) void gram_wave_kernel(const GramJobDev *__restrict__ jobs,
+__global__ __launch_bounds__(64, NT == 2 ? 2 : PREC == QK_SPLIT_BF16 || PREC == QK_SPLIT_I8 ? 3 : 4) void gram_wave_kernel(const GramJobDev *__restrict__ jobs,
                                                                          const GramTile *__restrict__ tiles,
                                                                          int64_t n_units, int th, int tw,
                                                                          unsigned long long *counter) {
@@ -2176,7 +2197,7 @@ qk_status noalloc_scratch(void **ptr) {
 // MFMAs on zeros and, with one pair per workgroup, most of its time in
 // barriers and idle waves.  One row of 1,000 165-site pairs at bond 2:
 // 9.34 ms with the workgroup kernel, 0.39 ms at four pairs per wave; 12,880
-// 50-site FP32 pairs at bond 32: 15.5 ms against 7.2 ms at one pair per wave
+// 50-site FP32 pairs at bond 32: 15.5 ms against 5.2 ms at one pair per wave
 // (both whole calls).  At three tiles of 16 the FP64 operands leave no
 // registers for a second wave per SIMD, so larger bonds take a workgroup.
 enum GramKernel { KERNEL_QUAD = 0, KERNEL_WAVE16, KERNEL_WAVE32, KERNEL_BLOCK, KERNEL_WIDE, KERNEL_KINDS };

@@ -162,3 +162,10 @@ def test_steps_next_to_bonds_above_64(m, d, chi, routing):
             assert list(dims[i]) == r.bond_dims
             assert fidelity(b.export(i), r.tensors) > 1 - 1e-10
             assert abs(disc[i] - r.discarded) <= 1e-9 * max(1.0, r.discarded)
+
+
+@pytest.mark.parametrize("chi", [65, 67, 127])
+def test_odd_numbers_of_column_blocks(chi):
+    """Both neighbouring bonds above 64: 65, 67 and 127 blocks of two columns
+    (one block of a round has no partner)."""
+    test_steps_next_to_bonds_above_64(16, 6, chi, 0)
