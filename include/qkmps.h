@@ -227,9 +227,10 @@ qk_status mps_simulate_trace(const double *features_dev, int64_t n_points,
  * hip_stream and before later work on it.  0 picks equal chunks of at most
  * QK_GRAPH_CIRCUITS circuits.  Each circuit goes through the same steps with
  * the same kernels as in mps_simulate, so the batch is bit-identical; the
- * SVD scratch is sized for one chunk (512 KiB per circuit, plus 2 MiB for
- * chi_max above 64) instead of the whole batch, and the host launch work is that of one chunk whatever the
- * batch size.  QK_EINVAL if circuits_per_graph < 0; QK_EDEVICE if capture,
+ * SVD scratch is sized for one chunk instead of the whole batch (per
+ * circuit: none where the bonds it can reach stay up to 16, 64 KiB up to 32,
+ * 256 KiB above, plus 2.5 MiB where bonds above 64 can be reached), and the
+ * host launch work is that of one chunk whatever the batch size.  QK_EINVAL if circuits_per_graph < 0; QK_EDEVICE if capture,
  * instantiation or a replay fails.  The call returns after the simulation
  * has finished. */
 #define QK_GRAPH_CIRCUITS 1024
@@ -294,7 +295,9 @@ qk_status mps_gram_block(const qk_mps_batch *a, int64_t a0, int64_t na,
  * before any launch.  QK_EINVAL,
  * before any launch, when the work queue does not fit the array: with the
  * default pair tiles of side 16 that is about 520,000 tiles, e.g. a
- * symmetric Gram of up to ~16,000 MPS.  Every call on a device uses that
+ * symmetric Gram of up to ~16,000 MPS.  A queue of up to 21 KB (a few hundred
+ * tiles) travels in kernel arguments, so the call can be recorded into a HIP
+ * graph; a larger one is copied and waited for.  Every call on a device uses that
  * device's one array: calls that overlap in time on one device (other
  * threads, other streams) race and must be serialised by the caller. */
 #define QK_NOALLOC_SCRATCH_BYTES (8u << 20)
@@ -303,9 +306,9 @@ qk_status mps_gram_block_noalloc(const qk_mps_batch *a, int64_t a0, int64_t na,
                                  int32_t upper_only, qk_precision prec,
                                  double *K_dev, int64_t ldk, void *hip_stream);
 
-/* Several Gram jobs (different batches, qubit counts and pads) in ONE
- * persistent launch: workgroups pop tiles from a device work queue across
- * all jobs.  Each job is as in mps_gram_block with `upper_only` meaning
+/* Several Gram jobs (different batches, qubit counts and pads) in one call:
+ * one persistent launch per kernel that the jobs' bonds need, in which
+ * workgroups pop tiles from a device work queue across its jobs.  Each job is as in mps_gram_block with `upper_only` meaning
  * symmetric. */
 typedef struct {
   const qk_mps_batch *a;
@@ -324,7 +327,7 @@ qk_status mps_gram_multi(const qk_gram_job *jobs, int32_t n_jobs,
 /* Autotuner of the Gram kernels' tile shapes.  For `prec` and the bond-pad
  * bucket of batch `b` (pads <= 32, <= 64 or <= 128), every valid configuration
  * (block size 32 or 64 for the FP64 / FP32 forms when the pads allow, 128
- * above 64, pair-tile
+ * above 64, at bonds up to 32 the same kernel whichever; pair-tile
  * side 8 / 16 / 32, one work queue or one per XCD) computes the symmetric
  * Gram of the first min(sample, n) MPS of `b` (one warm-up run, then the
  * best of two timed runs, wall clock including the launch's host work).

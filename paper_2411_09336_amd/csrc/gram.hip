@@ -1009,7 +1009,7 @@ __device__ inline void slice_mac(const Sl4 &X, const Sl4 &Y, f32x4 &hi, f32x4 &l
 // the bonds at a site (the chain's ends, bonds 33..63) hold zeros and are left
 // out by wave-uniform branches, which cost nothing where every tile is filled.
 // 5,050 pairs of 14 sites, chi 64: 4.13 -> 2.54 ms; 1,830 of 100 sites, chi 45:
-// 12.05 -> 10.38 ms.  At chi 64 the kernel issues 1.38 PFLOP/s of products,
+// 12.05 -> 10.38 ms.  At chi 64 the kernel issues 1.29 PFLOP/s of products,
 // above what a large bf16 matrix product reaches on the card (1.12), so the
 // matrix cores' rate, not the order of the phases, bounds it: slicing in one
 // wave of a SIMD while the other multiplies measured 4 % slower.
