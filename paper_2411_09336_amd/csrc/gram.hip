@@ -105,15 +105,6 @@ __device__ inline uint4 neg_bf16(uint4 v) {
   return make_uint4(v.x ^ 0x80008000u, v.y ^ 0x80008000u, v.z ^ 0x80008000u, v.w ^ 0x80008000u);
 }
 
-__device__ inline float wave_max(float v) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-__device__ inline double wave_max(double v) {
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-  return v;
-}
-
 // Work queues: nq queues, one per XCD (workgroups are dispatched to the
 // XCDs round-robin, so workgroup b runs on XCD b mod 8).  Queue x serves the
 // tiles x, x + nq, x + 2 nq, ... so that the workgroups of one XCD work on

@@ -1072,7 +1072,7 @@ __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t c
   const int tid = W == 1 ? threadIdx.x & 63 : threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: scalar register
   const int cp = lane % LC, row0 = (wave * Y::RG + lane / LC) * ROWS;
-  const int c0 = 2 * cp, c1 = 2 * cp + 1;
+  const int c0 = 2 * cp;
 
   int32_t *dims = P.dims + ci * (P.m + 1);
   const int p = st.p;
