@@ -460,16 +460,20 @@ static qk_status make_job(const qk_mps_batch *a, int64_t a0, int64_t na, const q
     return fail(QK_EINVAL, "unknown precision");
   auto *am = const_cast<qk_mps_batch *>(a);
   auto *bm = const_cast<qk_mps_batch *>(b);
+  auto present = [&](const qk_mps_batch *x) {
+    return prec == QK_FP64 ? x->f64 != nullptr : prec == QK_FP32 ? x->f32 != nullptr
+                                               : prec == QK_SPLIT_BF16 ? x->sbf16 != nullptr : x->si8 != nullptr;
+  };
   if (pack) {
+    const bool packs = !present(a) || !present(b);
     st = batch_ensure_packed(am, prec, stream);
     if (st != QK_OK) return st;
     st = batch_ensure_packed(bm, prec, stream);
     if (st != QK_OK) return st;
+    // planes belong to the batch: the next call may read them on another
+    // stream, which nothing orders after this one
+    if (packs) QK_HIP_CHECK(hipStreamSynchronize(stream));
   } else {
-    auto present = [&](const qk_mps_batch *x) {
-      return prec == QK_FP64 ? x->f64 != nullptr : prec == QK_FP32 ? x->f32 != nullptr
-                                                 : prec == QK_SPLIT_BF16 ? x->sbf16 != nullptr : x->si8 != nullptr;
-    };
     if (!present(a) || !present(b))
       return fail(QK_ENOTSUP, "the precision's packed form is not built: call mps_batch_pack first");
   }
