@@ -267,7 +267,9 @@ typedef struct {
  * support bond pads up to 128 (bond dimensions up to 128; above 64 with E in a global scratch
  * slot of 2 x 128 x 128 complex values per workgroup, drawn from the
  * device's allocator for the call), the split forms up to 64: QK_ENOTSUP
- * for larger batches.  `stats` may be NULL. */
+ * for larger batches.  `stats` may be NULL.  The call draws its work queue
+ * from the allocator, so a stream under capture is refused (QK_EDEVICE, before
+ * any launch): mps_gram_block_noalloc is the form for graphs. */
 qk_status mps_gram(const qk_mps_batch *a, const qk_mps_batch *b,
                    qk_precision prec, double *K_dev, int64_t ldk,
                    void *hip_stream, qk_gram_stats *stats);

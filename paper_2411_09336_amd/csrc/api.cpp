@@ -446,6 +446,18 @@ static int max_bond_of(const qk_mps_batch *x) {
   return *std::max_element(x->bond.begin(), x->bond.end());
 }
 
+// Calls that draw memory from the allocator for their own duration cannot be
+// recorded into a graph: a replay would use memory that has gone back.
+static qk_status refuse_capture(hipStream_t stream) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return QK_OK;
+  }
+  if (cs == hipStreamCaptureStatusNone) return QK_OK;
+  return fail(QK_EDEVICE, "the stream is under capture: only mps_gram_block_noalloc can be recorded");
+}
+
 static qk_status make_job(const qk_mps_batch *a, int64_t a0, int64_t na, const qk_mps_batch *b,
                           int64_t b0, int64_t nb, int32_t upper, double *K, int64_t ldk,
                           qk_precision prec, hipStream_t stream, GramJobDev *job, bool pack = true) {
@@ -465,6 +477,8 @@ static qk_status make_job(const qk_mps_batch *a, int64_t a0, int64_t na, const q
                                                : prec == QK_SPLIT_BF16 ? x->sbf16 != nullptr : x->si8 != nullptr;
   };
   if (pack) {
+    if (na > 0 && nb > 0) st = refuse_capture(stream);
+    if (st != QK_OK) return st;
     const bool packs = !present(a) || !present(b);
     st = batch_ensure_packed(am, prec, stream);
     if (st != QK_OK) return st;
@@ -628,11 +642,13 @@ qk_status mps_gram_autotune(qk_mps_batch *b, qk_precision prec, int64_t sample, 
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
   const int64_t n = std::min<int64_t>(sample, b->n);
   if (n < 1) return fail(QK_EINVAL, "empty batch");
+  qk_status st = refuse_capture(stream);
+  if (st != QK_OK) return st;
   const DevAlloc al = allocator_for_current_device();
   auto *K = static_cast<double *>(dev_alloc(al, sizeof(double) * size_t(n) * size_t(n), stream, true));
   if (!K) return fail(QK_ENOMEM, "device allocation of the autotuning Gram failed");
   GramJobDev job;
-  qk_status st = make_job(b, 0, n, b, 0, n, 1, K, n, prec, stream, &job);
+  st = make_job(b, 0, n, b, 0, n, 1, K, n, prec, stream, &job);
   const int max_pad = max_pad_of(b);
   std::vector<GramJobDev> jobs{job};
   auto run_ms = [&](const GramConfig &c, double &ms) -> qk_status {

@@ -35,3 +35,33 @@ def test_first_use_packs_for_every_stream(prec):
     torch.cuda.synchronize()
     assert torch.equal(other, ref)
     assert torch.equal(first, ref)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "split_i8"])
+def test_allocating_calls_are_refused_under_capture(prec):
+    """Calls that draw their work queue (and planes) from the allocator cannot
+    be recorded: a replay would use memory that has gone back to it.  They say
+    so before any launch, so the capture and the batch stay usable."""
+    import paper_2411_09336_amd as q
+    torch = require_gpu()
+    ref = q.gram(_batch(6, 8, 12, 2), precision=prec)
+    b = _batch(6, 8, 12, 2)
+    out = torch.zeros((6, 6), dtype=torch.float64, device="cuda")
+    flag = torch.zeros(1, device="cuda")
+    job = dict(a=b, b=b, na=6, nb=6, upper_only=True, out=out)
+    calls = [lambda: q.gram(b, precision=prec, out=out),
+             lambda: q.gram_block(b, 0, 2, b, 1, 3, precision=prec, out=out[:2, :3]),
+             lambda: q.gram_multi([job], precision=prec),
+             lambda: q.autotune(b, prec, sample=4)]
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        flag.add_(1.0)
+        for call in calls:
+            with pytest.raises(q.QKError) as e:
+                call()
+            assert "capture" in str(e.value)
+    g.replay()
+    torch.cuda.synchronize()
+    assert flag.item() == 1.0 and not out.any()
+    assert torch.equal(q.gram(b, precision=prec), ref)
