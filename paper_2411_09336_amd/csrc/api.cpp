@@ -521,8 +521,6 @@ static qk_status make_job(const qk_mps_batch *a, int64_t a0, int64_t na, const q
   job->ldk = ldk;
   job->m = a->m;
   job->upper = upper ? 1 : 0;
-  job->tiles_i = 0;
-  job->tiles_j = 0;
   job->a_bond = am->bond_dev;
   job->b_bond = bm->bond_dev;
   job->max_bond = std::max(max_bond_of(am), max_bond_of(bm));

@@ -2250,7 +2250,7 @@ qk_status upload(void *dst, const void *src, size_t bytes, hipStream_t stream) {
   return QK_OK;
 }
 
-qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs_in, int max_pad, qk_precision prec,
+qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs, int max_pad, qk_precision prec,
                           const GramConfig &cfg, hipStream_t stream, qk_gram_stats *stats, void *ws_given,
                           size_t ws_cap) {
   if (max_pad > kWideP) return fail(QK_ENOTSUP, "Gram kernels support bond pads up to 128");
@@ -2260,7 +2260,6 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs_in, int max_pad, q
     return fail(QK_ENOTSUP, "the allocation-free Gram supports bond pads up to 64");
   if (cfg.maxp < max_pad) return fail(QK_EINVAL, "tile configuration smaller than the batch's bond pads");
   const int side = cfg.tile_side;
-  std::vector<GramJobDev> jobs = jobs_in;
   // One launch per kernel kind that the jobs need: a pair's bits then do not
   // depend on the jobs it is launched with.  Tiles hold side * side entries;
   // a kind whose jobs have fewer than `side` rows takes flatter, wider ones.
@@ -2268,7 +2267,9 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs_in, int max_pad, q
     size_t tile0 = 0;
     int64_t n_tiles = 0;
     int th = 0, tw = 0;
+    size_t counters = 0;   // index of the part's block of counters
   } parts[KERNEL_KINDS];
+  size_t n_parts = 0;
   std::vector<GramTile> tiles;
   for (int kind = 0; kind < KERNEL_KINDS; ++kind) {
     Part &pt = parts[kind];
@@ -2280,12 +2281,11 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs_in, int max_pad, q
     pt.tw = side * side / pt.th;
     pt.tile0 = tiles.size();
     for (size_t k = 0; k < jobs.size(); ++k) {
-      GramJobDev &J = jobs[k];
+      const GramJobDev &J = jobs[k];
       if (kernel_of(J, prec) != kind) continue;
-      J.tiles_i = (J.na + pt.th - 1) / pt.th;
-      J.tiles_j = (J.nb + pt.tw - 1) / pt.tw;
-      for (int64_t ti = 0; ti < J.tiles_i; ++ti)
-        for (int64_t tj = 0; tj < J.tiles_j; ++tj) {
+      const int64_t tiles_i = (J.na + pt.th - 1) / pt.th, tiles_j = (J.nb + pt.tw - 1) / pt.tw;
+      for (int64_t ti = 0; ti < tiles_i; ++ti)
+        for (int64_t tj = 0; tj < tiles_j; ++tj) {
           if (J.upper) {
             // skip tiles entirely below the global diagonal
             const int64_t max_col = J.b0 + std::min(J.nb, (tj + 1) * pt.tw) - 1;
@@ -2296,6 +2296,7 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs_in, int max_pad, q
         }
     }
     pt.n_tiles = int64_t(tiles.size() - pt.tile0);
+    if (pt.n_tiles > 0) pt.counters = n_parts++;
   }
   if (stats) {
     stats->tiles = int64_t(tiles.size());
@@ -2309,10 +2310,10 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs_in, int max_pad, q
   const int64_t n_tiles = int64_t(tiles.size());
   const size_t jbytes = sizeof(GramJobDev) * jobs.size();
   const size_t tbytes = sizeof(GramTile) * tiles.size();
-  // workspace: [queue counters of every kind | job table | tile list],
+  // workspace: [queue counters of the kinds in use | job table | tile list],
   // uploaded as one block whose counter bytes are zero (no memset node in the
   // stream)
-  const size_t cbytes = kGramCounterBytes * KERNEL_KINDS;
+  const size_t cbytes = kGramCounterBytes * n_parts;
   const size_t ws_bytes = cbytes + jbytes + tbytes;
   if (ws_given && ws_bytes > ws_cap)
     return fail(QK_EINVAL, "the Gram work queue needs " + std::to_string(ws_bytes) + " bytes (" +
@@ -2338,7 +2339,7 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs_in, int max_pad, q
   for (int kind = 0; kind < KERNEL_KINDS && st == QK_OK; ++kind) {
     const Part &pt = parts[kind];
     if (pt.n_tiles == 0) continue;
-    auto *counters = reinterpret_cast<unsigned long long *>(ws + kGramCounterBytes * kind);
+    auto *counters = reinterpret_cast<unsigned long long *>(ws + kGramCounterBytes * pt.counters);
     auto *tiles_dev = reinterpret_cast<GramTile *>(ws + cbytes + jbytes) + pt.tile0;
     int wgs = 0;
     auto wave = [&](auto launch) { return launch(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.th, pt.tw, stream, &wgs); };

@@ -171,7 +171,6 @@ struct GramJobDev {
   const int32_t *a_bond;           // m + 1: largest bond of batch a at each cut
   const int32_t *b_bond;
   int32_t max_bond, max_pad;       // over both batches
-  int64_t tiles_i, tiles_j;        // tile grid of this job
 };
 
 // Gram kernel configuration: block size of the plain forms (32, 64 or 128), pair

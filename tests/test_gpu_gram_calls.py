@@ -65,3 +65,19 @@ def test_allocating_calls_are_refused_under_capture(prec):
     torch.cuda.synchronize()
     assert flag.item() == 1.0 and not out.any()
     assert torch.equal(q.gram(b, precision=prec), ref)
+
+
+def test_largest_allocation_free_queue():
+    """724 x 724 pair tiles of side 16: 8,386,816 bytes of tiles, to which the
+    counters and the job of one kernel add 656, in the 8,388,608 of the
+    allocation-free scratch."""
+    import paper_2411_09336_amd as q
+    torch = require_gpu()
+    x = torch.tensor([[0.3], [0.9], [0.1]], dtype=torch.float64, device="cuda")
+    few = q.simulate(x, q.CircuitSpec(1, 1, 2), 2, 0.0)
+    n = 16 * 724
+    idx = torch.arange(n, device="cuda") % 3
+    b = few.gather(idx.cpu().numpy())
+    out = torch.zeros((n, n), dtype=torch.float64, device="cuda")
+    q.gram_block_noalloc(b, 0, n, b, 0, n, out)
+    assert torch.equal(out, q.gram_block(few, 0, 3, few, 0, 3)[idx][:, idx])
