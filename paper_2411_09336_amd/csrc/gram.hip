@@ -2061,6 +2061,12 @@ size_t lds_bytes() {
   return size_t(2) * kI8BufBytes;                                  // two int8 operand buffers
 }
 
+// Fewer tiles than queues take one queue, as some queues (and their
+// workgroups) would have none: split-int8, 64 pairs of 60 sites at bond 64 in
+// one tile, 1.17 ms with eight queues and 0.58 with one.  There are at least as
+// many workgroups as tiles, so every queue has some.
+int queues_of(const GramConfig &cfg, int64_t n_tiles) { return n_tiles < cfg.queues ? 1 : cfg.queues; }
+
 template <int PREC, int MAXP>
 qk_status launch_one(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int64_t n_tiles,
                      unsigned long long *counters, const GramConfig &cfg, int th, int tw, hipStream_t stream,
@@ -2077,8 +2083,7 @@ qk_status launch_one(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int6
   per_cu = std::max(per_cu, 1);
   int64_t grid = int64_t(cus) * per_cu;
   grid = std::min<int64_t>(grid, std::max<int64_t>(n_tiles * th * tw, 1));
-  // every queue needs workgroups: at most one queue per workgroup
-  const int nq = int(std::min<int64_t>(cfg.queues, grid));
+  const int nq = queues_of(cfg, n_tiles);
   hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(threads_of<PREC>()), lds, stream, jobs_dev, tiles_dev,
                      n_tiles, nq, th, tw, counters);
   QK_HIP_CHECK(hipGetLastError());
@@ -2135,7 +2140,7 @@ qk_status launch_wide(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int
   per_cu = std::max(per_cu, 1);
   int64_t grid = int64_t(cus) * per_cu;
   grid = std::min<int64_t>(grid, std::max<int64_t>(n_tiles * th * tw, 1));
-  const int nq = int(std::min<int64_t>(cfg.queues, grid));
+  const int nq = queues_of(cfg, n_tiles);
   // one E / E' slot per workgroup
   const size_t slot = (PREC == QK_FP64 ? sizeof(double2) : sizeof(float2)) * kWideSlot;
   uint8_t *es = static_cast<uint8_t *>(dev_alloc(al, slot * size_t(grid), stream, true));
@@ -2262,7 +2267,11 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs, int max_pad, qk_p
   const int side = cfg.tile_side;
   // One launch per kernel kind that the jobs need: a pair's bits then do not
   // depend on the jobs it is launched with.  Tiles hold side * side entries;
-  // a kind whose jobs have fewer than `side` rows takes flatter, wider ones.
+  // a kind whose jobs have fewer than `side` rows takes flatter ones, and
+  // wider ones where one queue serves them all.  With a queue per XCD a wide
+  // tile would leave a row's pairs to a few of the queues (split-int8, 1 x 256
+  // pairs of 60 sites at bond 64: 4.87 ms as one tile of 1 x 256, 0.62 as 16
+  // of 1 x 16).
   struct Part {
     size_t tile0 = 0;
     int64_t n_tiles = 0;
@@ -2278,7 +2287,7 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs, int max_pad, qk_p
       if (kernel_of(J, prec) == kind) rows = std::max(rows, J.na);
     pt.th = side;
     while (pt.th > 1 && pt.th / 2 >= rows) pt.th /= 2;
-    pt.tw = side * side / pt.th;
+    pt.tw = cfg.queues > 1 && (kind == KERNEL_BLOCK || kind == KERNEL_WIDE) ? side : side * side / pt.th;
     pt.tile0 = tiles.size();
     for (size_t k = 0; k < jobs.size(); ++k) {
       const GramJobDev &J = jobs[k];

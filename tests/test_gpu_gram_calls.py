@@ -81,3 +81,20 @@ def test_largest_allocation_free_queue():
     out = torch.zeros((n, n), dtype=torch.float64, device="cuda")
     q.gram_block_noalloc(b, 0, n, b, 0, n, out)
     assert torch.equal(out, q.gram_block(few, 0, 3, few, 0, 3)[idx][:, idx])
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 256), (1, 500), (3, 200), (5, 37), (8, 8), (1, 3), (9, 130)])
+@pytest.mark.parametrize("bond", [33, 64])
+def test_rows_over_the_queues(bond, rows, cols):
+    """Few rows with a queue per XCD (split-int8): the pairs lie in tiles of
+    at most 16 columns, so that every queue has its share."""
+    import paper_2411_09336_amd as q
+    torch = require_gpu()
+    few = _batch(3, 13, bond, 3)
+    few.pack("split_i8")
+    i, j = torch.arange(rows) % 3, torch.arange(cols) % 3
+    a, b = few.gather(i.numpy(), ("split_i8",)), few.gather(j.numpy(), ("split_i8",))
+    st = {}
+    K = q.gram(a, b, precision="split_i8", stats=st)
+    assert st["tiles"] == -(-rows // 16) * -(-cols // 16) and st["entries"] == rows * cols
+    assert torch.equal(K.cpu(), q.gram_block(few, 0, 3, few, 0, 3, precision="split_i8").cpu()[i][:, j])
