@@ -310,9 +310,10 @@ qk_status mps_gram_block_noalloc(const qk_mps_batch *a, int64_t a0, int64_t na,
                                  double *K_dev, int64_t ldk, void *hip_stream);
 
 /* Several Gram jobs (different batches, qubit counts and pads) in one call:
- * one persistent launch per kernel that the jobs' bonds need, in which
- * workgroups pop tiles from a device work queue across its jobs.  Each job is as in mps_gram_block with `upper_only` meaning
- * symmetric. */
+ * one persistent launch per kernel that the jobs' bonds need (one launch for
+ * all where the split forms have few pairs), in which workgroups pop tiles
+ * from a device work queue across its jobs.  Each job is as in mps_gram_block
+ * with `upper_only` meaning symmetric. */
 typedef struct {
   const qk_mps_batch *a;
   const qk_mps_batch *b;   /* == a with upper_only != 0 for symmetric jobs */

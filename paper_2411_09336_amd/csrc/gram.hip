@@ -2067,24 +2067,32 @@ size_t lds_bytes() {
 // many workgroups as tiles, so every queue has some.
 int queues_of(const GramConfig &cfg, int64_t n_tiles) { return n_tiles < cfg.queues ? 1 : cfg.queues; }
 
+// Workgroups of the kernel for bonds up to 64 that the device holds at once.
 template <int PREC, int MAXP>
-qk_status launch_one(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int64_t n_tiles,
-                     unsigned long long *counters, const GramConfig &cfg, int th, int tw, hipStream_t stream,
-                     int *grid_out) {
-  int dev = 0, cus = 256;
+qk_status block_residents(int64_t *n) {
+  int dev = 0, cus = 256, per_cu = 0;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   const size_t lds = lds_bytes<PREC, MAXP>();
   auto kern = gram_kernel<PREC, MAXP>;
   QK_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
-  int per_cu = 0;
   QK_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads_of<PREC>(), lds));
-  per_cu = std::max(per_cu, 1);
-  int64_t grid = int64_t(cus) * per_cu;
+  *n = int64_t(cus) * std::max(per_cu, 1);
+  return QK_OK;
+}
+
+template <int PREC, int MAXP>
+qk_status launch_one(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int64_t n_tiles,
+                     unsigned long long *counters, const GramConfig &cfg, int th, int tw, hipStream_t stream,
+                     int *grid_out) {
+  int64_t grid = 0;
+  const qk_status st = block_residents<PREC, MAXP>(&grid);
+  if (st != QK_OK) return st;
   grid = std::min<int64_t>(grid, std::max<int64_t>(n_tiles * th * tw, 1));
   const int nq = queues_of(cfg, n_tiles);
-  hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(threads_of<PREC>()), lds, stream, jobs_dev, tiles_dev,
+  hipLaunchKernelGGL((gram_kernel<PREC, MAXP>), dim3(unsigned(grid)), dim3(threads_of<PREC>()),
+                     (lds_bytes<PREC, MAXP>()), stream, jobs_dev, tiles_dev,
                      n_tiles, nq, th, tw, counters);
   QK_HIP_CHECK(hipGetLastError());
   *grid_out = int(grid);
@@ -2204,6 +2212,40 @@ static int kernel_of(const GramJobDev &J, qk_precision prec) {
   return J.max_pad <= 64 ? KERNEL_BLOCK : KERNEL_WIDE;
 }
 
+// Pairs of a job, counted up to about `most`.
+static int64_t pairs_of(const GramJobDev &J, int64_t most) {
+  if (!J.upper || J.na >= 2 * most || J.nb >= 2 * most) return J.na * J.nb;
+  int64_t n = 0;
+  for (int64_t i = 0; i < J.na && n <= most; ++i)   // columns b0 + j >= a0 + i
+    n += std::max<int64_t>(0, J.nb - std::max<int64_t>(0, J.a0 + i - J.b0));
+  return n;
+}
+
+// Kernels of a call's jobs.  In the split forms, whose bits are the same in
+// every kernel, a call with no more pairs than the workgroup kernel holds at
+// once takes that kernel for all of them if it must for some (bonds above
+// 32), or if that is the faster one for a single pair (split-int8 from bond
+// 17: four waves share a pair's slicing): all pairs then run side by side,
+// where a launch per kernel adds up their times.  60 sites: split-int8 at
+// bond 32, 1 and 250 pairs: 0.74 and 0.83 ms with a wave each, 0.41 and 0.44
+// with a workgroup; 20 pairs at bonds 32 and 64 in one call: split-int8 1.29 ->
+// 0.59 ms, split-BF16 1.46 -> 0.84.
+static qk_status kernels_of(const std::vector<GramJobDev> &jobs, qk_precision prec, std::vector<int> *kinds) {
+  kinds->clear();
+  for (const GramJobDev &J : jobs) kinds->push_back(kernel_of(J, prec));
+  if (prec != QK_SPLIT_BF16 && prec != QK_SPLIT_I8) return QK_OK;
+  const int from = prec == QK_SPLIT_I8 ? KERNEL_WAVE32 : KERNEL_BLOCK;
+  const auto [least, most] = std::minmax_element(kinds->begin(), kinds->end());
+  if (jobs.empty() || *most < from || *least == KERNEL_BLOCK) return QK_OK;
+  int64_t residents = 0, pairs = 0;
+  const qk_status st = prec == QK_SPLIT_I8 ? block_residents<QK_SPLIT_I8, 64>(&residents)
+                                           : block_residents<QK_SPLIT_BF16, 64>(&residents);
+  if (st != QK_OK) return st;
+  for (size_t k = 0; k < jobs.size() && pairs <= residents; ++k) pairs += pairs_of(jobs[k], residents);
+  if (pairs <= residents) std::fill(kinds->begin(), kinds->end(), int(KERNEL_BLOCK));
+  return QK_OK;
+}
+
 template <int PREC, int NT>
 static qk_status launch_wave(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int64_t n_tiles,
                              unsigned long long *counters, int th, int tw, hipStream_t stream, int *grid_out) {
@@ -2265,7 +2307,10 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs, int max_pad, qk_p
     return fail(QK_ENOTSUP, "the allocation-free Gram supports bond pads up to 64");
   if (cfg.maxp < max_pad) return fail(QK_EINVAL, "tile configuration smaller than the batch's bond pads");
   const int side = cfg.tile_side;
-  // One launch per kernel kind that the jobs need: a pair's bits then do not
+  std::vector<int> kinds;
+  const qk_status ks = kernels_of(jobs, prec, &kinds);
+  if (ks != QK_OK) return ks;
+  // One launch per kernel kind that the jobs need: a pair's bits do not
   // depend on the jobs it is launched with.  Tiles hold side * side entries;
   // a kind whose jobs have fewer than `side` rows takes flatter ones, and
   // wider ones where one queue serves them all.  With a queue per XCD a wide
@@ -2283,15 +2328,15 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs, int max_pad, qk_p
   for (int kind = 0; kind < KERNEL_KINDS; ++kind) {
     Part &pt = parts[kind];
     int64_t rows = 0;
-    for (const GramJobDev &J : jobs)
-      if (kernel_of(J, prec) == kind) rows = std::max(rows, J.na);
+    for (size_t k = 0; k < jobs.size(); ++k)
+      if (kinds[k] == kind) rows = std::max(rows, jobs[k].na);
     pt.th = side;
     while (pt.th > 1 && pt.th / 2 >= rows) pt.th /= 2;
     pt.tw = cfg.queues > 1 && (kind == KERNEL_BLOCK || kind == KERNEL_WIDE) ? side : side * side / pt.th;
     pt.tile0 = tiles.size();
     for (size_t k = 0; k < jobs.size(); ++k) {
       const GramJobDev &J = jobs[k];
-      if (kernel_of(J, prec) != kind) continue;
+      if (kinds[k] != kind) continue;
       const int64_t tiles_i = (J.na + pt.th - 1) / pt.th, tiles_j = (J.nb + pt.tw - 1) / pt.tw;
       for (int64_t ti = 0; ti < tiles_i; ++ti)
         for (int64_t tj = 0; tj < tiles_j; ++tj) {

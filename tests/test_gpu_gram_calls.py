@@ -98,3 +98,33 @@ def test_rows_over_the_queues(bond, rows, cols):
     K = q.gram(a, b, precision="split_i8", stats=st)
     assert st["tiles"] == -(-rows // 16) * -(-cols // 16) and st["entries"] == rows * cols
     assert torch.equal(K.cpu(), q.gram_block(few, 0, 3, few, 0, 3, precision="split_i8").cpu()[i][:, j])
+
+
+def test_few_pairs_of_the_split_forms():
+    """No more pairs than the workgroup kernel holds at once: split-int8 from
+    bond 17, and any call with a bond above 32, is one launch of that kernel,
+    whose bits are those of a wave per pair."""
+    import paper_2411_09336_amd as q
+    torch = require_gpu()
+    batches = {bond: _batch(4, 13, bond, bond) for bond in (3, 12, 20, 32, 40)}
+    idx = torch.arange(44) % 4   # 990 pairs of the triangle, 1,936 of the block
+    for prec in ("split_bf16", "split_i8"):
+        ref = {}
+        for bond, b in batches.items():
+            b.pack(prec)
+            st = {}
+            K = q.gram(b, precision=prec, stats=st)
+            assert st["block"] == (64 if bond > (16 if prec == "split_i8" else 32) else 32)
+            many = q.gram(b.gather(idx.numpy(), (prec,)), precision=prec, stats=st)
+            assert st["block"] == (64 if bond > 32 else 32)
+            ref[bond] = many[:4, :4]
+            assert torch.equal(K, ref[bond])
+            # every ordered pair, as the triangle of repeats contracts them
+            full = q.gram_block(b, 0, 4, b, 0, 4, precision=prec).cpu()[idx][:, idx]
+            assert torch.equal(torch.triu(many.cpu()), torch.triu(full))
+        for bonds in ((3, 12, 20, 40), (12, 32), (3, 40)):
+            outs = {x: torch.zeros((4, 4), dtype=torch.float64, device="cuda") for x in bonds}
+            q.gram_multi([dict(a=batches[x], b=batches[x], na=4, nb=4, upper_only=True, out=outs[x]) for x in bonds],
+                         precision=prec)
+            for x in bonds:
+                assert torch.equal(outs[x], ref[x])
