@@ -128,3 +128,17 @@ def test_few_pairs_of_the_split_forms():
                          precision=prec)
             for x in bonds:
                 assert torch.equal(outs[x], ref[x])
+
+
+def test_longest_queue_has_its_workgroups():
+    """1 x 400 split-int8 pairs are 25 tiles of 16 over eight queues, of which
+    one has four: 64 pairs, as many as an eighth of the full grid."""
+    import paper_2411_09336_amd as q
+    torch = require_gpu()
+    few = _batch(3, 9, 40, 7)
+    few.pack("split_i8")
+    j = torch.arange(400) % 3
+    st = {}
+    K = q.gram(few.gather([1], ("split_i8",)), few.gather(j.numpy(), ("split_i8",)), precision="split_i8", stats=st)
+    assert st["workgroups"] // 8 >= 64
+    assert torch.equal(K.cpu(), q.gram_block(few, 1, 1, few, 0, 3, precision="split_i8").cpu()[:, j])
