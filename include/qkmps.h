@@ -247,9 +247,11 @@ typedef struct {
   int64_t entries;      /* overlaps contracted (a mirrored entry counts once) */
   int64_t tiles;        /* pair tiles in the work queue                       */
   int32_t workgroups;   /* persistent workgroups launched                     */
-  int32_t tile_side;    /* pair-tile side of the kernel configuration         */
-  int32_t queues;       /* work queues (1, or one per XCD)                    */
-  int32_t block;        /* block size of the FP64 / FP32 forms (32, 64, 128)  */
+  int32_t tile_side;    /* pair-tile side of the configuration (the tiles of  */
+                        /* fewer rows are flatter); several kernels: of the   */
+                        /* one for the largest bonds                          */
+  int32_t queues;       /* work queues of the launch (1, or one per XCD)      */
+  int32_t block;        /* largest bonds of the kernel: 32 (or fewer), 64, 128 */
   double flops;         /* algorithmic flops of the contracted overlaps: 8 per */
                         /* complex MAC of Fig. 2's site updates, counted from  */
                         /* the actual bond dimensions of every pair            */
@@ -328,23 +330,25 @@ qk_status mps_gram_multi(const qk_gram_job *jobs, int32_t n_jobs,
                          qk_precision prec, void *hip_stream,
                          qk_gram_stats *stats);
 
-/* Autotuner of the Gram kernels' tile shapes.  For `prec` and the bond-pad
- * bucket of batch `b` (pads <= 32, <= 64 or <= 128), every valid configuration
- * (block size 32 or 64 for the FP64 / FP32 forms when the pads allow, 128
- * above 64, at bonds up to 32 the same kernel whichever; pair-tile
- * side 8 / 16 / 32, one work queue or one per XCD) computes the symmetric
+/* Autotuner of the Gram kernels' tile shapes.  For `prec` and the kernel that
+ * the bonds of batch `b` take (up to 4 in FP64, 16, 32, 64 or 128), every valid
+ * configuration (pair-tile side 8 / 16 / 32, one work queue or one per XCD;
+ * the block size, 32 or 64 for the FP64 / FP32 forms at pads up to 32, 64, or
+ * 128 above, selects nothing) computes the symmetric
  * Gram of the first min(sample, n) MPS of `b` (one warm-up run, then the
- * best of two timed runs, wall clock including the launch's host work).
+ * best of two timed runs, wall clock including the launch's host work);
+ * configurations that launch alike (at bonds up to 32 all of one tile side)
+ * are timed once.
  * The fastest configuration, if it beats the default by more than 2 % (the
  * timing's run-to-run spread is about 1 %), else the default, is stored for
- * this device, precision and pad bucket and used by every later mps_gram*
+ * this device, precision and kernel and used by every later mps_gram*
  * call on this process; `report` (may be NULL) receives it with its time and
- * the default configuration's time.  Not thread-safe with concurrent Gram calls of the same bucket. */
+ * the default configuration's time.  Not thread-safe with concurrent Gram calls of the same kernel. */
 typedef struct {
   int32_t maxp;           /* block size of the winning configuration        */
   int32_t tile_side;      /* pair-tile side                                  */
   int32_t queues;         /* 1 or one per XCD                                */
-  int32_t n_candidates;   /* configurations timed                            */
+  int32_t n_candidates;   /* valid configurations                            */
   double best_ms;         /* wall time of the winner on the sample           */
   double default_ms;      /* wall time of the default configuration          */
 } qk_tune_report;

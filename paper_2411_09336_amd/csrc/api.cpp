@@ -617,8 +617,7 @@ qk_status mps_gram_block_noalloc(const qk_mps_batch *a, int64_t a0, int64_t na, 
   if (st != QK_OK) return st;
   const int max_pad = std::max(max_pad_of(a), max_pad_of(b));
   std::vector<GramJobDev> jobs{job};
-  st = launch_gram_cfg(jobs, max_pad, prec, current_gram_config(prec, max_pad), stream, nullptr, ws,
-                       kNoAllocScratchBytes);
+  st = launch_gram(jobs, max_pad, prec, stream, nullptr, ws, kNoAllocScratchBytes);
   if (st != QK_OK) return st;
   return ok();
 }
@@ -653,7 +652,7 @@ qk_status mps_gram_autotune(qk_mps_batch *b, qk_precision prec, int64_t sample, 
     double best = 1e300;
     for (int rep = 0; rep < 3; ++rep) {
       const auto t0 = std::chrono::steady_clock::now();
-      qk_status s2 = launch_gram_cfg(jobs, max_pad, prec, c, stream);
+      qk_status s2 = launch_gram(jobs, max_pad, prec, stream, nullptr, nullptr, 0, &c);
       if (s2 != QK_OK) return s2;
       QK_HIP_CHECK(hipStreamSynchronize(stream));
       const double dt = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
@@ -662,14 +661,22 @@ qk_status mps_gram_autotune(qk_mps_batch *b, qk_precision prec, int64_t sample, 
     ms = best;
     return QK_OK;
   };
-  GramConfig best_cfg = default_gram_config(prec, max_pad);
+  const int kernel = st == QK_OK ? gram_kernel_of(job, prec) : 0;
+  GramConfig best_cfg = default_gram_config(prec, kernel);
   double default_ms = 0.0, best_ms = 1e300;
-  const auto cands = gram_config_candidates(prec, max_pad);
+  const auto cands = gram_config_candidates(prec, kernel, max_pad);
   if (st == QK_OK) st = run_ms(best_cfg, default_ms);
   best_ms = default_ms;
   GramConfig fastest = best_cfg;
   double fastest_ms = default_ms;
+  // configurations that launch alike are timed once: the shortest of several
+  // runs of one launch would be taken for a faster configuration
+  std::vector<GramConfig> timed{best_cfg};
   for (size_t k = 0; k < cands.size() && st == QK_OK; ++k) {
+    if (std::any_of(timed.begin(), timed.end(),
+                    [&](const GramConfig &c) { return gram_configs_alike(c, cands[k], kernel); }))
+      continue;
+    timed.push_back(cands[k]);
     double ms = 0.0;
     st = run_ms(cands[k], ms);
     if (st == QK_OK && ms < fastest_ms) {
@@ -686,7 +693,7 @@ qk_status mps_gram_autotune(qk_mps_batch *b, qk_precision prec, int64_t sample, 
   }
   dev_free(al, K, stream, true);
   if (st != QK_OK) return st;
-  store_gram_config(prec, max_pad, best_cfg);
+  store_gram_config(prec, kernel, best_cfg);
   if (report) {
     report->maxp = best_cfg.maxp;
     report->tile_side = best_cfg.tile_side;

@@ -2067,6 +2067,11 @@ size_t lds_bytes() {
 // many workgroups as tiles, so every queue has some.
 int queues_of(const GramConfig &cfg, int64_t n_tiles) { return n_tiles < cfg.queues ? 1 : cfg.queues; }
 
+// What a launch took.
+struct LaunchShape {
+  int workgroups = 0, queues = 1;
+};
+
 // A workgroup for every pair of the longest queue, as far as the device holds
 // them: of several queues one can have a tile more than the others, and its
 // pairs run at once only if its share of the grid is as large.  split-int8,
@@ -2094,7 +2099,7 @@ qk_status block_residents(int64_t *n) {
 template <int PREC, int MAXP>
 qk_status launch_one(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int64_t n_tiles,
                      unsigned long long *counters, const GramConfig &cfg, int th, int tw, hipStream_t stream,
-                     int *grid_out) {
+                     LaunchShape *shape) {
   int64_t grid = 0;
   const qk_status st = block_residents<PREC, MAXP>(&grid);
   if (st != QK_OK) return st;
@@ -2104,7 +2109,7 @@ qk_status launch_one(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int6
                      (lds_bytes<PREC, MAXP>()), stream, jobs_dev, tiles_dev,
                      n_tiles, nq, th, tw, counters);
   QK_HIP_CHECK(hipGetLastError());
-  *grid_out = int(grid);
+  *shape = LaunchShape{int(grid), nq};
   return QK_OK;
 }
 
@@ -2147,7 +2152,7 @@ __global__ __launch_bounds__(kWideThreads, 1) void gram_wide_kernel(const GramJo
 template <int PREC>
 qk_status launch_wide(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int64_t n_tiles,
                       unsigned long long *counters, const GramConfig &cfg, int th, int tw, const DevAlloc &al,
-                      hipStream_t stream, int *grid_out) {
+                      hipStream_t stream, LaunchShape *shape) {
   int dev = 0, cus = 256;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -2168,7 +2173,7 @@ qk_status launch_wide(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) st = fail(QK_EDEVICE, std::string("Gram kernel launch -> ") + hipGetErrorString(e));
   dev_free(al, es, stream, true);
-  *grid_out = int(grid);
+  *shape = LaunchShape{int(grid), nq};
   return st;
 }
 
@@ -2215,7 +2220,7 @@ qk_status noalloc_scratch(void **ptr) {
 // registers for a second wave per SIMD, so larger bonds take a workgroup.
 enum GramKernel { KERNEL_QUAD = 0, KERNEL_WAVE16, KERNEL_WAVE32, KERNEL_BLOCK, KERNEL_WIDE, KERNEL_KINDS };
 
-static int kernel_of(const GramJobDev &J, qk_precision prec) {
+int gram_kernel_of(const GramJobDev &J, qk_precision prec) {
   if (prec == QK_FP64 && J.max_bond <= 4) return KERNEL_QUAD;
   if (J.max_bond <= 32) return J.max_bond <= 16 ? KERNEL_WAVE16 : KERNEL_WAVE32;
   return J.max_pad <= 64 ? KERNEL_BLOCK : KERNEL_WIDE;
@@ -2241,7 +2246,7 @@ static int64_t pairs_of(const GramJobDev &J, int64_t most) {
 // 0.59 ms, split-BF16 1.46 -> 0.84.
 static qk_status kernels_of(const std::vector<GramJobDev> &jobs, qk_precision prec, std::vector<int> *kinds) {
   kinds->clear();
-  for (const GramJobDev &J : jobs) kinds->push_back(kernel_of(J, prec));
+  for (const GramJobDev &J : jobs) kinds->push_back(gram_kernel_of(J, prec));
   if (prec != QK_SPLIT_BF16 && prec != QK_SPLIT_I8) return QK_OK;
   const int from = prec == QK_SPLIT_I8 ? KERNEL_WAVE32 : KERNEL_BLOCK;
   const auto [least, most] = std::minmax_element(kinds->begin(), kinds->end());
@@ -2257,7 +2262,7 @@ static qk_status kernels_of(const std::vector<GramJobDev> &jobs, qk_precision pr
 
 template <int PREC, int NT>
 static qk_status launch_wave(const GramJobDev *jobs_dev, const GramTile *tiles_dev, int64_t n_tiles,
-                             unsigned long long *counters, int th, int tw, hipStream_t stream, int *grid_out) {
+                             unsigned long long *counters, int th, int tw, hipStream_t stream, LaunchShape *shape) {
   int dev = 0, cus = 256;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -2268,7 +2273,7 @@ static qk_status launch_wave(const GramJobDev *jobs_dev, const GramTile *tiles_d
   const int64_t grid = std::min<int64_t>(int64_t(cus) * std::max(per_cu, 1), units);
   hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(64), 0, stream, jobs_dev, tiles_dev, units, th, tw, counters);
   QK_HIP_CHECK(hipGetLastError());
-  *grid_out = int(grid);
+  *shape = LaunchShape{int(grid), 1};
   return QK_OK;
 }
 
@@ -2306,19 +2311,20 @@ qk_status upload(void *dst, const void *src, size_t bytes, hipStream_t stream) {
   return QK_OK;
 }
 
-qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs, int max_pad, qk_precision prec,
-                          const GramConfig &cfg, hipStream_t stream, qk_gram_stats *stats, void *ws_given,
-                          size_t ws_cap) {
+qk_status launch_gram(const std::vector<GramJobDev> &jobs, int max_pad, qk_precision prec, hipStream_t stream,
+                      qk_gram_stats *stats, void *ws_given, size_t ws_cap, const GramConfig *tuned) {
   if (max_pad > kWideP) return fail(QK_ENOTSUP, "Gram kernels support bond pads up to 128");
   if (max_pad > 64 && prec != QK_FP64 && prec != QK_FP32)
     return fail(QK_ENOTSUP, "the split forms support bond pads up to 64");
   if (max_pad > 64 && ws_given)
     return fail(QK_ENOTSUP, "the allocation-free Gram supports bond pads up to 64");
-  if (cfg.maxp < max_pad) return fail(QK_EINVAL, "tile configuration smaller than the batch's bond pads");
-  const int side = cfg.tile_side;
   std::vector<int> kinds;
-  const qk_status ks = kernels_of(jobs, prec, &kinds);
-  if (ks != QK_OK) return ks;
+  if (tuned) {   // a trial of the jobs' own kernels
+    for (const GramJobDev &J : jobs) kinds.push_back(gram_kernel_of(J, prec));
+  } else {
+    const qk_status ks = kernels_of(jobs, prec, &kinds);
+    if (ks != QK_OK) return ks;
+  }
   // One launch per kernel kind that the jobs need: a pair's bits do not
   // depend on the jobs it is launched with.  Tiles hold side * side entries;
   // a kind whose jobs have fewer than `side` rows takes flatter ones, and
@@ -2331,17 +2337,22 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs, int max_pad, qk_p
     int64_t n_tiles = 0;
     int th = 0, tw = 0;
     size_t counters = 0;   // index of the part's block of counters
+    GramConfig cfg;
   } parts[KERNEL_KINDS];
   size_t n_parts = 0;
+  int last = 0;   // the kernel for the largest bonds in use
   std::vector<GramTile> tiles;
   for (int kind = 0; kind < KERNEL_KINDS; ++kind) {
     Part &pt = parts[kind];
+    if (std::find(kinds.begin(), kinds.end(), kind) == kinds.end()) continue;
+    pt.cfg = tuned ? *tuned : current_gram_config(prec, kind);
+    const int side = pt.cfg.tile_side;
     int64_t rows = 0;
     for (size_t k = 0; k < jobs.size(); ++k)
       if (kinds[k] == kind) rows = std::max(rows, jobs[k].na);
     pt.th = side;
     while (pt.th > 1 && pt.th / 2 >= rows) pt.th /= 2;
-    pt.tw = cfg.queues > 1 && (kind == KERNEL_BLOCK || kind == KERNEL_WIDE) ? side : side * side / pt.th;
+    pt.tw = pt.cfg.queues > 1 && (kind == KERNEL_BLOCK || kind == KERNEL_WIDE) ? side : side * side / pt.th;
     pt.tile0 = tiles.size();
     for (size_t k = 0; k < jobs.size(); ++k) {
       const GramJobDev &J = jobs[k];
@@ -2359,12 +2370,15 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs, int max_pad, qk_p
         }
     }
     pt.n_tiles = int64_t(tiles.size() - pt.tile0);
-    if (pt.n_tiles > 0) pt.counters = n_parts++;
+    if (pt.n_tiles > 0) {
+      pt.counters = n_parts++;
+      last = kind;
+    }
   }
   if (stats) {
     stats->tiles = int64_t(tiles.size());
-    stats->tile_side = side;
-    stats->queues = cfg.queues;
+    stats->tile_side = parts[last].cfg.tile_side;
+    stats->queues = 0;
     stats->block = parts[KERNEL_WIDE].n_tiles ? kWideP : parts[KERNEL_BLOCK].n_tiles ? 64 : kPadQuantum;
     stats->workgroups = 0;
     stats->kernel_ms = 0.0;
@@ -2380,7 +2394,8 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs, int max_pad, qk_p
   const size_t ws_bytes = cbytes + jbytes + tbytes;
   if (ws_given && ws_bytes > ws_cap)
     return fail(QK_EINVAL, "the Gram work queue needs " + std::to_string(ws_bytes) + " bytes (" +
-                               std::to_string(n_tiles) + " pair tiles of side " + std::to_string(side) +
+                               std::to_string(n_tiles) + " pair tiles of side " +
+                               std::to_string(parts[last].cfg.tile_side) +
                                "), above the " + std::to_string(ws_cap) + "-byte scratch");
   std::vector<uint8_t> host(ws_bytes, 0);
   std::memcpy(host.data() + cbytes, jobs.data(), jbytes);
@@ -2404,8 +2419,8 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs, int max_pad, qk_p
     if (pt.n_tiles == 0) continue;
     auto *counters = reinterpret_cast<unsigned long long *>(ws + kGramCounterBytes * pt.counters);
     auto *tiles_dev = reinterpret_cast<GramTile *>(ws + cbytes + jbytes) + pt.tile0;
-    int wgs = 0;
-    auto wave = [&](auto launch) { return launch(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.th, pt.tw, stream, &wgs); };
+    LaunchShape shape;
+    auto wave = [&](auto launch) { return launch(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.th, pt.tw, stream, &shape); };
     if (kind == KERNEL_QUAD)
       st = wave(launch_wave<QK_FP64, 0>);
     else if (kind == KERNEL_WAVE16)
@@ -2420,17 +2435,18 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs, int max_pad, qk_p
                                    : wave(launch_wave<QK_SPLIT_I8, 2>);
     else if (kind == KERNEL_WIDE)
       st = prec == QK_FP64
-               ? launch_wide<QK_FP64>(jobs_dev, tiles_dev, pt.n_tiles, counters, cfg, pt.th, pt.tw, al, stream, &wgs)
-               : launch_wide<QK_FP32>(jobs_dev, tiles_dev, pt.n_tiles, counters, cfg, pt.th, pt.tw, al, stream, &wgs);
+               ? launch_wide<QK_FP64>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.cfg, pt.th, pt.tw, al, stream, &shape)
+               : launch_wide<QK_FP32>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.cfg, pt.th, pt.tw, al, stream, &shape);
     else if (prec == QK_FP64)
-      st = launch_one<QK_FP64, 64>(jobs_dev, tiles_dev, pt.n_tiles, counters, cfg, pt.th, pt.tw, stream, &wgs);
+      st = launch_one<QK_FP64, 64>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.cfg, pt.th, pt.tw, stream, &shape);
     else if (prec == QK_FP32)
-      st = launch_one<QK_FP32, 64>(jobs_dev, tiles_dev, pt.n_tiles, counters, cfg, pt.th, pt.tw, stream, &wgs);
+      st = launch_one<QK_FP32, 64>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.cfg, pt.th, pt.tw, stream, &shape);
     else if (prec == QK_SPLIT_BF16)
-      st = launch_one<QK_SPLIT_BF16, 64>(jobs_dev, tiles_dev, pt.n_tiles, counters, cfg, pt.th, pt.tw, stream, &wgs);
+      st = launch_one<QK_SPLIT_BF16, 64>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.cfg, pt.th, pt.tw, stream, &shape);
     else
-      st = launch_one<QK_SPLIT_I8, 64>(jobs_dev, tiles_dev, pt.n_tiles, counters, cfg, pt.th, pt.tw, stream, &wgs);
-    grid += wgs;
+      st = launch_one<QK_SPLIT_I8, 64>(jobs_dev, tiles_dev, pt.n_tiles, counters, pt.cfg, pt.th, pt.tw, stream, &shape);
+    grid += shape.workgroups;
+    if (stats) stats->queues = std::max(stats->queues, shape.queues);
   }
   if (st == QK_OK && stats && hipEventRecord(ev1, stream) != hipSuccess) st = fail(QK_EDEVICE, "event record failed");
   if (!ws_given) dev_free(al, ws, stream, true);
@@ -2448,30 +2464,31 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs, int max_pad, qk_p
 
 
 // ------------------------------------------------------------------------
-// Kernel configurations and the autotuner.  A configuration is the block
-// size of the plain forms (32, 64, or 128 with E in global scratch), the pair-tile side and the number of
-// work queues.  Defaults were chosen by measurement on 165-site chi = 64
-// batches; mps_gram_autotune times every valid configuration on a sample of
-// the caller's batch and stores the fastest per (device, form, pad bucket).
+// Kernel configurations and the autotuner.  A configuration is the pair-tile
+// side and the number of work queues (the kernels for bonds up to 32 have one);
+// its block size (64, or 128 above; 32 or 64 at pads up to 32) names no other
+// kernel any more.  Defaults were chosen by measurement on 165-site chi = 64
+// batches; mps_gram_autotune times every configuration that launches
+// differently on a sample of the caller's batch and stores the fastest per
+// (device, form, kernel): a pair of bond 2 and one of bond 32 differ in time
+// by a factor of ten, and want tiles of other sizes.
 
 namespace {
 std::mutex g_tune_mu;
 std::map<std::tuple<int, int, int>, GramConfig> g_tuned;
-
-int pad_bucket(int max_pad) { return max_pad <= 32 ? 32 : max_pad <= 64 ? 64 : 128; }
 }  // namespace
 
-GramConfig default_gram_config(qk_precision prec, int max_pad) {
+GramConfig default_gram_config(qk_precision prec, int kernel) {
   GramConfig c;
-  c.maxp = max_pad > 64 ? kWideP : 64;
+  c.maxp = kernel == KERNEL_WIDE ? kWideP : 64;
   c.tile_side = kDefaultTileSide;
   c.queues = prec == QK_SPLIT_I8 ? kQueues : 1;
   return c;
 }
 
-std::vector<GramConfig> gram_config_candidates(qk_precision prec, int max_pad) {
+std::vector<GramConfig> gram_config_candidates(qk_precision prec, int kernel, int max_pad) {
   std::vector<GramConfig> out;
-  std::vector<int> maxps{max_pad > 64 ? kWideP : 64};
+  std::vector<int> maxps{kernel == KERNEL_WIDE ? kWideP : 64};
   if ((prec == QK_FP64 || prec == QK_FP32) && max_pad <= 32) maxps.push_back(32);
   for (int mp : maxps)
     for (int side : {8, 16, 32})
@@ -2485,29 +2502,29 @@ std::vector<GramConfig> gram_config_candidates(qk_precision prec, int max_pad) {
   return out;
 }
 
-GramConfig current_gram_config(qk_precision prec, int max_pad) {
-  int dev = 0;
-  (void)hipGetDevice(&dev);
-  std::lock_guard<std::mutex> lk(g_tune_mu);
-  auto it = g_tuned.find(std::make_tuple(dev, int(prec), pad_bucket(max_pad)));
-  return it != g_tuned.end() ? it->second : default_gram_config(prec, max_pad);
+bool gram_configs_alike(const GramConfig &a, const GramConfig &b, int kernel) {
+  return a.tile_side == b.tile_side &&
+         (a.queues == b.queues || (kernel != KERNEL_BLOCK && kernel != KERNEL_WIDE));
 }
 
-void store_gram_config(qk_precision prec, int max_pad, const GramConfig &c) {
+GramConfig current_gram_config(qk_precision prec, int kernel) {
   int dev = 0;
   (void)hipGetDevice(&dev);
   std::lock_guard<std::mutex> lk(g_tune_mu);
-  g_tuned[std::make_tuple(dev, int(prec), pad_bucket(max_pad))] = c;
+  auto it = g_tuned.find(std::make_tuple(dev, int(prec), kernel));
+  return it != g_tuned.end() ? it->second : default_gram_config(prec, kernel);
+}
+
+void store_gram_config(qk_precision prec, int kernel, const GramConfig &c) {
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  std::lock_guard<std::mutex> lk(g_tune_mu);
+  g_tuned[std::make_tuple(dev, int(prec), kernel)] = c;
 }
 
 void clear_gram_configs() {
   std::lock_guard<std::mutex> lk(g_tune_mu);
   g_tuned.clear();
-}
-
-qk_status launch_gram(const std::vector<GramJobDev> &jobs, int max_pad, qk_precision prec, hipStream_t stream,
-                      qk_gram_stats *stats) {
-  return launch_gram_cfg(jobs, max_pad, prec, current_gram_config(prec, max_pad), stream, stats);
 }
 
 // ------------------------------------------------------------------------

@@ -173,21 +173,20 @@ struct GramJobDev {
   int32_t max_bond, max_pad;       // over both batches
 };
 
-// Gram kernel configuration: block size of the plain forms (32, 64 or 128), pair
-// tile side, number of work queues (1, or one per XCD).
+// Gram kernel configuration: pair tile side and number of work queues (1, or
+// one per XCD); maxp is the block size that the autotuner reports.
 struct GramConfig {
   int maxp = 64;
   int tile_side = 16;
   int queues = 1;
 };
 
-qk_status launch_gram(const std::vector<GramJobDev> &jobs, int max_pad,
-                      qk_precision prec, hipStream_t stream, qk_gram_stats *stats = nullptr);
 // ws / ws_cap: caller-provided workspace for the work queue (nullptr: drawn
-// from the device's allocator for the launch).
-qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs, int max_pad,
-                          qk_precision prec, const GramConfig &cfg, hipStream_t stream,
-                          qk_gram_stats *stats = nullptr, void *ws = nullptr, size_t ws_cap = 0);
+// from the device's allocator for the launch).  tuned: a configuration on
+// trial, in place of the stored or default one of each kernel.
+qk_status launch_gram(const std::vector<GramJobDev> &jobs, int max_pad, qk_precision prec, hipStream_t stream,
+                      qk_gram_stats *stats = nullptr, void *ws = nullptr, size_t ws_cap = 0,
+                      const GramConfig *tuned = nullptr);
 
 // Scratch of the allocation-free Gram entry point: a static device array of
 // kNoAllocScratchBytes per device.  noalloc_scratch returns its address on
@@ -195,10 +194,13 @@ qk_status launch_gram_cfg(const std::vector<GramJobDev> &jobs, int max_pad,
 constexpr size_t kNoAllocScratchBytes = size_t(8) << 20;
 constexpr int kMaxScratchDevices = 64;
 qk_status noalloc_scratch(void **ptr);
-GramConfig default_gram_config(qk_precision prec, int max_pad);
-GramConfig current_gram_config(qk_precision prec, int max_pad);
-std::vector<GramConfig> gram_config_candidates(qk_precision prec, int max_pad);
-void store_gram_config(qk_precision prec, int max_pad, const GramConfig &c);
+// Kernel of a job by its bonds and pads, and the configurations of a kernel.
+int gram_kernel_of(const GramJobDev &J, qk_precision prec);
+GramConfig default_gram_config(qk_precision prec, int kernel);
+GramConfig current_gram_config(qk_precision prec, int kernel);
+std::vector<GramConfig> gram_config_candidates(qk_precision prec, int kernel, int max_pad);
+bool gram_configs_alike(const GramConfig &a, const GramConfig &b, int kernel);   // the same launch
+void store_gram_config(qk_precision prec, int kernel, const GramConfig &c);
 void clear_gram_configs();
 
 // Simulation: the step list of a circuit under a bond cap and cutoff, with

@@ -142,3 +142,36 @@ def test_longest_queue_has_its_workgroups():
     K = q.gram(few.gather([1], ("split_i8",)), few.gather(j.numpy(), ("split_i8",)), precision="split_i8", stats=st)
     assert st["workgroups"] // 8 >= 64
     assert torch.equal(K.cpu(), q.gram_block(few, 1, 1, few, 0, 3, precision="split_i8").cpu()[:, j])
+
+
+def test_tuned_choice_is_a_different_launch_of_its_kernel():
+    """The tuner chooses among launches that differ: at bonds up to 32, whose
+    kernels have one queue and one block, tile sides alone; and a choice made
+    for one kernel leaves the others alone."""
+    import paper_2411_09336_amd as q
+    torch = require_gpu()
+    rng = np.random.default_rng(11)
+    # 33 states: a triangle that sides of 8, 16 and 32 fill differently
+    by_bond = {}
+    for bond in (2, 12, 32, 40):
+        few = _batch(3, 13, bond, bond)
+        by_bond[bond] = few.gather(rng.integers(0, 3, 33))
+    try:
+        for prec in ("fp64", "fp32", "split_bf16", "split_i8"):
+            default = (64, 16, 8 if prec == "split_i8" else 1)
+            st = {}
+            for bond in (32, 40):
+                rep = q.autotune(by_bond[bond], prec, sample=33)
+                chosen = (rep["maxp"], rep["tile_side"], rep["queues"])
+                print(prec, bond, chosen, flush=True)
+                assert rep["n_candidates"] == (12 if prec in ("fp64", "fp32") and bond <= 32 else 6)
+                if chosen != default and bond <= 32:
+                    assert rep["maxp"] == 64 and rep["queues"] == 1 and rep["tile_side"] != 16
+                q.gram(by_bond[bond], precision=prec, stats=st)
+                assert st["tile_side"] == rep["tile_side"]
+                assert st["queues"] == (1 if bond <= 32 or st["tiles"] < 8 else rep["queues"])
+            for bond in (2, 12) if prec == "fp64" else (12,):
+                q.gram(by_bond[bond], precision=prec, stats=st)
+                assert st["tile_side"] == 16 and st["queues"] == 1
+    finally:
+        q.autotune_reset()
