@@ -300,7 +300,7 @@ qk_status mps_gram_block(const qk_mps_batch *a, int64_t a0, int64_t na,
  * before any launch.  QK_EINVAL,
  * before any launch, when the work queue does not fit the array: with the
  * default pair tiles of side 16 that is about 520,000 tiles, e.g. a
- * symmetric Gram of up to ~16,000 MPS.  A queue of up to 21 KB (a few hundred
+ * symmetric Gram of up to ~16,000 MPS.  A queue of up to 21 KB (about 1,300
  * tiles) travels in kernel arguments, so the call can be recorded into a HIP
  * graph; a larger one is copied and waited for.  Every call on a device uses that
  * device's one array: calls that overlap in time on one device (other

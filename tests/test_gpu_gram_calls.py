@@ -175,3 +175,25 @@ def test_tuned_choice_is_a_different_launch_of_its_kernel():
                 assert st["tile_side"] == 16 and st["queues"] == 1
     finally:
         q.autotune_reset()
+
+
+# One kernel argument block carries 3,584 bytes: 512 of counters, a job of 144
+# and 183 tiles; six of them 1,303 tiles, beyond which the queue is copied.
+@pytest.mark.parametrize("rows,cols,tiles", [(48, 976, 183), (128, 368, 184), (224, 1488, 1302), (128, 2608, 1304),
+                                             (800, 800, 2500)])
+def test_queues_by_arguments_and_by_copy(rows, cols, tiles):
+    """Work queues just within and beyond one argument block and all of them,
+    drawn from the allocator and in the allocation-free scratch."""
+    import paper_2411_09336_amd as q
+    torch = require_gpu()
+    few = _batch(7, 4, 4, 5)
+    idx = torch.arange(max(rows, cols)) % 7
+    b = few.gather(idx.numpy())
+    st = {}
+    K = q.gram_block(b, 0, rows, b, 0, cols, stats=st)
+    assert st["tiles"] == tiles
+    ref = q.gram_block(few, 0, 7, few, 0, 7).cpu()
+    assert torch.equal(K.cpu(), ref[idx[:rows]][:, idx[:cols]])
+    out = torch.zeros_like(K)
+    q.gram_block_noalloc(b, 0, rows, b, 0, cols, out)
+    assert torch.equal(out, K)
