@@ -169,3 +169,26 @@ def test_odd_numbers_of_column_blocks(chi):
     """Both neighbouring bonds above 64: 65, 67 and 127 blocks of two columns
     (one block of a round has no partner)."""
     test_steps_next_to_bonds_above_64(16, 6, chi, 0)
+
+
+@pytest.mark.parametrize("m,d,chi,routing", [(15, 5, 70, 0), (16, 5, 96, 1), (16, 6, 128, 0), (16, 6, 67, 0)])
+def test_every_circuit_next_to_bonds_above_64(m, d, chi, routing):
+    """As above with nothing left out: no cut of these circuits is degenerate,
+    for the oracle or the device, so every bond, weight and state is compared,
+    and the kernel matrix."""
+    import paper_2411_09336_amd as q
+    torch = require_gpu()
+    X = sd.make_uniform(2, m, seed=m + d)
+    b = q.simulate(torch.tensor(X, device="cuda"), q.CircuitSpec(m, d, 2, 2.0, 2.0, routing), chi, 1e-12)
+    ref = [omps.simulate(x, d, 2, chi, 1e-12, 2.0, 2.0, routing=routing) for x in X]
+    disc, deg = b.trunc_stats()
+    assert [r.degenerate_cuts for r in ref] == [0, 0] and list(deg) == [0, 0]
+    assert max(r.max_bond_seen for r in ref) > 64
+    dims = b.bond_dims()
+    for i, r in enumerate(ref):
+        assert list(dims[i]) == r.bond_dims
+        assert fidelity(b.export(i), r.tensors) > 1 - 1e-10
+        assert abs(disc[i] - r.discarded) <= 1e-9 * max(1.0, r.discarded)
+    K = q.gram(b).cpu().numpy()
+    # a fidelity within 1e-10 of 1 leaves an overlap of magnitude at most 1 within 2e-5
+    assert np.abs(K - ogram.gram([r.tensors for r in ref])).max() < 4e-5
