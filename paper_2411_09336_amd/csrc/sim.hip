@@ -1245,8 +1245,9 @@ __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t c
   if (tid == 0) dims[p + 1] = k;
 }
 
-// Two-site step of circuit ci whose Jacobi matrix has more than 128 rows and
-// columns (both neighbouring bonds above 64; one 1024-thread workgroup).  The same
+// Two-qubit gate of circuit ci whose Jacobi matrix has more than 128 rows and
+// columns (both neighbouring bonds above 64; one 1024-thread workgroup); a
+// centre move has at most 128 columns, the cap of its bond.  The same
 // operation as svd_step -- pair product, theta, one-sided Jacobi on the
 // columns, truncation by Eq. (8) with the bond cap, isometric factor from the
 // normalised columns and the other factor as an exact projection -- with the
@@ -1299,13 +1300,8 @@ __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, in
     const double phi = P.coef_xx * (1.0 - xi) * (1.0 - xj);
     sincos(0.5 * phi, &sg, &cg);
   }
-  const bool right = (st.mode == GATE_RIGHT || st.mode == MOVE_RIGHT);
-  const bool gate = (st.mode == GATE_RIGHT || st.mode == GATE_LEFT);
-  int nr, nc, ncs;
-  if (st.mode == GATE_RIGHT) { nr = 2 * Dp; nc = 2 * Dn; ncs = nc; }
-  else if (st.mode == GATE_LEFT) { nr = 2 * Dn; nc = 2 * Dp; ncs = nc; }
-  else if (st.mode == MOVE_RIGHT) { nr = 2 * Dp; nc = Dm; ncs = 2 * Dn; }
-  else { nr = 2 * Dn; nc = Dm; ncs = 2 * Dp; }
+  const bool right = st.mode == GATE_RIGHT;
+  const int nr = 2 * (right ? Dp : Dn), nc = 2 * (right ? Dn : Dp);
 
   // ---------------------------------------------------------- pair product -> W
   // P[(s', a)][(t', b)] = sum_c A_p[s'][a][c] A_{p+1}[t'][c][b]
@@ -1335,43 +1331,24 @@ __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, in
     }
   __syncthreads();
   // ---------------------------------------------------------- projection source -> S
-  // gates: theta (absorb right) or theta^H (absorb left), which is also the
-  // Jacobi matrix; centre moves: the identity theta P or its adjoint
-  for (int e = tid; e < nr * ncs; e += kSvThreads) {
-    const int r = e / ncs, c = e % ncs;
-    double2 v;
-    if (st.mode == GATE_RIGHT) v = theta_from_pair(W, st.op, cg, sg, Dp, Dn, r / Dp, r % Dp, c / Dn, c % Dn, kWideN);
-    else if (st.mode == GATE_LEFT)
-      v = cconj(theta_from_pair(W, st.op, cg, sg, Dp, Dn, c / Dp, c % Dp, r / Dn, r % Dn, kWideN));
-    else if (st.mode == MOVE_RIGHT) v = W[size_t(r) * kWideN + c];
-    else v = cconj(W[size_t(c) * kWideN + r]);
-    S[size_t(r) * kWideN + c] = v;
+  // theta (absorb right) or theta^H (absorb left), which is also the Jacobi
+  // matrix
+  for (int e = tid; e < nr * nc; e += kSvThreads) {
+    const int r = e / nc, c = e % nc;
+    S[size_t(r) * kWideN + c] =
+        right ? theta_from_pair(W, st.op, cg, sg, Dp, Dn, r / Dp, r % Dp, c / Dn, c % Dn, kWideN)
+              : cconj(theta_from_pair(W, st.op, cg, sg, Dp, Dn, c / Dp, c % Dp, r / Dn, r % Dn, kWideN));
   }
   __syncthreads();
   // ---------------------------------------------------------- Jacobi matrix -> W (column-major)
-  const int NC = nc + (nc & 1);
-  for (int e = tid; e < NC * kWideN; e += kSvThreads) {
-    const int c = e / kWideN, r = e % kWideN;
-    double2 v = make_double2(0.0, 0.0);
-    if (r < nr && c < nc) {
-      if (gate) v = S[size_t(r) * kWideN + c];
-      else if (st.mode == MOVE_RIGHT) v = Ap[(size_t(r / Dp) * Pp + r % Dp) * Pm + c];
-      else v = cconj(Aq[(size_t(r / Dn) * Pm + c) * Pn + r % Dn]);
-    }
-    W[size_t(c) * kWideN + r] = v;
-  }
-  // ||M||_F^2 (invariant under the rotations), from the values just written
+  // with ||M||_F^2 (invariant under the rotations)
   {
     double t = 0.0;
-    for (int e = tid; e < NC * kWideN; e += kSvThreads) {
+    for (int e = tid; e < nc * kWideN; e += kSvThreads) {
       const int c = e / kWideN, r = e % kWideN;
-      if (r < nr && c < nc) {
-        double2 v;
-        if (gate) v = S[size_t(r) * kWideN + c];
-        else if (st.mode == MOVE_RIGHT) v = Ap[(size_t(r / Dp) * Pp + r % Dp) * Pm + c];
-        else v = cconj(Aq[(size_t(r / Dn) * Pm + c) * Pn + r % Dn]);
-        t = fma(v.x, v.x, fma(v.y, v.y, t));
-      }
+      const double2 v = r < nr ? S[size_t(r) * kWideN + c] : make_double2(0.0, 0.0);
+      W[size_t(c) * kWideN + r] = v;
+      t = fma(v.x, v.x, fma(v.y, v.y, t));
     }
     t = wave_sum(t);
     if (lane == 0) w_part[wave] = t;
@@ -1584,43 +1561,37 @@ __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, in
     double total = 0.0;
 #pragma unroll 1
     for (int u = kWideN - 1; u >= 0; --u) total += w_sorted[u];
-    int k;
-    if (gate) {
-      int kcut = nsv;
-      if (P.cutoff > 0.0) {
-        // smallest k with sum_{r >= k} w_r <= cutoff * total
-        double tail = 0.0;
-#pragma unroll 1
-        for (int kk = nsv; kk >= 0; --kk) {
-          if (kk < nsv) tail += w_sorted[kk];
-          if (tail <= P.cutoff * total) kcut = kk;
-          else break;
-        }
-      }
-      k = max(1, min(min(P.chi, kcut), max(nnz, 1)));
-      if (P.gate_split) {
-        const double cmax = fmax(fabs(cg), fabs(sg));
-        const int rg = st.op == OP_RXX ? (fabs(cg) > 1e-12 * cmax ? 1 : 0) + (fabs(sg) > 1e-12 * cmax ? 1 : 0) : 4;
-        k = max(1, min(k, rg * Dm));
-      }
-      k = min(k, st.nr);
-      double kept = 0.0;
-#pragma unroll 1
-      for (int u = k - 1; u >= 0; --u) kept += w_sorted[u];
+    int kcut = nsv;
+    if (P.cutoff > 0.0) {
+      // smallest k with sum_{r >= k} w_r <= cutoff * total
       double tail = 0.0;
 #pragma unroll 1
-      for (int u = kWideN - 1; u >= k; --u) tail += w_sorted[u];
-      const double disc = total > 0.0 ? tail / total : 0.0;
-      w_nrm = kept > 0.0 ? 1.0 / sqrt(kept) : 1.0;
-      cl.disc += disc;
-      cl.maxdisc = fmax(cl.maxdisc, disc);
-      if (k < nsv && w_sorted[0] > 0.0 &&
-          (sqrt(w_sorted[k - 1]) - sqrt(w_sorted[k])) / sqrt(w_sorted[0]) < kDegenerateGap)
-        cl.degen += 1;
-    } else {
-      k = min(max(1, min(nsv, max(nnz, 1))), st.nr);
-      w_nrm = 1.0;
+      for (int kk = nsv; kk >= 0; --kk) {
+        if (kk < nsv) tail += w_sorted[kk];
+        if (tail <= P.cutoff * total) kcut = kk;
+        else break;
+      }
     }
+    int k = max(1, min(min(P.chi, kcut), max(nnz, 1)));
+    if (P.gate_split) {
+      const double cmax = fmax(fabs(cg), fabs(sg));
+      const int rg = st.op == OP_RXX ? (fabs(cg) > 1e-12 * cmax ? 1 : 0) + (fabs(sg) > 1e-12 * cmax ? 1 : 0) : 4;
+      k = max(1, min(k, rg * Dm));
+    }
+    k = min(k, st.nr);
+    double kept = 0.0;
+#pragma unroll 1
+    for (int u = k - 1; u >= 0; --u) kept += w_sorted[u];
+    double tail = 0.0;
+#pragma unroll 1
+    for (int u = kWideN - 1; u >= k; --u) tail += w_sorted[u];
+    const double disc = total > 0.0 ? tail / total : 0.0;
+    w_nrm = kept > 0.0 ? 1.0 / sqrt(kept) : 1.0;
+    cl.disc += disc;
+    cl.maxdisc = fmax(cl.maxdisc, disc);
+    if (k < nsv && w_sorted[0] > 0.0 &&
+        (sqrt(w_sorted[k - 1]) - sqrt(w_sorted[k])) / sqrt(w_sorted[0]) < kDegenerateGap)
+      cl.degen += 1;
     if (!converged) cl.unconv += 1;
     w_k = k;
   }
@@ -1643,7 +1614,7 @@ __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, in
     else Aq[(size_t(r / Dn) * Pm + j) * Pn + r % Dn] = make_double2(vr, -vi);
   }
   // projection: out[j][x] = nrm sum_y conj(U[y][j]) S[y][x]
-  for (int x0 = 0; x0 < ncs; x0 += kSvMaxN)
+  for (int x0 = 0; x0 < nc; x0 += kSvMaxN)
     for (int j0 = 0; j0 < k; j0 += kSvMaxN / 2) {
       double2 acc[T::HROWS][2];
       staged_tile_gemm<kSvMaxN, kSvWaves, T::HROWS>(
@@ -1655,14 +1626,14 @@ __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, in
             const double2 u = W[c * kWideN + y];
             return make_double2(inv * u.x, -inv * u.y);
           },
-          [&](int y, int x) { return x0 + x < ncs ? S[y * kWideN + x0 + x] : make_double2(0.0, 0.0); }, sh, acc);
+          [&](int y, int x) { return x0 + x < nc ? S[y * kWideN + x0 + x] : make_double2(0.0, 0.0); }, sh, acc);
 #pragma unroll
       for (int rr = 0; rr < T::HROWS; ++rr)
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
           const int j = j0 + wave * T::HROWS + rr, x = x0 + 2 * lane + q;
           const double2 v = acc[rr][q];
-          if (j < k && x < ncs) {
+          if (j < k && x < nc) {
             if (right) aq_at(j, x) = make_double2(nrm * v.x, nrm * v.y);
             else ap_at(x, j) = make_double2(nrm * v.x, -nrm * v.y);
           }
