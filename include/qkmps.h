@@ -264,8 +264,8 @@ typedef struct {
  * If b == NULL or b == a the matrix is symmetric: only i <= j is contracted
  * and mirrored (the diagonal is computed, not assumed).
  * `a` and `b` must have the same m.  The precision's packed form is built
- * (and kept) on first use; a call that builds one waits for its stream, so
- * the form can be read on any stream afterwards.  The FP64 and FP32 forms
+ * (and kept) on first use; a call that builds one returns when it is built, so
+ * that it can be read on any stream afterwards.  The FP64 and FP32 forms
  * support bond pads up to 128 (bond dimensions up to 128; above 64 with E in a global scratch
  * slot of 2 x 128 x 128 complex values per workgroup, drawn from the
  * device's allocator for the call), the split forms up to 64: QK_ENOTSUP
