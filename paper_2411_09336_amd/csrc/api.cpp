@@ -344,11 +344,11 @@ static std::vector<int32_t> largest_bonds(const int32_t *dims, int64_t n, int m)
   return bond;
 }
 
-// The simulation allocates for the largest bonds its chi cap allows; once
-// the states are known, the batch is re-laid with the pads of the bonds they
-// reached (pad of the largest bond at each site), so Gram kernels of the
-// plain forms work on blocks that size (bond-2 states: 32-wide pads instead
-// of 64).  Tensors, bond dimensions and statistics are copied unchanged.
+// The simulation allocates for the largest bonds that the circuit's steps can
+// leave under the cap; once the states are known, the batch keeps the largest
+// bond that they reached at each site, by which the Gram kernels are chosen,
+// and is re-laid where its pads shrink.  Tensors, bond dimensions and
+// statistics are copied unchanged.
 static qk_status shrink_to_bonds(qk_mps_batch **pb, hipStream_t stream) {
   qk_mps_batch *b = *pb;
   const int m = b->m;

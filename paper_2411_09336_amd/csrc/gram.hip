@@ -197,7 +197,9 @@ __device__ inline uint32_t mag_bits(float x) { return __float_as_uint(x) & 0x7ff
 // loaded one step of MFMAs ahead (12 of 64 cycles in FP64, longer than an L2
 // hit), and the steps of a site are straight-line code where both bonds take
 // all four (or three) 16-row blocks, so that loads are not serialised by
-// branches.  12,880 pairs of 100 sites at bond 64: FP64 211 -> 117 ms (82
+// branches.  T of all four row blocks is held between the GEMMs beside E': in
+// FP64 192 registers of accumulators, of which 63 registers' worth of other
+// values spill (216 bytes a lane); the matrix cores are 73 % busy.  12,880 pairs of 100 sites at bond 64: FP64 211 -> 117 ms (82
 // algorithmic TFLOP/s; 61 by MFMA count of the 78.6 of the matrix cores),
 // FP32 78.9 -> 55.1 ms for 8,256; bond 45: FP64 37.1 -> 12.9 ms for 2,080.
 constexpr int kPlainBlocks = 4;
@@ -391,7 +393,8 @@ __device__ void overlap_plain(const GramJobDev &J, int64_t ia, int64_t ib, T2 *E
 // are held across the site; FP64 uses three real products per complex one in
 // GEMM1 (three accumulators per E' tile would leave no registers).  Bounds:
 // MFMA issue and, with one pair per CU, the loads of a step from L2, issued
-// one step ahead.  300 pairs of 40 sites at bond 128 (two rounds of the 256
+// one step ahead (FP64: 256 registers and 30 spilled; the matrix cores are 41 %
+// busy over both rounds).  300 pairs of 40 sites at bond 128 (two rounds of the 256
 // CUs): FP64 24.7 -> 15.6 ms, FP32 18.8 -> 9.6 ms; 300 at bond 100: FP64 24.4
 // -> 11.9 ms.
 constexpr int kWideP = 128;
@@ -716,10 +719,10 @@ __device__ inline void overlap_wave(const GramJobDev &J, int64_t ia, int64_t ib,
     V4 En[NT][NT][2];   // E'^T: [ket column block][bra column block]
     // FP32: where every block is filled, one body without branches, whose loads
     // the compiler moves far ahead of their MFMAs (194 registers, two waves per
-    // SIMD).  With a load's wait in front of every eight MFMAs, four waves per
-    // SIMD kept the matrix cores 53 % busy: 12,880 pairs of 50 sites, chi 32,
-    // 6.79 -> 5.19 ms (81 -> 106 TFLOP/s; a large FP32 product reaches 143), and
-    // spilling at four waves 6.3.  FP64 (72 % busy) needs all its registers for
+    // SIMD; the matrix cores are 70 % busy).  With a load's wait in front of
+    // every eight MFMAs, four waves per SIMD kept them about half busy: 12,880
+    // pairs of 50 sites, chi 32, 6.79 -> 5.19 ms (81 -> 106 TFLOP/s; a large FP32
+    // product reaches 143), and spilling at four waves 6.3.  FP64 (73 % busy) needs all its registers for
     // the accumulators of three products: the same body spills (7.5 -> 13.9 ms).
     uint32_t mx;
     if (!k3 && NT > 1 && na == NT && nb == NT && nan == NT && nbn == NT)
@@ -1000,10 +1003,13 @@ __device__ inline void slice_mac(const Sl4 &X, const Sl4 &Y, f32x4 &hi, f32x4 &l
 // the bonds at a site (the chain's ends, bonds 33..63) hold zeros and are left
 // out by wave-uniform branches, which cost nothing where every tile is filled.
 // 5,050 pairs of 14 sites, chi 64: 4.13 -> 2.54 ms; 1,830 of 100 sites, chi 45:
-// 12.05 -> 10.38 ms.  At chi 64 the kernel issues 1.29 PFLOP/s of products,
-// above what a large bf16 matrix product reaches on the card (1.12), so the
-// matrix cores' rate, not the order of the phases, bounds it: slicing in one
-// wave of a SIMD while the other multiplies measured 4 % slower.
+// 12.05 -> 10.38 ms.  At chi 64 the kernel issues 1.29 PFLOP/s of products (a
+// large bf16 matrix product reaches 1.12 on the card), which keeps the matrix
+// cores 53 % busy at 2.32 GHz; other VALU instructions, slicing above all, take
+// 23 % of the issue cycles, and the two waves of a SIMD, whose phases are the
+// same, wait for each other at the barriers for most of the rest (counters of
+// 8,256 pairs of 165 sites).  Slicing in one wave of a SIMD while the other
+// multiplies measured 4 % slower.
 constexpr int kSplitThreads = 512;
 constexpr int kSP = 64;
 
@@ -1441,8 +1447,10 @@ __device__ inline void i8_corrections(const int (&cs)[4], i32x4 (&corr)[4]) {
 // 100 sites, chi 64: 65.4 -> 63.1 ms).
 // Digits of E and T are read one digit ahead of their MFMAs, site digit sums
 // with the fragments a GEMM ahead and offsets a site ahead: 63.1 -> 62.2 ms, so
-// little of what is left is latency: int8 products issue at 2.2 POP/s at the
-// clock of about 2.0 GHz that they leave the card.
+// little of what is left is latency.  What the counters of that case show is
+// that matrix and vector work hardly overlap: MFMAs take 57 % of the cycles and
+// the issue of the other VALU instructions 42 % (590 and 1,750 a wave and site,
+// 33,200 cycles), at a clock of 1.94 GHz against 2.3 to 2.4 of the other kernels.
 // Work split of the int8 kernel: workgroups of four waves, two per CU, each
 // workgroup on its own pair, so the two workgroups of a CU interleave their
 // MFMA and VALU phases.  Wave w owns column block c = w of every 64 x 64
@@ -1683,6 +1691,8 @@ __device__ void overlap_i8(const GramJobDev &J, int64_t ia, int64_t ib, uint8_t 
 // LDS of the wave.  5,050 pairs of 100 sites: split-BF16 30.3 -> 5.8 ms at
 // bond 32 and 1.5 ms at bonds up to 16, split-int8 18.7 -> 8.0 and 2.0 ms
 // (VALU slicing now outweighs the MFMAs, which both carriers hide less).
+// split-int8 spills 67 registers at two tiles (two waves per SIMD) and 13 at
+// one (three).
 __device__ inline double rows_max(double x) {   // over the four lane rows
   auto step = [&](auto sw) {
     const auto lo = sw(__double2loint(x)), hi = sw(__double2hiint(x));

@@ -33,9 +33,10 @@
 // ordering, each pair exchanged after its rotation), so n rounds visit every
 // pair once per sweep and the only data movement is one DPP lane shift each
 // way in every second round.  Each round the partial inner products of the
-// waves go through LDS to a few waves that form the rotation parameters,
-// which all waves then apply; a matrix up to 16 x 16 lies in one wave, which
-// needs neither LDS nor barriers for its rounds.
+// waves go through LDS.  Up to 64 x 64 every wave adds them up and forms the
+// rotations of its own lanes; at 128 four waves form them for all.  A matrix
+// up to 16 x 16 lies in one wave, which needs neither LDS nor barriers for its
+// rounds.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1266,9 +1267,11 @@ __device__ __attribute__((noinline)) void svd_step(const SvParams *Pp, int64_t c
 // two columns meet once per sweep and a round moves each column through L2
 // once for two rotations: single columns made a round of 256 x 256 a transfer
 // of 2 MiB at the 125 bytes a cycle that one CU reaches.
-// 4 points x 16 qubits, d = 5, chi 128 (saturated): 814 -> 664 ms, with the
-// heaviest remaining row as the next pivot and the pair product and projection
-// staged through LDS 617.
+// Whole simulation of 4 points x 16 qubits, d = 5, chi 128, whose bonds
+// saturate (gates with both bonds above 64 are here, those with one of them in
+// svd_step_wide): blocks of two columns 814 -> 664 ms, with the heaviest
+// remaining row as the next pivot and the pair product and projection staged
+// through LDS 617.  Other points take up to 670: their sweeps differ.
 __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, int64_t ci_, const SimStep *stp, int lds) {
   CircuitLds &cl = *lds_at<CircuitLds>(lds);
   const SvParams P = uniform_load(Pq);
@@ -1656,7 +1659,9 @@ __device__ __attribute__((noinline)) void svd_step_stream(const SvParams *Pq, in
 // (row-major, kWideN), and the reflection vectors of a tall M with their
 // factors.
 // With the sweeps streaming the columns from L2 instead (every round of 256 x
-// 128 columns ~7 us): 4 points x 16 qubits, d = 5, chi 128, 594 ms against 270.
+// 128 columns ~7 us): 594 ms against 270 for 4 points x 16 qubits, d = 5, chi
+// 128, on points whose bonds stay below the cap, so that nearly every step next
+// to a bond above 64 has one side within 128.
 struct WideLds {
   double2 vec[kWideN];          // pivot row of a reflection
   double2 dot[8][kSvMaxN];      // partial products row . conj(w)
@@ -1968,7 +1973,8 @@ __device__ __attribute__((noinline)) void svd_step_wide(const SvParams *Pq, int6
 
 // Rz on a run of gate records (Fig. 1a) for circuit ci: A[site][s] *=
 // exp(-/+ i theta / 2), one record per wave.  The records of a run act on
-// distinct sites.
+// distinct sites, but for circuits without two-qubit gates, whose layers are
+// one run: their bonds are 1, so one wave takes the records in order.
 template <int W>
 __device__ inline void rz_run(const SvParams &P, int64_t ci, const qk_gate *recs, int n_recs, double coef_z) {
   const int lane = threadIdx.x & 63;
