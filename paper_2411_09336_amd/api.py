@@ -547,7 +547,8 @@ def gram_block_noalloc(a: MPSBatch, a0: int, na: int, b: MPSBatch, b0: int, nb: 
 
 
 def gram_multi(jobs, precision="fp64", stream=None, stats: Optional[dict] = None):
-    """jobs: list of dicts {a, b, a0, na, b0, nb, upper_only, out} -> one persistent launch."""
+    """jobs: list of dicts {a, b, a0, na, b0, nb, upper_only, out}, in one call
+    (one persistent launch per kernel that the jobs need)."""
     arr = (_Job * len(jobs))()
     for k, j in enumerate(jobs):
         _check_out(j["out"], j["na"], j["nb"], f"jobs[{k}]['out']")
